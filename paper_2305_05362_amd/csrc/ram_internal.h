@@ -45,11 +45,9 @@ struct MeshTab {
     const double *dx = nullptr;
     const double *dxinv = nullptr;
     const double *hinv = nullptr;     // 1 / (centre_{j+1} - centre_j), periodic
-    const double *stc = nullptr;      // [n][2(order+1)]: stencil data, below
     const float *dxf = nullptr;
     const float *dxinvf = nullptr;
     const float *hinvf = nullptr;
-    const float *stcf = nullptr;
     const int32_t *bucket = nullptr;  // largest j with x_j <= x0 + b L / nb
     const double2 *bnext = nullptr;   // per bucket: the next two nodes (or +inf)
     int32_t nb = 0;
@@ -90,7 +88,7 @@ constexpr double kUniformTol = 1e-10;
 
 // Everything the bulk shift needs about source cell c in one record (one
 // cache line in FP32, two in FP64): x_c, 1/dx_c, and the stencil data
-// (offsets and reciprocal denominators, as in MeshTab::stc) in type T.
+// (offsets and reciprocal denominators, below) in type T.
 template <typename T> struct CellRec {
     double xc;
     double dxinv;
@@ -100,10 +98,10 @@ template <typename T> struct CellRec {
 static_assert(sizeof(CellRec<float>) == 64, "one cache line");
 static_assert(sizeof(CellRec<double>) == 112, "FP64 record");
 // Stencil data of source cell c (order p, lo = (p-1)/2), in units of dx_c:
-//   stc[c][a]       = (x_{c-lo+a} - x_c) / dx_c                   a = 0..p
-//   stc[c][p+1+a]   = 1 / prod_{b != a} (stc[c][a] - stc[c][b])
+//   th[a] = (x_{c-lo+a} - x_c) / dx_c                   a = 0..p
+//   rd[a] = 1 / prod_{b != a} (th[a] - th[b])
 // so the Lagrange weight of node a at theta = (xh - x_c)/dx_c is
-//   stc[c][p+1+a] * prod_{b != a} (theta - stc[c][b]).
+//   rd[a] * prod_{b != a} (theta - th[b]).
 
 // Where the rows are.  Uniform batches (n_cols > 0) map tile t to
 // (row = t / tiles_per_row, start = (t % tiles_per_row) * kTile); ragged
@@ -379,7 +377,8 @@ hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
                              hipStream_t stream);
 // Bytes of scratch the shared-mesh tables of an n-cell mesh need.
 size_t mesh_tab_bytes(int64_t n, int order);
-// Build the tables in `mem` (mesh_tab_bytes) and point `tab` at them.
+// Build the tables in `mem` (mesh_tab_bytes) and point `tab` at them, with the
+// uniform-run counts if `uniform`: one launch.
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
                             MeshTab &tab, hipStream_t stream, bool uniform = false);
 hipError_t launch_step(const StepArgs &a, bool f64, int scan, int order,

@@ -4,14 +4,13 @@
 // on tiles of consecutive cells of one row, one workgroup (kBlock threads =
 // four wave64) per tile, with row-major coalesced HBM access.
 //
-//   k_step       bulk shift (Section 3, Steps 1-3), optionally fused with the
-//                residual upwind step (Eq. splitting_second).  Per tile, with
-//                one shifted node per thread:
+//   k_step       bulk shift (Section 3, Steps 1-3) on rows of their own
+//                meshes, optionally fused with the residual upwind step (Eq.
+//                splitting_second).  Per tile:
 //                (A) x~ = x - v0 dt is wrapped into the period and its source
-//                    cell found (Eq. condition_p) -- through the mesh's bucket
-//                    index when the mesh is shared, by binary search when
-//                    every row has its own mesh; the Lagrange weights of the
-//                    node's degree-p stencil stay in registers;
+//                    cell found (Eq. condition_p) by binary search; the
+//                    Lagrange weights of the node's degree-p stencil stay in
+//                    registers;
 //                (B) the tile's source window is staged in LDS as cell masses
 //                    M = Q dx (Eq. Qmass_i) and turned into an exclusive prefix
 //                    (the cumulative integral) by a block scan in FP64,
@@ -42,41 +41,17 @@ using namespace dev;
 
 
 // Lagrange weights of the stencil nodes c-LO .. c-LO+P at xh, in WT.
-// Shared meshes use the per-cell stencil table: node offsets and reciprocal
-// denominators in units of dx_c, so only theta = (xh - x_c)/dx_c is formed in
-// FP64 and every factor is O(1).  Per-row meshes form the weights from the
-// nodes directly.
 template <typename WT, int P>
-__device__ inline void stencil_weights(const double *x, int n, double len,
-                                       const Rows &R, int c, double xh, WT *w)
+__device__ inline void stencil_weights(const double *x, int n, double len, int c, double xh,
+                                       WT *w)
 {
     constexpr int LO = (P - 1) / 2;
-    if (!R.has_tab) {
-        double X[P + 1], wd[P + 1];
+    double X[P + 1], wd[P + 1];
 #pragma unroll
-        for (int a = 0; a <= P; ++a) X[a] = node_x(x, n, len, c - LO + a);
-        lagrange_weights<P>(xh, X, wd);
+    for (int a = 0; a <= P; ++a) X[a] = node_x(x, n, len, c - LO + a);
+    lagrange_weights<P>(xh, X, wd);
 #pragma unroll
-        for (int a = 0; a <= P; ++a) w[a] = (WT)wd[a];
-        return;
-    }
-    const WT *st;
-    if constexpr (std::is_same<WT, double>::value) st = R.tab.stc + c * (2 * (P + 1));
-    else st = R.tab.stcf + c * (2 * (P + 1));
-    const WT th = (WT)((xh - x[c]) * R.tab.dxinv[c]);
-    WT t[P + 1];
-#pragma unroll
-    for (int a = 0; a <= P; ++a) t[a] = th - st[a];
-    // products of all t but one, from prefix and suffix products
-    WT pre[P + 1], suf[P + 1];
-    pre[0] = (WT)1;
-#pragma unroll
-    for (int a = 1; a <= P; ++a) pre[a] = pre[a - 1] * t[a - 1];
-    suf[P] = (WT)1;
-#pragma unroll
-    for (int a = P - 1; a >= 0; --a) suf[a] = suf[a + 1] * t[a + 1];
-#pragma unroll
-    for (int a = 0; a <= P; ++a) w[a] = st[P + 1 + a] * (pre[a] * suf[a]);
+    for (int a = 0; a <= P; ++a) w[a] = (WT)wd[a];
 }
 
 
@@ -146,9 +121,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
     const double s = a.v0[ti.row] * a.dt;
     const double len = x[n] - x[0];
     const int t = threadIdx.x;
-    const bool tab = R.has_tab != 0;
-    const double bsc = tab ? R.tab.scal[0] : 0.0;
-    const double invlen = tab ? R.tab.scal[1] : 1.0 / len;
+    const double invlen = 1.0 / len;
 
     // residual velocity of the faces this thread will need, fetched early
     const TQ *dv = H ? (const TQ *)a.dv + ti.qoff : nullptr;
@@ -159,28 +132,6 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
         dvr[k] = (H && f < nd + 1) ? dv[wrap_small(i0 + f, n)] : (TQ)0;
     }
 
-    // conservative window from the bucket index (shared mesh): the first and
-    // last shifted nodes' buckets, widened by one bucket and the stencil
-    if (tab && t < 2) {
-        int e = t == 0 ? i0 - H : i0 - H + NE - 1;
-        int kx = 0;
-        if (e < 0) { e += n; kx = -1; }
-        while (e >= n) { e -= n; kx += 1; }
-        double xh;
-        int64_t k;
-        shifted_node_inv(x, n, s, e, invlen, len, xh, k);
-        int b = (int)((xh - x[0]) * bsc);
-        b = min(max(b, 0), R.tab.nb - 1);
-        int64_t gb;
-        if (t == 0) {
-            gb = (int64_t)R.tab.bucket[max(b - 1, 0)] + (k + kx) * (int64_t)n;
-            s_wlo = gb - LO - 1;
-        } else {
-            gb = (int64_t)R.tab.bucket[min(b + 2, R.tab.nb - 1)] + (k + kx) * (int64_t)n;
-            if (b + 2 >= R.tab.nb) gb = (int64_t)n + (k + kx) * (int64_t)n;
-            s_whi = gb - LO + P + 2;
-        }
-    }
     if (t == 0) s_flag = 1;
 
     // Per-row meshes: the tile's window from its two end nodes (global
@@ -188,30 +139,23 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
     // LDS, where every node finds its cell and its stencil nodes.
     double *sxs = (double *)su;                          // window nodes (FP64)
     short *skq = (short *)(su + sizeof(double) * (kWinStep + 1));   // periods
-    if (!tab) {
-        if (t < 2) {
-            int e = t == 0 ? i0 - H : i0 - H + NE - 1;
-            int kx = 0;
-            if (e < 0) { e += n; kx = -1; }
-            while (e >= n) { e -= n; kx += 1; }
-            double xh;
-            int64_t k;
-            shifted_node_inv(x, n, s, e, invlen, len, xh, k);
-            const int64_t gg = (int64_t)find_cell(x, n, xh) + (k + kx) * (int64_t)n;
-            if (t == 0) s_wlo = gg - LO;
-            else s_whi = gg - LO + P;
-        }
-        __syncthreads();
+    if (t < 2) {
+        int e = t == 0 ? i0 - H : i0 - H + NE - 1;
+        int kx = 0;
+        if (e < 0) { e += n; kx = -1; }
+        while (e >= n) { e -= n; kx += 1; }
+        double xh;
+        int64_t k;
+        shifted_node_inv(x, n, s, e, invlen, len, xh, k);
+        const int64_t gg = (int64_t)find_cell(x, n, xh) + (k + kx) * (int64_t)n;
+        if (t == 0) s_wlo = gg - LO;
+        else s_whi = gg - LO + P;
     }
-    int64_t pwlo = 0, pk0 = 0;
-    bool stage = false;
-    int pW = 0;
-    if (!tab) {
-        pwlo = s_wlo;
-        pk0 = pwlo >= 0 ? pwlo / n : -((-pwlo + n - 1) / n);   // period of wlo
-        stage = s_whi - pwlo >= P && s_whi - pwlo <= kWinStep;
-        pW = stage ? (int)(s_whi - pwlo) : 0;
-    }
+    __syncthreads();
+    const int64_t pwlo = s_wlo;
+    const int64_t pk0 = pwlo >= 0 ? pwlo / n : -((-pwlo + n - 1) / n);   // period of wlo
+    const bool stage = s_whi - pwlo >= P && s_whi - pwlo <= kWinStep;
+    const int pW = stage ? (int)(s_whi - pwlo) : 0;
     if (stage) {
         const int pbase = (int)(pwlo - pk0 * n);
         for (int j = t; j <= pW; j += kBlock) {
@@ -270,9 +214,9 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
                 }
             }
             if (!done) {
-                const int c = tab ? find_cell_tab(x, n, R.tab, bsc, xh) : find_cell(x, n, xh);
+                const int c = find_cell(x, n, xh);
                 g[k] = (int64_t)c + (kk + kx) * (int64_t)n;
-                stencil_weights<TQ, P>(x, n, len, R, c, xh, w[k]);
+                stencil_weights<TQ, P>(x, n, len, c, xh, w[k]);
             }
         }
     }
@@ -297,8 +241,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
         // (B) window masses and the block scan into the cumulative
         for (int j = t; j < W; j += kBlock) {
             const int mm = wrap_small(base + j, n);
-            if (tab) sm[j] = (M)q[mm] * TabT<M>::dx(R.tab)[mm];
-            else sm[j] = AC::template mass<TQ>(q[mm], x[mm + 1] - x[mm]);
+            sm[j] = AC::template mass<TQ>(q[mm], x[mm + 1] - x[mm]);
         }
         __syncthreads();
         const int per = (W + kBlock - 1) / kBlock;
@@ -361,8 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
                 const double wh = direct_whole<TQ>(x, q, n, sg[ci], sg[ci + 1]);
                 mp = (D)(wh + ((double)sell[ci + 1] - (double)sell[ci]));
             }
-            if (tab) qs[k] = (CT)(mp * (D)TabT<D>::dxinv(R.tab)[cell]);
-            else qs[k] = (CT)(mp / (D)(x[cell + 1] - x[cell]));
+            qs[k] = (CT)(mp / (D)(x[cell + 1] - x[cell]));
             if (H == 0) qo[cell] = (TQ)qs[k];
             else if (qmid && ci >= H && ci < H + nd) qmid[cell] = (TQ)qs[k];
         }
@@ -382,14 +324,8 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
         if (u < nd + 2) {
             const int cm = wrap_small(i0 - 2 + u, n);
             const int c0 = wrap_small(i0 - 1 + u, n);
-            CT hp, hm;
-            if (tab) {
-                hp = TabT<CT>::hinv(R.tab)[c0];
-                hm = TabT<CT>::hinv(R.tab)[cm];
-            } else {
-                hp = (CT)(1.0 / centre_gap(x, n, len, c0));
-                hm = (CT)(1.0 / centre_gap(x, n, len, cm));
-            }
+            const CT hp = (CT)(1.0 / centre_gap(x, n, len, c0));
+            const CT hm = (CT)(1.0 / centre_gap(x, n, len, cm));
             const CT dp = (sq[u + 2] - sq[u + 1]) * hp;
             const CT dm = (sq[u + 1] - sq[u]) * hm;
             ssig[u] = (dp * dm <= (CT)0) ? (CT)0 : harmonic2(dp, dm);
@@ -406,10 +342,10 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
             CT qf;
             if (v >= (CT)0) {
                 const int c = wrap_small(i0 + u - 1, n);
-                const CT dxu = tab ? TabT<CT>::dx(R.tab)[c] : (CT)(x[c + 1] - x[c]);
+                const CT dxu = (CT)(x[c + 1] - x[c]);
                 qf = sq[u + 1] + (CT)0.5 * ssig[u] * (dxu - v * dt);
             } else {
-                const CT dxu = tab ? TabT<CT>::dx(R.tab)[f] : (CT)(x[f + 1] - x[f]);
+                const CT dxu = (CT)(x[f + 1] - x[f]);
                 qf = sq[u + 2] - (CT)0.5 * ssig[u + 1] * (dxu + v * dt);
             }
             sf[u] = v * qf;
@@ -422,7 +358,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
         const int u = t + k * kBlock;
         if (u < nd) {
             const int i = i0 + u;
-            const CT inv = tab ? TabT<CT>::dxinv(R.tab)[i] : (CT)(1.0 / (x[i + 1] - x[i]));
+            const CT inv = (CT)(1.0 / (x[i + 1] - x[i]));
             qo[i] = (TQ)(sq[u + 2] - dt * (sf[u + 1] - sf[u]) * inv);
         }
     }
@@ -529,8 +465,8 @@ __global__ __launch_bounds__(kBlock) void k_residual(ResidualArgs a)
 // ---------------------------------------------------------------------------
 
 struct MeshTabW {
-    double *dx, *dxinv, *hinv, *stc;
-    float *dxf, *dxinvf, *hinvf, *stcf;
+    double *dx, *dxinv, *hinv;
+    float *dxf, *dxinvf, *hinvf;
     int32_t *bucket;
     double2 *bnext;
     int32_t nb;
@@ -548,146 +484,248 @@ struct MeshTabW {
     int32_t *nonu_min;
 };
 
+// Every table of the mesh in one launch of B-thread workgroups, each with one
+// part: the uniform-run counts (workgroup 0, when they are asked for), then
+// per B cells the sizes, gaps and PPM weights, then the stencils, then per B
+// buckets the search index.  Short dependent chains bound it (FP64 divisions,
+// node loads of about a microsecond when first touched), not bytes, so the
+// parts run side by side instead of one after the other in one thread, and
+// the run counts do not wait for a launch of their own.  B: the run counts'
+// one workgroup sets the time of long rows (it keeps its cells in registers,
+// 32 a lane at 16384 cells), four waves a workgroup are quicker to start on
+// short ones: 256 threads against 512 4.6 and 6.2 us at 2048 cells, 5.9 and
+// 6.3 at 4096, 15.5 and 7.5 at 6001, 20.5 and 12.2 at 16384.  One thread a
+// cell and bucket, then the run counts in a launch of their own: 10.2 us at
+// 256 cells (now 4.7), 11.1 at 2048, 22.0 at 16384.
+constexpr int kPrepShort = 4096;                     // longest row of 256-thread workgroups
+
+// Cell sizes, reciprocals, centre gaps and PPM interface weights of cell j.
+__device__ __forceinline__ void prep_sizes(const double *x, int n, int j, const MeshTabW &T)
+{
+    const double len = x[n] - x[0];
+    const double dx = x[j + 1] - x[j];
+    const double h = centre_gap(x, n, len, j);
+    const double dxi = 1.0 / dx, hi = 1.0 / h;
+    T.dx[j] = dx;
+    T.dxinv[j] = dxi;
+    T.hinv[j] = hi;
+    T.dxf[j] = (float)dx;
+    T.dxinvf[j] = (float)dxi;
+    T.hinvf[j] = (float)hi;
+    T.rrf[j] = make_float2((float)dx, (float)hi);
+    T.rrd[j] = make_double2(dx, hi);
+    const PpmW pw = ppm_weights(x[wrap_small(j - 1, n) + 1] - x[wrap_small(j - 1, n)], dx,
+                                x[wrap_small(j + 1, n) + 1] - x[wrap_small(j + 1, n)],
+                                x[wrap_small(j + 2, n) + 1] - x[wrap_small(j + 2, n)]);
+    const double pv[5] = {pw.d1, pw.d2, pw.e1, pw.e2, pw.e3};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        T.ppmd[k * n + j] = pv[k];
+        T.ppmf[k * n + j] = (float)pv[k];
+    }
+}
+
+// Stencil data of cell j (order P) in the layouts the kernels read.
 template <int P>
-__global__ __launch_bounds__(256) void k_mesh_prep(const double *x, int n, MeshTabW T)
+__device__ __forceinline__ void prep_stencil(const double *x, int n, int j, const MeshTabW &T)
 {
     constexpr int LO = (P - 1) / 2;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
     const double len = x[n] - x[0];
-    if (j < n) {
-        const double dx = x[j + 1] - x[j];
-        const double h = centre_gap(x, n, len, j);
-        T.dx[j] = dx;
-        T.dxinv[j] = 1.0 / dx;
-        T.hinv[j] = 1.0 / h;
-        T.dxf[j] = (float)dx;
-        T.dxinvf[j] = (float)(1.0 / dx);
-        T.hinvf[j] = (float)(1.0 / h);
-        T.rrf[j] = make_float2((float)dx, (float)(1.0 / h));
-        T.rrd[j] = make_double2(dx, 1.0 / h);
-        double th[P + 1];
-        const double xc = x[j];
-        for (int a = 0; a <= P; ++a) th[a] = (node_x(x, n, len, j - LO + a) - xc) / dx;
-        // the cell's own edges, exactly (the FP32 streaming kernel relies on it)
-        th[LO] = 0.0;
-        th[LO + 1] = 1.0;
-        double *st = T.stc + j * (2 * (P + 1));
-        float *sf = T.stcf + j * (2 * (P + 1));
-        CellRec<float> rf;
-        CellRec<double> rd;
-        rf.xc = rd.xc = xc;
-        rf.dxinv = rd.dxinv = 1.0 / dx;
-        for (int a = 0; a < 6; ++a) {
-            rf.th[a] = rf.rd[a] = 0.0f;
-            rd.th[a] = rd.rd[a] = 0.0;
-        }
+    const double dx = x[j + 1] - x[j];
+    double th[P + 1];
+    const double xc = x[j];
+#pragma unroll
+    for (int a = 0; a <= P; ++a) th[a] = (node_x(x, n, len, j - LO + a) - xc) / dx;
+    // the cell's own edges, exactly (the streaming kernels rely on it)
+    th[LO] = 0.0;
+    th[LO + 1] = 1.0;
+    CellRec<float> rf;
+    CellRec<double> rd;
+    rf.xc = rd.xc = xc;
+    rf.dxinv = rd.dxinv = 1.0 / dx;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        rf.th[a] = rf.rd[a] = 0.0f;
+        rd.th[a] = rd.rd[a] = 0.0;
+    }
+#pragma unroll
+    for (int a = 0; a <= P; ++a) {
+        double den = 1.0;
+#pragma unroll
+        for (int b = 0; b <= P; ++b)
+            if (b != a) den *= th[a] - th[b];
+        rd.th[a] = th[a];
+        rd.rd[a] = 1.0 / den;
+        rf.th[a] = (float)th[a];
+        rf.rd[a] = (float)rd.rd[a];
+    }
+    T.crf[j] = rf;
+    T.crd[j] = rd;
+    {
+        float v[9];
+        int k = 0;
+#pragma unroll
+        for (int a = 0; a <= P; ++a)
+            if (a != LO && a != LO + 1) v[k++] = rf.th[a];
+#pragma unroll
+        for (int a = 0; a <= P; ++a)
+            if (a != LO) v[k++] = rf.rd[a];
+        for (; k < 9; ++k) v[k] = 0.0f;
+        float4 *p4 = (float4 *)T.stp;
+        p4[j] = make_float4(v[0], v[1], v[2], v[3]);
+        p4[n + j] = make_float4(v[4], v[5], v[6], v[7]);
+        T.stp[8 * n + j] = v[8];
+    }
+    {
+        // FP64: the cell's left edge and 1/dx, then the same values, in
+        // pairs (six planes of double2)
+        double v[12];
+        int k = 0;
+        v[k++] = xc;
+        v[k++] = rd.dxinv;
+#pragma unroll
+        for (int a = 0; a <= P; ++a)
+            if (a != LO && a != LO + 1) v[k++] = rd.th[a];
+#pragma unroll
+        for (int a = 0; a <= P; ++a)
+            if (a != LO) v[k++] = rd.rd[a];
+        for (; k < 12; ++k) v[k] = 0.0;
+#pragma unroll
+        for (int pl = 0; pl < 6; ++pl) T.stpd[pl * n + j] = make_double2(v[2 * pl], v[2 * pl + 1]);
+        // the same offsets and denominators as FP32 deviations from those
+        // of equally spaced nodes (offset b - LO, denominator 1 / prod_{a != b}
+        // (b - a)): th_b - (b - LO), and rd_b / rd_eq_b - 1
+        float dv9[9];
+        int m = 0;
+#pragma unroll
+        for (int a = 0; a <= P; ++a)
+            if (a != LO && a != LO + 1) dv9[m++] = (float)(rd.th[a] - (double)(a - LO));
+#pragma unroll
         for (int a = 0; a <= P; ++a) {
-            double den = 1.0;
+            if (a == LO) continue;
+            double eq = 1.0;
+#pragma unroll
             for (int b = 0; b <= P; ++b)
-                if (b != a) den *= th[a] - th[b];
-            st[a] = th[a];
-            st[P + 1 + a] = 1.0 / den;
-            sf[a] = (float)th[a];
-            sf[P + 1 + a] = (float)(1.0 / den);
-            rf.th[a] = (float)th[a];
-            rf.rd[a] = (float)(1.0 / den);
-            rd.th[a] = th[a];
-            rd.rd[a] = 1.0 / den;
+                if (b != a) eq *= (double)(a - b);
+            dv9[m++] = (float)(rd.rd[a] * eq - 1.0);
         }
-        T.crf[j] = rf;
-        T.crd[j] = rd;
-        {
-            float v[9];
-            int k = 0;
-            for (int a = 0; a <= P; ++a)
-                if (a != LO && a != LO + 1) v[k++] = rf.th[a];
-            for (int a = 0; a <= P; ++a)
-                if (a != LO) v[k++] = rf.rd[a];
-            for (; k < 9; ++k) v[k] = 0.0f;
-            float4 *p4 = (float4 *)T.stp;
-            p4[j] = make_float4(v[0], v[1], v[2], v[3]);
-            p4[n + j] = make_float4(v[4], v[5], v[6], v[7]);
-            T.stp[8 * n + j] = v[8];
-        }
-        {
-            // FP64: the cell's left edge and 1/dx, then the same values, in
-            // pairs (six planes of double2)
-            double v[12];
-            int k = 0;
-            v[k++] = xc;
-            v[k++] = 1.0 / dx;
-            for (int a = 0; a <= P; ++a)
-                if (a != LO && a != LO + 1) v[k++] = rd.th[a];
-            for (int a = 0; a <= P; ++a)
-                if (a != LO) v[k++] = rd.rd[a];
-            for (; k < 12; ++k) v[k] = 0.0;
-            for (int pl = 0; pl < 6; ++pl) T.stpd[pl * n + j] = make_double2(v[2 * pl], v[2 * pl + 1]);
-            // the same offsets and denominators as FP32 deviations from those
-            // of equally spaced nodes (offset b - LO, denominator 1 / prod_{a != b}
-            // (b - a)): th_b - (b - LO), and rd_b / rd_eq_b - 1
-            float dv9[9];
-            int m = 0;
-            for (int a = 0; a <= P; ++a)
-                if (a != LO && a != LO + 1) dv9[m++] = (float)(rd.th[a] - (double)(a - LO));
-            for (int a = 0; a <= P; ++a) {
-                if (a == LO) continue;
-                double eq = 1.0;
-                for (int b = 0; b <= P; ++b)
-                    if (b != a) eq *= (double)(a - b);
-                dv9[m++] = (float)(rd.rd[a] * eq - 1.0);
-            }
-            for (; m < 9; ++m) dv9[m] = 0.0f;
-            float4 *d4 = (float4 *)T.stdv;
-            d4[j] = make_float4(dv9[0], dv9[1], dv9[2], dv9[3]);
-            d4[n + j] = make_float4(dv9[4], dv9[5], dv9[6], dv9[7]);
-            T.stdv[8 * n + j] = dv9[8];
-        }
-        const PpmW pw = ppm_weights(x[wrap_small(j - 1, n) + 1] - x[wrap_small(j - 1, n)], dx,
-                                    x[wrap_small(j + 1, n) + 1] - x[wrap_small(j + 1, n)],
-                                    x[wrap_small(j + 2, n) + 1] - x[wrap_small(j + 2, n)]);
-        const double pv[5] = {pw.d1, pw.d2, pw.e1, pw.e2, pw.e3};
-        for (int k = 0; k < 5; ++k) {
-            T.ppmd[k * n + j] = pv[k];
-            T.ppmf[k * n + j] = (float)pv[k];
-        }
+        for (; m < 9; ++m) dv9[m] = 0.0f;
+        float4 *d4 = (float4 *)T.stdv;
+        d4[j] = make_float4(dv9[0], dv9[1], dv9[2], dv9[3]);
+        d4[n + j] = make_float4(dv9[4], dv9[5], dv9[6], dv9[7]);
+        T.stdv[8 * n + j] = dv9[8];
     }
-    if (j < T.nb) {
-        // lower-bound cell of bucket j, taken a hair below the bucket start so
-        // that a bucket number rounded up by one still bounds the cell from
-        // below; then the next two nodes (+inf past the last cell)
-        const double w = len / (double)T.nb;
-        const int c0 = find_cell(x, n, x[0] + ((double)j - 1e-6) * w);
-        T.bucket[j] = c0;
-        const double inf = __builtin_huge_val();
-        T.bnext[j] = make_double2(c0 + 1 < n ? x[c0 + 1] : inf, c0 + 2 < n ? x[c0 + 2] : inf);
+}
+
+// The search index: the lower-bound cell of bucket j, taken a hair below the
+// bucket start so that a bucket number rounded up by one still bounds the
+// cell from below; then the next two nodes (+inf past the last cell).  Two
+// loads deep on rows of up to 64 B cells (a binary search of 16384 nodes is
+// fourteen): B nodes sampled evenly over the row, shared by
+// the workgroup, place a wave's first bucket within 64 cells; the cells of
+// its 64 neighbouring buckets are then found among the kPrepWin nodes from
+// there in LDS.  Longer rows narrow 64-fold a load until there; a lane whose
+// cell lies beyond the window (a mesh far finer here than on average)
+// searches the rest of the row by itself.
+constexpr int kPrepWin = 192;
+template <int B>
+__device__ __forceinline__ void prep_buckets(const double *x, int n, int j, const MeshTabW &T,
+                                             double *smp, double *win)
+{
+    const int t = (int)threadIdx.x, lane = t & 63;
+    const double inf = __builtin_huge_val();
+    const int step0 = (n + B - 1) / B;
+    smp[t] = t * step0 < n ? x[t * step0] : inf;
+    const double len = x[n] - x[0];
+    const double w = len / (double)T.nb;
+    const double tj = x[0] + ((double)j - 1e-6) * w;
+    __syncthreads();
+    if (j - lane >= T.nb) return;                    // (whole waves)
+    const double t0 = __shfl(tj, 0);
+    // x[lo] <= t0 (or lo == 0), x[hi] > t0 (or hi == n)
+    int k = 0;
+#pragma unroll
+    for (int i = 0; i < B / 64; ++i) k += __popcll(__ballot(smp[64 * i + lane] <= t0));
+    int lo = min(max(k - 1, 0) * step0, n - 1), hi = min(n, lo + step0);
+    while (hi - lo > 64) {
+        const int step = (hi - lo + 63) / 64;
+        const int at = lo + lane * step;
+        const int m = __popcll(__ballot((at < hi ? x[at] : inf) <= t0));
+        lo = min(lo + max(m - 1, 0) * step, n - 1);
+        hi = min(hi, lo + step);
     }
-    if (j == 0) {
-        T.scal[0] = (double)T.nb / len;
-        T.scal[1] = 1.0 / len;
-        T.scal[2] = x[0] * ((double)T.nb / len);
+    double v[kPrepWin / 64];
+#pragma unroll
+    for (int i = 0; i < kPrepWin / 64; ++i) {
+        const int at = lo + lane + 64 * i;
+        v[i] = at < n ? x[at] : inf;
     }
+#pragma unroll
+    for (int i = 0; i < kPrepWin / 64; ++i) win[lane + 64 * i] = v[i];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    int cnt = 0;                                     // of the first 128 nodes: at or below tj
+#pragma unroll
+    for (int d = 64; d > 0; d >>= 1)
+        if (win[cnt + d - 1] <= tj) cnt += d;
+    if (cnt == 127 && win[127] <= tj) cnt = 128;
+    if (j >= T.nb) return;
+    int c = max(lo + cnt - 1, 0);
+    double2 nx;
+    if (cnt < 128) {
+        const int d = c - lo;
+        nx = make_double2(win[d + 1], win[d + 2]);
+    } else {                                         // x[c] <= tj
+        int b = n - 1;
+        c = min(c, b);
+        while (c < b) {
+            const int mid = c + (b - c + 1) / 2;
+            if (x[mid] <= tj) c = mid;
+            else b = mid - 1;
+        }
+        nx = make_double2(c + 1 < n ? x[c + 1] : inf, c + 2 < n ? x[c + 2] : inf);
+    }
+    T.bucket[j] = min(c, n - 1);
+    T.bnext[j] = nx;
 }
 
 // Uniform runs of a shared mesh: prefix counts of the cells whose size
 // differs from the largest (nonu) and from the smallest (nonu_min) by more
-// than kUniformTol of it.  One workgroup of 1024 threads: both sizes by a
-// coalesced pass and block reductions; then each of the 16 waves takes one
-// contiguous segment of the row, counts its flagged cells, and after one
-// scan of the 16 counts writes its segment's prefix 64 cells at a time from
-// one ballot per flag (no barrier inside the segment loops).
-__global__ __launch_bounds__(1024) void k_mesh_uniform(const double *x, int n, int32_t *nonu,
-                                                       int32_t *nonu_min)
+// than kUniformTol of it.  One workgroup: each of its waves takes one
+// contiguous segment of the row, whose first 64 KEEP cells it keeps in
+// registers (one load of the nodes on rows of up to B KEEP cells); both sizes by a block reduction, then each wave counts its flagged
+// cells, and after one scan of the waves' counts writes its segment's prefix
+// 64 cells at a time from one ballot per flag.
+template <int B, int KEEP>
+__device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *nonu,
+                                             int32_t *nonu_min, double *sx)
 {
-    __shared__ double smax[16], smin[16];
-    __shared__ int32_t soff[2][17];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    constexpr int kPrepWaves = B / 64;
+    double *smax = sx, *smin = sx + kPrepWaves;
+    int32_t *soff = (int32_t *)(sx + 2 * kPrepWaves);          // [2][kPrepWaves]
+    const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int seg = (n + kPrepWaves - 1) / kPrepWaves;
+    const int a0 = min(n, wv * seg), a1 = min(n, a0 + seg);
+    double keep[KEEP];
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+        const int j = min(a0 + 64 * k + lane, n - 1);
+        keep[k] = x[j + 1] - x[j];
+    }
     double mx = 0.0, mn = __builtin_huge_val();
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+        mx = fmax(mx, keep[k]);                      // (clamped lanes: cells of the row as well)
+        mn = fmin(mn, keep[k]);
+    }
 #pragma unroll 8
-    for (int j = t; j < n; j += 1024) {
+    for (int j = a0 + 64 * KEEP + lane; j < a1; j += 64) {
         const double d = x[j + 1] - x[j];
         mx = fmax(mx, d);
         mn = fmin(mn, d);
     }
+#pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         mx = fmax(mx, __shfl_xor(mx, o, 64));
         mn = fmin(mn, __shfl_xor(mn, o, 64));
@@ -698,59 +736,97 @@ __global__ __launch_bounds__(1024) void k_mesh_uniform(const double *x, int n, i
     }
     __syncthreads();
     double hx = smax[0], hn = smin[0];
-    for (int w = 1; w < 16; ++w) {
+#pragma unroll
+    for (int w = 1; w < kPrepWaves; ++w) {
         hx = fmax(hx, smax[w]);
         hn = fmin(hn, smin[w]);
     }
     auto off_max = [&](double d) { return fabs(d - hx) > kUniformTol * hx; };
     auto off_min = [&](double d) { return fabs(d - hn) > kUniformTol * hn; };
-    const int seg = (n + 15) / 16;
-    const int a0 = min(n, wv * seg), a1 = min(n, a0 + seg);
     int32_t cx = 0, cn = 0;
-#pragma unroll 4
-    for (int j = a0 + lane; j < a1; j += 64) {
-        const double d = x[j + 1] - x[j];
-        cx += off_max(d) ? 1 : 0;
-        cn += off_min(d) ? 1 : 0;
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+        const bool in = a0 + 64 * k + lane < a1;
+        cx += __popcll(__ballot(in && off_max(keep[k])));
+        cn += __popcll(__ballot(in && off_min(keep[k])));
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        cx += __shfl_xor(cx, o, 64);
-        cn += __shfl_xor(cn, o, 64);
+    for (int j0 = a0 + 64 * KEEP; j0 < a1; j0 += 64) {
+        const int j = min(j0 + lane, n - 1);
+        const double d = x[j + 1] - x[j];
+        cx += __popcll(__ballot(j0 + lane < a1 && off_max(d)));
+        cn += __popcll(__ballot(j0 + lane < a1 && off_min(d)));
     }
     if (lane == 0) {
-        soff[0][wv + 1] = cx;
-        soff[1][wv + 1] = cn;
+        soff[wv] = cx;
+        soff[kPrepWaves + wv] = cn;
     }
     __syncthreads();
-    if (t == 0) {
-        soff[0][0] = soff[1][0] = 0;
-        for (int w = 1; w <= 16; ++w) {
-            soff[0][w] += soff[0][w - 1];
-            soff[1][w] += soff[1][w - 1];
-        }
+    int32_t bx = 0, bn = 0, tx = 0, tn = 0;
+#pragma unroll
+    for (int w = 0; w < kPrepWaves; ++w) {
+        const int32_t ux = soff[w], un = soff[kPrepWaves + w];
+        bx += w < wv ? ux : 0;
+        bn += w < wv ? un : 0;
+        tx += ux;
+        tn += un;
     }
-    __syncthreads();
-    int32_t bx = soff[0][wv], bn = soff[1][wv];
     const uint64_t below = (1ull << lane) - 1ull;
-    for (int j0 = a0; j0 < a1; j0 += 64) {
+    auto put = [&](int j0, double d) {
         const int j = j0 + lane;
-        bool fx = false, fn = false;
-        if (j < a1) {
-            const double d = x[j + 1] - x[j];
-            fx = off_max(d);
-            fn = off_min(d);
-        }
-        const uint64_t mbx = __ballot(fx), mbn = __ballot(fn);
-        if (j < a1) {
+        const bool in = j < a1;
+        const uint64_t mbx = __ballot(in && off_max(d)), mbn = __ballot(in && off_min(d));
+        if (in) {
             nonu[j] = bx + __popcll(mbx & below);
             nonu_min[j] = bn + __popcll(mbn & below);
         }
         bx += __popcll(mbx);
         bn += __popcll(mbn);
+    };
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+        if (a0 + 64 * k < a1) put(a0 + 64 * k, keep[k]);
+    for (int j0 = a0 + 64 * KEEP; j0 < a1; j0 += 64) {
+        const int j = min(j0 + lane, n - 1);
+        put(j0, x[j + 1] - x[j]);
     }
     if (t == 0) {
-        nonu[n] = soff[0][16];
-        nonu_min[n] = soff[1][16];
+        nonu[n] = tx;
+        nonu_min[n] = tn;
+    }
+}
+
+template <int P, int B>
+__global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTabW T,
+                                                          int uniform)
+{
+    __shared__ double sx[B];
+    __shared__ double swin[B / 64][kPrepWin];
+    const int t = (int)threadIdx.x;
+    const int nc = (n + B - 1) / B;
+    int b = (int)blockIdx.x;
+    if (uniform) {
+        if (b == 0) {
+            constexpr int K1 = B == 256 ? 4 : 12, K2 = B == 256 ? 16 : 32;
+            if (n <= B * K1) prep_uniform<B, K1>(x, n, T.nonu, T.nonu_min, sx);
+            else prep_uniform<B, K2>(x, n, T.nonu, T.nonu_min, sx);
+            return;
+        }
+        --b;
+    }
+    if (b < nc) {
+        const int j = b * B + t;
+        if (j < n) prep_sizes(x, n, j, T);
+    } else if (b < 2 * nc) {
+        const int j = (b - nc) * B + t;
+        if (j < n) prep_stencil<P>(x, n, j, T);
+        if (j == 0) {
+            const double len = x[n] - x[0];
+            T.scal[0] = (double)T.nb / len;
+            T.scal[1] = 1.0 / len;
+            T.scal[2] = x[0] * ((double)T.nb / len);
+        }
+    } else {
+        prep_buckets<B>(x, n, (b - 2 * nc) * B + t, T, sx, swin[t >> 6]);
     }
 }
 
@@ -812,6 +888,21 @@ hipError_t step_order(const StepArgs &a, int scan, int order, hipStream_t st)
     }
 }
 
+template <int B>
+hipError_t mesh_prep_launch(const double *x, int64_t n, int order, const MeshTabW &w, bool uniform,
+                            hipStream_t st)
+{
+    const int64_t nc = (n + B - 1) / B;
+    const dim3 g((unsigned)(2 * nc + ((int64_t)w.nb + B - 1) / B + (uniform ? 1 : 0))), b(B);
+    const int u = uniform ? 1 : 0;
+    switch (order) {
+    case 1: hipLaunchKernelGGL((k_mesh_prep<1, B>), g, b, 0, st, x, (int)n, w, u); break;
+    case 3: hipLaunchKernelGGL((k_mesh_prep<3, B>), g, b, 0, st, x, (int)n, w, u); break;
+    default: hipLaunchKernelGGL((k_mesh_prep<5, B>), g, b, 0, st, x, (int)n, w, u); break;
+    }
+    return hipGetLastError();
+}
+
 size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
 
 } // namespace
@@ -838,12 +929,10 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     w.dxf = (float *)p; p += al256(4 * n);
     w.dxinvf = (float *)p; p += al256(4 * n);
     w.hinvf = (float *)p; p += al256(4 * n);
-    w.stc = (double *)p; p += al256(8 * n * 2 * (order + 1));
-    w.stcf = (float *)p; p += al256(4 * n * 2 * (order + 1));
     w.bucket = (int32_t *)p; p += al256(4 * 4 * n);
     w.nb = (int32_t)(4 * n);
     w.bnext = (double2 *)p; p += al256(16 * 4 * n);
-    w.scal = (double *)p; p += al256(16);
+    w.scal = (double *)p; p += al256(24);
     w.crf = (CellRec<float> *)p; p += al256(sizeof(CellRec<float>) * n);
     w.crd = (CellRec<double> *)p; p += al256(sizeof(CellRec<double>) * n);
     w.rrf = (float2 *)p; p += al256(8 * n);
@@ -855,8 +944,8 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     w.ppmf = (float *)p; p += al256(20 * n);
     w.nonu = (int32_t *)p; p += al256(4 * (n + 1));
     w.nonu_min = (int32_t *)p;
-    tab.dx = w.dx; tab.dxinv = w.dxinv; tab.hinv = w.hinv; tab.stc = w.stc;
-    tab.dxf = w.dxf; tab.dxinvf = w.dxinvf; tab.hinvf = w.hinvf; tab.stcf = w.stcf;
+    tab.dx = w.dx; tab.dxinv = w.dxinv; tab.hinv = w.hinv;
+    tab.dxf = w.dxf; tab.dxinvf = w.dxinvf; tab.hinvf = w.hinvf;
     tab.bucket = w.bucket;
     tab.nb = w.nb;
     tab.scal = w.scal;
@@ -872,19 +961,8 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     tab.ppmf = w.ppmf;
     tab.nonu = uniform ? w.nonu : nullptr;
     tab.nonu_min = uniform ? w.nonu_min : nullptr;
-    // one wave per workgroup, so that the cells' tables (the first n threads,
-    // FP64 divisions) spread over every CU
-    const unsigned grid = (unsigned)((w.nb + 63) / 64);
-    switch (order) {
-    case 1: hipLaunchKernelGGL(k_mesh_prep<1>, dim3(grid), dim3(64), 0, stream, x, (int)n, w); break;
-    case 3: hipLaunchKernelGGL(k_mesh_prep<3>, dim3(grid), dim3(64), 0, stream, x, (int)n, w); break;
-    default: hipLaunchKernelGGL(k_mesh_prep<5>, dim3(grid), dim3(64), 0, stream, x, (int)n, w); break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !uniform) return e;
-    hipLaunchKernelGGL(k_mesh_uniform, dim3(1), dim3(1024), 0, stream, x, (int)n, w.nonu,
-                       w.nonu_min);
-    return hipGetLastError();
+    if (n <= kPrepShort) return mesh_prep_launch<256>(x, n, order, w, uniform, stream);
+    return mesh_prep_launch<512>(x, n, order, w, uniform, stream);
 }
 
 hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
