@@ -49,7 +49,6 @@ constexpr int kStage = kFT + 8;          // staged cells of one array (cell c at
 constexpr int kPadQ = 8;                 // zeros around a uniform tile's Qbar^{n+1/2} (>= p)
 constexpr int kSwOff = 288;              // a uniform tile's window values, LDS floats
 constexpr size_t kGenU = 8 * (kFastWin + 8);   // bytes: staging, FP64 window, Cbar or node data
-constexpr int kGenShareA = 4;            // other tiles: a grid of a quarter of the tiles
 
 static_assert(2 * kPadQ + kFT <= kSwOff, "uniform LDS layout");
 static_assert(kSwOff + kFT + 16 <= 3 * kStage, "uniform LDS layout");
@@ -1392,7 +1391,7 @@ hipError_t ladj_r(const StepAdjArgs &a, hipStream_t st)
     return v0 ? ladj_kernels<R, false, true>(a, st) : ladj_kernels<R, false, false>(a, st);
 }
 
-// The uniform tiles (the compacted list's first part), one a wave.
+// The uniform tiles, one a wave.
 template <int P, bool RES, bool V0>
 __global__ __launch_bounds__(kBlock) void k_adjf_uni(StepAdjArgs a)
 {
@@ -1400,23 +1399,22 @@ __global__ __launch_bounds__(kBlock) void k_adjf_uni(StepAdjArgs a)
     const int wid = wave_id();
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= a.fast.totals[0]) return;
-    const FastTile r = load_rec(a.fast.rec + a.rows.n_tiles, i);
+    const FastTile r = load_rec(a.fast.urec, i);
     adj_uniform_tile<P, RES, V0>(a, r, su[wid], (int)threadIdx.x % kLanes);
 }
 
-// The other tiles: waves stepping through the rest of the list.
+// The other tiles.
 template <int P, bool RES, bool V0>
 __global__ __launch_bounds__(kBlock) void k_adjf_gen(StepAdjArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char su[kWaves][kGenU];
     __shared__ __attribute__((aligned(16))) float smb[kWaves][kFT + 8];
     const int wid = wave_id();
-    const int nt = (int)a.rows.n_tiles;
     const int n = (int)a.rows.n_cols;
     const int t = (int)threadIdx.x % kLanes;
-    const int stride = (int)gridDim.x * kWaves;
-    for (int i = a.fast.totals[0] + (int)blockIdx.x * kWaves + wid; i < nt; i += stride) {
-        const FastTile r = load_rec(a.fast.rec + nt, i);
+    const int total = a.fast.totals[1];
+    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+        const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
         if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n)
             adj_window_tile<P, RES, V0>(a, r, su[wid], smb[wid], t);
         else
@@ -1430,8 +1428,7 @@ hipError_t adjf_kernels(const StepAdjArgs &a, hipStream_t st)
 {
     const int64_t nt = a.rows.n_tiles;
     const dim3 b(kBlock);
-    const dim3 gu((unsigned)((nt + kWaves - 1) / kWaves));
-    const dim3 gg((unsigned)((nt + kWaves * kGenShareA - 1) / (kWaves * kGenShareA)));
+    const dim3 gu(uniform_grid(nt)), gg(other_grid(nt));
     if (const ForkJoin *fj = capture_fork) {
         // inside a captured loop: the two kinds of tile (disjoint outputs and
         // partials) as parallel graph branches, joined before the edges pass

@@ -167,50 +167,55 @@ struct FastTile {
     int32_t wlo_lo, wlo_hi;  // extended source index of the window start
     float cc[6];             // uniform: weights of the (order+1)-point stencil
     float dx, hinv, dxinv;   // uniform: the run's cell size, 1/centre gap, 1/size
-    int32_t pad[2];          // tile id; the k-th other tile: k (its node data),
-                             // a uniform tile: the bits of its FP32 theta
+    int32_t pad[2];          // tile id; a tile in no run: the tile id (its node
+                             // data), a uniform tile: the bits of its FP32 theta
 };
 static_assert(sizeof(FastTile) == 64, "one record a tile");
-// The tiles of one call: their records (rec[0 .. n_tiles)), then the same
-// records compacted (rec[n_tiles ..)): the uniform tiles in tile order
-// (totals[0] of them), then the others in tile order, each with its tile id in
-// pad[0]; the per-1024-tile counts the compacted order is built from; and for
-// the k-th non-uniform tile, the source-window index (jc) and position in its
-// cell (theta, FP32) of each of its shifted nodes, kFastNodes entries a tile
-// (the shift of a row is the same at every step of a call).
+// The tiles of one call: their records in tile order (rec); copies of the
+// uniform ones' alone, in tile order (urec, totals[0] of them), and the ids of
+// the others (oid, totals[1]); per kPlanGroup tiles, which ones are others
+// (mask); and for each tile in no uniform run the source-window index (jc) and
+// position in its cell (theta, FP32) of each of its shifted nodes, kFastNodes
+// entries a tile (the shift of a row is the same at every step of a call).
 constexpr int kFastNodes = kFastTile + 8;
+constexpr int kPlanGroup = 32;
 struct FastPlan {
     FastTile *rec = nullptr;
-    int32_t *counts = nullptr;
+    FastTile *urec = nullptr;
+    int32_t *oid = nullptr;
     int32_t *totals = nullptr;
+    uint32_t *mask = nullptr;
     float *theta = nullptr;
     int16_t *jc = nullptr;
 };
-// Device bytes of the plan of n_tiles tiles (each piece 256-byte aligned).
+inline int64_t plan_groups(int64_t n_tiles) { return (n_tiles + kPlanGroup - 1) / kPlanGroup; }
+// The plan of n_tiles tiles in mem (each piece 256-byte aligned), and its size.
+inline FastPlan fast_plan_at(void *mem, int64_t n_tiles, size_t *bytes = nullptr)
+{
+    auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
+    const size_t nt = (size_t)n_tiles, nn = nt * kFastNodes;
+    size_t off = 0;
+    auto take = [&](size_t b) {
+        char *p = (char *)mem + off;
+        off += al(b);
+        return p;
+    };
+    FastPlan f;
+    f.rec = (FastTile *)take(sizeof(FastTile) * nt);
+    f.urec = (FastTile *)take(sizeof(FastTile) * nt);
+    f.oid = (int32_t *)take(sizeof(int32_t) * nt);
+    f.totals = (int32_t *)take(2 * sizeof(int32_t));
+    f.mask = (uint32_t *)take(sizeof(uint32_t) * (size_t)plan_groups(n_tiles));
+    f.theta = (float *)take(sizeof(float) * nn);
+    f.jc = (int16_t *)take(sizeof(int16_t) * nn);
+    if (bytes) *bytes = off;
+    return f;
+}
 inline size_t fast_plan_bytes(int64_t n_tiles)
 {
-    auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
-    const size_t nn = (size_t)n_tiles * kFastNodes;
-    return al(2 * sizeof(FastTile) * (size_t)n_tiles) +
-           al(sizeof(int32_t) * (size_t)((n_tiles + 1023) / 1024)) + al(2 * sizeof(int32_t)) +
-           al(sizeof(float) * nn) + al(sizeof(int16_t) * nn);
-}
-inline FastPlan fast_plan_at(void *mem, int64_t n_tiles)
-{
-    auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
-    const size_t nn = (size_t)n_tiles * kFastNodes;
-    char *p = (char *)mem;
-    FastPlan f;
-    f.rec = (FastTile *)p;
-    p += al(2 * sizeof(FastTile) * (size_t)n_tiles);
-    f.counts = (int32_t *)p;
-    p += al(sizeof(int32_t) * (size_t)((n_tiles + 1023) / 1024));
-    f.totals = (int32_t *)p;
-    p += al(2 * sizeof(int32_t));
-    f.theta = (float *)p;
-    p += al(sizeof(float) * nn);
-    f.jc = (int16_t *)p;
-    return f;
+    size_t b = 0;
+    (void)fast_plan_at(nullptr, n_tiles, &b);
+    return b;
 }
 
 // Bulk shift, optionally fused with the residual step (dv != null).
@@ -393,9 +398,8 @@ hipError_t launch_plan(const StepArgs &a, int order, int64_t *wlo, int32_t *w,
 hipError_t launch_step_shared(const StepArgs &a, bool f64, int scan, int order,
                               int items, hipStream_t stream);
 // The FP32 direct-sum step on a shared mesh: plan the tiles into `plan`
-// (R.tile == kFastTile, tables with the uniform-run counts; records, then the
-// two tile lists), then per step the uniform-tile and the searching-tile
-// kernels (a.fast set).
+// (R.tile == kFastTile, tables with the uniform-run counts), then per step the
+// uniform-tile and the searching-tile kernels (a.fast set).
 hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan,
                             hipStream_t stream);
 hipError_t launch_step_fast(const StepArgs &a, int order, int scan, hipStream_t stream);

@@ -797,7 +797,7 @@ __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *no
 
 template <int P, int B>
 __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTabW T,
-                                                          int uniform)
+                                                 int uniform)
 {
     __shared__ double sx[B];
     __shared__ double swin[B / 64][kPrepWin];

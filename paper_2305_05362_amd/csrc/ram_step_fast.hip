@@ -12,9 +12,8 @@
 //     waits on the other waves of its workgroup (no workgroup barrier);
 //   * everything about a tile that does not change between steps is planned
 //     once per call: its source window, whether it lies in one of the mesh's
-//     uniform runs (then the stencil weights and the run's geometry), the
-//     records sorted into the uniform tiles and the others, and for the
-//     others each shifted node's window index and position in its cell;
+//     uniform runs (then the stencil weights and the run's geometry), and if
+//     not each shifted node's window index and position in its cell;
 //   * a tile in a uniform run (every node of the tile in the next source cell
 //     at one theta) needs no search and no masses: the shifted value of a
 //     cell is a fixed (P+1)-point stencil on the window's cell values.  Those
@@ -66,68 +65,96 @@ template <int S> constexpr size_t wave_lds_bytes()
 }
 
 
-// The record of one tile: which path, its window, and for a uniform tile the
-// stencil and the run's geometry.  One thread per tile; the node search is the
-// shared-mesh one of the step kernels (bucket index, Eq. condition_p).
+// The record of each tile: which path, its window, and for a uniform tile the
+// stencil and the run's geometry; and of each group which tiles are in no run.
+// A wave plans kPlanGroup tiles, two lanes each: one for either end node
+// (bucket index, Eq. condition_p), which then look the tile's cells and window
+// up in one run count each (coarse and fine).  About six dependent loads bound
+// it, whatever the size.
 template <int P>
-__global__ __launch_bounds__(64) void k_plan_fast(StepArgs a, FastTile *out)
+__global__ __launch_bounds__(kLanes) void k_plan_fast(StepArgs a, FastPlan pl)
 {
     constexpr int LO = (P - 1) / 2;
-    const int64_t tile = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    static_assert(2 * kPlanGroup == kLanes, "two lanes a tile");
+    __shared__ FastTile srec[kPlanGroup];
     const Rows &R = a.rows;
-    if (tile >= R.n_tiles) return;
+    const MeshTab &tb = R.tab;
+    const int nt = (int)R.n_tiles;
     const int n = (int)R.n_cols;
-    const int64_t tpr = (n + kFT - 1) / kFT;
-    const int64_t row = tile / tpr;
-    const int i0 = (int)(tile - row * tpr) * kFT;
     const int H = a.dv ? 2 : 0;
-    const int nd = min(kFT, n - i0);
     const double *x = R.edges;
     const double len = x[n] - x[0];
-    const RowShift rs = row_shift(a.v0[row] * a.dt, len, R.tab.scal[1]);
-    double xt0;
-    int c0;
-    const int64_t g0 = node_locate(x, n, R.tab, rs, i0 - H, xt0, c0);
-    const int64_t g1 = node_index(x, n, R.tab, rs, len, i0 + nd + H);
+    const int first = (int)blockIdx.x * kPlanGroup;
+    const int t = (int)threadIdx.x;
+    const bool valid = first + (t >> 1) < nt;
+    const int tile = min(first + (t >> 1), nt - 1);
+    const TilePos p = tile_pos(tile, n, H);
+    const int i0 = p.i0, nd = p.nd;
+    const RowShift rs = row_shift(a.v0[p.row] * a.dt, len, tb.scal[1]);
+    double xt;
+    int c;
+    const int64_t g = node_locate(x, n, tb, rs, (t & 1) ? i0 + nd + H : i0 - H, xt, c);
+    const int64_t g0 = __shfl(g, t & ~1), g1 = __shfl(g, t | 1);
     const int64_t wide = g1 - g0 + P;
     const int64_t wlo = g0 - LO;
-    FastTile ft;
-    ft.kind = kFastWindow;
-    ft.w = (wide >= P && wide <= kFastWin) ? (int)wide : -1;
-    const int64_t kk = wlo >= 0 ? wlo / n : -((-wlo + n - 1) / n);
-    ft.base = (int)(wlo - kk * n);
-    ft.wlo_lo = (int32_t)(uint32_t)((uint64_t)wlo & 0xffffffffull);
-    ft.wlo_hi = (int32_t)((uint64_t)wlo >> 32);
-    for (int d = 0; d < 6; ++d) ft.cc[d] = 0.0f;
-    ft.dx = ft.hinv = ft.dxinv = 0.0f;
-    ft.pad[0] = (int32_t)tile;
-    ft.pad[1] = -1;
-    if (ft.w < 0) ft.kind = kFastDirect;
+    const bool fits = wide >= P && wide <= kFastWin;
     // uniform: the cells on both sides of the tile's nodes and its whole source
     // window lie in one uniform run of the mesh, and the window holds one
     // source cell per node plus the stencil, so node i0 - H + k sits in window
     // cell LO + k at the first node's theta (rows shorter than a full tile's
     // window stay with the other kernel, whose windows may wrap many times)
-    auto in_run = [&](const int32_t *pre) {
-        return nonu_count(pre, n, i0 - H - 1, i0 + nd + H + 1) == 0 &&
-               nonu_count(pre, n, wlo, wlo + wide) == 0;
-    };
-    if (ft.kind == kFastWindow && R.tab.nonu && wide == nd + 2 * H + P &&
-        n >= kFT + 2 * H + P && (in_run(R.tab.nonu) || in_run(R.tab.nonu_min))) {
-        ft.kind = kFastUniform;
-        const double th = (xt0 - x[c0]) * R.tab.dxinv[c0];
-        double cc[P + 1];
-        uniform_stencil<double, P>(th, cc);
-        for (int d = 0; d <= P; ++d) ft.cc[d] = (float)cc[d];
-        ft.pad[1] = __float_as_int((float)th);
-        const float2 rr = R.tab.rrf[i0];
-        ft.dx = rr.x;
-        ft.hinv = rr.y;
-        ft.dxinv = R.tab.dxinvf[i0];
+    bool run = false;
+    if (fits && tb.nonu && wide == nd + 2 * H + P && n >= kFT + 2 * H + P) {
+        const int32_t *pre = (t & 1) ? tb.nonu_min : tb.nonu;
+        run = nonu_count(pre, n, i0 - H - 1, i0 + nd + H + 1) == 0 &&
+              nonu_count(pre, n, wlo, wlo + wide) == 0;
     }
-    out[tile] = ft;
+    const int other = __shfl_xor(run ? 1 : 0, 1);
+    const bool uni = run || other != 0;
+    if ((t & 1) == 0) {
+        FastTile ft;
+        ft.kind = uni ? kFastUniform : (fits ? kFastWindow : kFastDirect);
+        ft.w = fits ? (int)wide : -1;
+        const int64_t kk = wlo >= 0 ? wlo / n : -((-wlo + n - 1) / n);
+        ft.base = (int)(wlo - kk * n);
+        ft.wlo_lo = (int32_t)(uint32_t)((uint64_t)wlo & 0xffffffffull);
+        ft.wlo_hi = (int32_t)((uint64_t)wlo >> 32);
+        for (int d = 0; d < 6; ++d) ft.cc[d] = 0.0f;
+        ft.dx = ft.hinv = ft.dxinv = 0.0f;
+        ft.pad[0] = ft.pad[1] = tile;
+        if (uni) {
+            const double th = (xt - x[c]) * tb.dxinv[c];
+            double cc[P + 1];
+            uniform_stencil<double, P>(th, cc);
+            for (int d = 0; d <= P; ++d) ft.cc[d] = (float)cc[d];
+            ft.pad[1] = __float_as_int((float)th);
+            const float2 rr = tb.rrf[i0];
+            ft.dx = rr.x;
+            ft.hinv = rr.y;
+            ft.dxinv = tb.dxinvf[i0];
+        }
+        srec[t >> 1] = ft;
+    }
+    uint64_t mo = __ballot(!uni && valid);           // bits 2 u and 2 u + 1: tile first + u
+    mo &= 0x5555555555555555ull;
+#pragma unroll
+    for (int d = 1; d < 32; d <<= 1) {               // even bits together
+        const uint64_t keep = d == 1 ? 0x3333333333333333ull : d == 2 ? 0x0f0f0f0f0f0f0f0full
+                            : d == 4 ? 0x00ff00ff00ff00ffull : d == 8 ? 0x0000ffff0000ffffull
+                                                                      : 0x00000000ffffffffull;
+        mo = (mo | mo >> d) & keep;
+    }
+    if (t == 0) pl.mask[blockIdx.x] = (uint32_t)mo;
+    wave_sync();
+    // the records out, kWords lanes a record
+    constexpr int kWords = (int)(sizeof(FastTile) / 4);
+    constexpr int kPer = kLanes / kWords;
+#pragma unroll
+    for (int k = 0; k < kPlanGroup / kPer; ++k) {
+        const int u = k * kPer + t / kWords, wd = t % kWords;
+        if (first + u < nt) ((int32_t *)(pl.rec + first + u))[wd] = ((const int32_t *)&srec[u])[wd];
+    }
 }
-
 
 // Residual step on four consecutive cells of a lane from the shifted state
 // s[0..7] of cells i0+4l-2 .. i0+4l+5 (Section 3.1's upwind step with the van
@@ -286,67 +313,171 @@ __device__ __forceinline__ void uniform_tile(const StepArgs &a, const FastTile &
 
 // ---------------------------------------------------------------------------
 // Every other tile.  Its nodes' source cells do not change between the steps
-// of a call, so k_node_plan locates them once (bucket index, Eq.
+// of a call, so k_plan_nodes locates them once (bucket index, Eq.
 // condition_p) and keeps each node's window index and theta; per step a wave
 // then needs two round trips to memory: the window, node data, faces and
 // geometry together, then the source cells' stencil records.
 // ---------------------------------------------------------------------------
 
-// The k-th non-uniform tile's nodes (k = list position - totals[0]): window
-// index and FP32 theta of nodes i0-H .. i0+nd+H, and in the slots past the
-// last node (up to kFastNodes) the last node again, so that whole 16-byte
-// groups of slots can be read; a node outside the window (not expected: the
-// plan sized it from the end nodes) turns the tile into a direct one, in both
-// copies of its record.  One wave per tile.
+// The second half of the plan, in two parts side by side.
+//
+// Lists (workgroups 0 .. lists - 1, a thread a tile): the records of the
+// uniform tiles in tile order without gaps, and the ids of the others.  Tile
+// order, because the uniform kernel on the 2048 x 16384 disk takes 70 us in it
+// and 80 when neighbouring waves run tiles of rows far apart (lists filled by
+// atomics); no gaps, because a wave that finds no tile of its kind keeps its
+// share of the workgroup's LDS from others (searching kernel 47 against 39 us
+// there).
+//
+// Nodes (the other workgroups, kNodeTiles tiles each, whose searching tiles
+// its waves take in turn): window index and FP32 theta of nodes i0-H ..
+// i0+nd+H, and in the slots past the last node (up to kFastNodes) the last node
+// again, so that whole 16-byte groups of slots can be read; a node outside the
+// window (not expected: the plan sized it from the end nodes) turns the tile
+// into a direct one.
+constexpr int kNodeTiles = 8;
+
+// Rows a multiple of eight workgroups long have their searching tiles in the
+// same workgroups of every row, and workgroups go to the chip's eight XCDs in
+// turn: each run of eight is rotated by its number (and by the number's higher
+// octal digits), so that every XCD gets its share.
+__device__ __forceinline__ int spread8(int b)
+{
+    const int o = b >> 3;
+    return (b & ~7) | ((b + o + (o >> 3) + (o >> 6) + (o >> 9)) & 7);
+}
+
+__device__ __forceinline__ void plan_lists(const FastPlan &pl, int nt, int block)
+{
+    __shared__ int sred[kWaves];
+    const int t = (int)threadIdx.x;
+    constexpr int kGroups = kBlock / kPlanGroup;     // groups of this workgroup's tiles
+    const int g0 = block * kGroups, ng = (nt + kPlanGroup - 1) / kPlanGroup;
+    // the other tiles before this workgroup's
+    int before = 0;
+    for (int g = t; g < g0; g += kBlock) before += __popc(pl.mask[g]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) before += __shfl_xor(before, d);
+    if (t % kLanes == 0) sred[t / kLanes] = before;
+    uint32_t m[kGroups];
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) m[k] = g0 + k < ng ? pl.mask[g0 + k] : 0;
+    __syncthreads();
+    before = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) before += sred[w];
+    const int tile = block * kBlock + t;
+    const int bit = t % kPlanGroup;
+    bool other = false;
+    int all = before;
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) {
+        if (k == t / kPlanGroup) {
+            before = all + __popc(m[k] & ((1u << bit) - 1u));
+            other = (m[k] >> bit & 1u) != 0;
+        }
+        all += __popc(m[k]);
+    }
+    if (tile < nt) {
+        if (other) {
+            pl.oid[before] = tile;
+        } else {
+            const float4 *from = (const float4 *)(pl.rec + tile);
+            float4 *to = (float4 *)(pl.urec + (tile - before));
+            const float4 v0 = from[0], v1 = from[1], v2 = from[2], v3 = from[3];
+            to[0] = v0;
+            to[1] = v1;
+            to[2] = v2;
+            to[3] = v3;
+        }
+        if (tile == nt - 1) {
+            pl.totals[0] = nt - all;
+            pl.totals[1] = all;
+        }
+    }
+}
+
 template <int P>
-__global__ __launch_bounds__(kBlock) void k_node_plan(StepArgs a)
+__global__ __launch_bounds__(kBlock) void k_plan_nodes(StepArgs a, int lists)
 {
     constexpr int LO = (P - 1) / 2;
     constexpr int NS = (kFastNodes + kLanes - 1) / kLanes;
-    const Rows &R = a.rows;
-    const int nu = a.fast.totals[0];
-    const int nt = (int)R.n_tiles;
-    const int k = (int)blockIdx.x * kWaves + wave_id();
-    if (nu + k >= nt) return;
-    FastTile *crec = a.fast.rec + nt;
-    const FastTile ft = load_rec(crec, nu + k);
-    if (ft.kind != kFastWindow) return;
+    const int nt = (int)a.rows.n_tiles;
+    if ((int)blockIdx.x < lists) {
+        plan_lists(a.fast, nt, (int)blockIdx.x);
+        return;
+    }
+    const int first = spread8((int)blockIdx.x - lists) * kNodeTiles;
+    if (first >= nt) return;
+    uint32_t todo = a.fast.mask[first / kPlanGroup] >> (first % kPlanGroup) & ((1u << kNodeTiles) - 1u);
+    const int wid = wave_id();
+    const MeshTab &tb = a.rows.tab;
+    const int n = (int)a.rows.n_cols;
     const int H = a.dv ? 2 : 0;
-    const int t = threadIdx.x % kLanes;
-    const MeshTab &tb = R.tab;
-    const int n = (int)R.n_cols;
-    const TilePos tp = tile_pos(ft.pad[0], n, H);
-    const int NE = tp.nd + 2 * H + 1;
-    const double *x = R.edges;
+    const int t = (int)threadIdx.x % kLanes;
+    const double *x = a.rows.edges;
     const double x0 = x[0], xN = x[n];
     const double len = xN - x0;
-    const RowShift rs = row_shift(a.v0[tp.row] * a.dt, len, tb.scal[1]);
-    const int64_t wlo = (int64_t)(((uint64_t)(uint32_t)ft.wlo_hi << 32) | (uint32_t)ft.wlo_lo);
-    const int jbase = (int)(rs.kf0 * (int64_t)n - wlo);
-    float *th = a.fast.theta + (int64_t)k * kFastNodes;
-    int16_t *jcw = a.fast.jc + (int64_t)k * kFastNodes;
-    bool ok = true;
+    for (int turn = 0; todo != 0; ++turn) {
+        const int tile = first + __ffs((int)todo) - 1;
+        todo &= todo - 1;
+        if (turn % kWaves != wid) continue;
+        const FastTile ft = load_rec(a.fast.rec, tile);
+        if (ft.kind != kFastWindow) continue;
+        const TilePos tp = tile_pos(tile, n, H);
+        const int NE = tp.nd + 2 * H + 1;
+        const RowShift rs = row_shift(a.v0[tp.row] * a.dt, len, tb.scal[1]);
+        const int64_t wlo = (int64_t)(((uint64_t)(uint32_t)ft.wlo_hi << 32) | (uint32_t)ft.wlo_lo);
+        const int jbase = (int)(rs.kf0 * (int64_t)n - wlo);
+        float *th = a.fast.theta + (int64_t)tile * kFastNodes;
+        int16_t *jcw = a.fast.jc + (int64_t)tile * kFastNodes;
+        // each load of all the lane's nodes before the next one's: x, the
+        // bucket, the cell's geometry (lanes past the last slot repeat it)
+        int ce[NS], kx[NS];
+        double xt[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int m = t + s * kLanes;
-        if (m < kFastNodes) {
-            int e = tp.i0 - H + min(m, NE - 1);
-            const int kx = e < 0 ? -n : (e >= n ? n : 0);
-            e -= kx;
-            const NodePos np = node_pos(x[e], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
-            const double2 nx = tb.bnext[np.b];
-            int c = cell_from_bucket(tb.bucket[np.b], nx, np.xt);
-            if (np.xt >= nx.y) c = cell_walk(x, n, c, np.xt);
-            const CellRec<float> &rc = RecT<float>::get(tb)[c];
-            const int j = c + np.dk * n + kx + jbase;
+        for (int s = 0; s < NS; ++s) {
+            const int m = min(t + s * kLanes, kFastNodes - 1);
+            const int en = tp.i0 - H + min(m, NE - 1);
+            kx[s] = en < 0 ? -n : (en >= n ? n : 0);
+            xt[s] = x[en - kx[s]];
+        }
+        double2 nx[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const NodePos np = node_pos(xt[s], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
+            ce[s] = tb.bucket[np.b];
+            nx[s] = tb.bnext[np.b];
+            xt[s] = np.xt;
+            kx[s] += np.dk * n;
+        }
+        bool walk = false;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            ce[s] = cell_from_bucket(ce[s], nx[s], xt[s]);
+            walk = walk || xt[s] >= nx[s].y;
+        }
+        if (__any(walk ? 1 : 0)) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (xt[s] >= nx[s].y) ce[s] = cell_walk(x, n, ce[s], xt[s]);
+        }
+        double xc[NS], di[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            xc[s] = x[ce[s]];
+            di[s] = tb.dxinv[ce[s]];
+        }
+        bool ok = true;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int m = min(t + s * kLanes, kFastNodes - 1);
+            const int j = ce[s] + kx[s] + jbase;
             ok = ok && j >= LO && j + P - LO <= ft.w;
-            th[m] = (float)((np.xt - rc.xc) * rc.dxinv);
+            th[m] = (float)((xt[s] - xc[s]) * di[s]);
             jcw[m] = (int16_t)min(max(j, 0), kFastWin);
         }
-    }
-    if (!__all(ok ? 1 : 0) && t == 0) {
-        a.fast.rec[ft.pad[0]].kind = kFastDirect;
-        crec[nu + k].kind = kFastDirect;
+        if (!__all(ok ? 1 : 0) && t == 0) a.fast.rec[tile].kind = kFastDirect;
     }
 }
 
@@ -454,7 +585,7 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
     float *sw = (float *)su;                         // window masses
     int64_t *sg = (int64_t *)su;                     // direct path: node indices
     float *sq = (float *)su;                         // shifted state
-    const int k = ft.pad[1];                         // position among the other tiles
+    const int k = ft.pad[1];                         // the tile's node data
     const MeshTab &tb = R.tab;
     const int n = (int)R.n_cols;
     const int c4 = 4 * t;
@@ -958,105 +1089,16 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     }
 }
 
-// ---------------------------------------------------------------------------
-// The compacted records, in tile order: uniform tiles first, then the others
-// (for the node plan), each with its tile id in pad[0]; the others' position
-// among them (their node data) in pad[1] of both copies.
-// ---------------------------------------------------------------------------
-
-__global__ __launch_bounds__(1024) void k_tile_count(const FastTile *rec, int nt, int32_t *counts)
-{
-    __shared__ int swc[16];
-    const int j = (int)blockIdx.x * 1024 + (int)threadIdx.x;
-    const bool u = j < nt && rec[j].kind == kFastUniform;
-    const int c = __popcll(__ballot(u));
-    if ((threadIdx.x & 63) == 0) swc[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int s = 0;
-        for (int w = 0; w < 16; ++w) s += swc[w];
-        counts[blockIdx.x] = s;
-    }
-}
-
-__global__ __launch_bounds__(1024) void k_tile_lists(FastTile *rec, int nt,
-                                                     const int32_t *counts, int nb,
-                                                     FastTile *crec, int32_t *totals)
-{
-    __shared__ int sred[2][16];
-    __shared__ int swo[2][17];
-    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // uniform tiles before this block and in total
-    int before = 0, all = 0;
-    for (int b = tid; b < nb; b += 1024) {
-        const int c = counts[b];
-        all += c;
-        if (b < (int)blockIdx.x) before += c;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        before += __shfl_xor(before, o, 64);
-        all += __shfl_xor(all, o, 64);
-    }
-    if (lane == 0) {
-        sred[0][wv] = before;
-        sred[1][wv] = all;
-    }
-    const int j = (int)blockIdx.x * 1024 + tid;
-    const bool in = j < nt;
-    const bool u = in && rec[j].kind == kFastUniform;
-    const uint64_t mu = __ballot(u), mg = __ballot(in && !u);
-    const uint64_t below = (1ull << lane) - 1ull;
-    if (lane == 0) {
-        swo[0][wv + 1] = __popcll(mu);
-        swo[1][wv + 1] = __popcll(mg);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int b0 = 0, a0 = 0;
-        for (int w = 0; w < 16; ++w) {
-            b0 += sred[0][w];
-            a0 += sred[1][w];
-        }
-        sred[0][0] = b0;
-        sred[1][0] = a0;
-        swo[0][0] = swo[1][0] = 0;
-        for (int w = 1; w <= 16; ++w) {
-            swo[0][w] += swo[0][w - 1];
-            swo[1][w] += swo[1][w - 1];
-        }
-        if (blockIdx.x == 0) {
-            totals[0] = a0;
-            totals[1] = nt - a0;
-        }
-    }
-    __syncthreads();
-    const int ub = sred[0][0], utot = sred[1][0];
-    const int gb = (int)blockIdx.x * 1024 - ub;      // other tiles before this block
-    if (in) {
-        int pos;
-        if (u) pos = ub + swo[0][wv] + __popcll(mu & below);
-        else pos = utot + gb + swo[1][wv] + __popcll(mg & below);
-        FastTile r = rec[j];
-        if (!u) {
-            r.pad[1] = pos - utot;                   // the tile's node data
-            rec[j].pad[1] = r.pad[1];
-        }
-        crec[pos] = r;
-    }
-}
-
-// The step, in two kernels, one tile a wave: the uniform tiles (the
-// compacted list's first part; 26 registers, eight waves a SIMD), then the
-// other tiles (the rest of the list).  Both grids span the whole tile count
-// (the host does not know the split); the waves past their part of the list
-// return at once.  Measured alternatives on the refined disk: one kernel over
-// both kinds (in tile order, or the other tiles spread evenly through the
-// grid) ran the uniform tiles at the other path's register and LDS footprint
-// and took 135-163 us a step against 123; persistent waves striding over the
-// other tiles, 128-157; the two kernels on two streams with an event pair
-// around every eager step, 342.  Inside a captured step loop the two kernels
-// are parallel branches of the graph (fork / join events, ForkJoin): the
-// latency-bound searching tiles then run beside the HBM-bound uniform ones.
+// The step, in two kernels, one tile a wave: the uniform tiles (26 registers,
+// eight waves a SIMD), then the other tiles, each from its list.  Measured
+// alternatives on the refined disk: one kernel over both kinds (in tile order,
+// or the other tiles spread evenly through the grid) ran the uniform tiles at
+// the other path's register and LDS footprint and took 135-163 us a step
+// against 123; persistent waves striding over the other tiles, 128-157; the
+// two kernels on two streams with an event pair around every eager step, 342.
+// Inside a captured step loop the two kernels are parallel branches of the
+// graph (fork / join events, ForkJoin): the latency-bound searching tiles then
+// run beside the HBM-bound uniform ones.
 template <int P, int H, bool VEC>
 __global__ __launch_bounds__(kBlock, 8) void k_step_uni(StepArgs a)
 {
@@ -1064,7 +1106,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_step_uni(StepArgs a)
     const int wid = wave_id();
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= a.fast.totals[0]) return;
-    const FastTile r = load_rec(a.fast.rec + a.rows.n_tiles, i);
+    const FastTile r = load_rec(a.fast.urec, i);
     uniform_tile<P, H, VEC>(a, r, swin[wid], (int)threadIdx.x % kLanes);
 }
 
@@ -1184,14 +1226,11 @@ __global__ __launch_bounds__(kBlock) void k_step_uni_lim(StepArgs a)
     const int wid = wave_id();
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= a.fast.totals[0]) return;
-    const FastTile r = load_rec(a.fast.rec + a.rows.n_tiles, i);
+    const FastTile r = load_rec(a.fast.urec, i);
     uniform_tile_lim<R, H, VEC>(a, r, swin[wid], (int)threadIdx.x % kLanes);
 }
 
-// The other tiles: a grid of a quarter of the tile count in waves (the host
-// does not know how many there are; a quarter covers the refined disk with
-// one tile a wave), each wave stepping through the list by the grid's size.
-constexpr int kGenShare = 4;
+// The other tiles.
 
 template <int P, int H, bool VEC, int S>
 __global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
@@ -1200,12 +1239,11 @@ __global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
     __shared__ __attribute__((aligned(16))) float sell_[kWaves][WaveLds::nodes];
     __shared__ __attribute__((aligned(16))) short sjc_[kWaves][WaveLds::nodes];
     const int wid = wave_id();
-    const int nt = (int)a.rows.n_tiles;
     const int n = (int)a.rows.n_cols;
     const int t = (int)threadIdx.x % kLanes;
-    const int stride = (int)gridDim.x * kWaves;
-    for (int i = a.fast.totals[0] + (int)blockIdx.x * kWaves + wid; i < nt; i += stride) {
-        const FastTile r = load_rec(a.fast.rec + nt, i);
+    const int total = a.fast.totals[1];
+    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+        const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
         if (VEC && r.kind == kFastWindow && r.base + r.w + 3 < 2 * n)
             window_tile<P, H, S>(a, r, su[wid], sell_[wid], sjc_[wid], t);
         else
@@ -1217,8 +1255,7 @@ __global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
 template <int P, int H, bool VEC, int S>
 hipError_t step_fast_kernels(const StepArgs &a, hipStream_t st)
 {
-    const dim3 g((unsigned)((a.rows.n_tiles + kWaves - 1) / kWaves)), b(kBlock);
-    const dim3 gg((unsigned)((a.rows.n_tiles + kWaves * kGenShare - 1) / (kWaves * kGenShare)));
+    const dim3 g(uniform_grid(a.rows.n_tiles)), b(kBlock), gg(other_grid(a.rows.n_tiles));
     if (const ForkJoin *fj = capture_fork) {
         // the two kinds of tile write disjoint cells and read only q_in: the
         // searching tiles' kernel on the side stream, between a fork after
@@ -1272,11 +1309,10 @@ __global__ __launch_bounds__(kBlock) void k_step_gen_lim(StepArgs a)
     __shared__ __attribute__((aligned(16))) float sell_[kWaves][WaveLds::nodes];
     __shared__ __attribute__((aligned(16))) short sjc_[kWaves][WaveLds::nodes];
     const int wid = wave_id();
-    const int nt = (int)a.rows.n_tiles;
     const int t = (int)threadIdx.x % kLanes;
-    const int stride = (int)gridDim.x * kWaves;
-    for (int i = a.fast.totals[0] + (int)blockIdx.x * kWaves + wid; i < nt; i += stride) {
-        const FastTile r = load_rec(a.fast.rec + nt, i);
+    const int total = a.fast.totals[1];
+    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+        const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
         general_tile<P, H, VEC, R>(a, r, su[wid], sell_[wid], sjc_[wid], t);
         wave_sync();                                 // the next tile reuses the LDS
     }
@@ -1285,8 +1321,7 @@ __global__ __launch_bounds__(kBlock) void k_step_gen_lim(StepArgs a)
 template <int R, int H, bool VEC>
 hipError_t step_fast_lim_kernels(const StepArgs &a, hipStream_t st)
 {
-    const dim3 g((unsigned)((a.rows.n_tiles + kWaves - 1) / kWaves)), b(kBlock);
-    const dim3 gg((unsigned)((a.rows.n_tiles + kWaves * kGenShare - 1) / (kWaves * kGenShare)));
+    const dim3 g(uniform_grid(a.rows.n_tiles)), b(kBlock), gg(other_grid(a.rows.n_tiles));
     if (const ForkJoin *fj = capture_fork) {
         // parallel graph branches, as in step_fast_kernels
         hipError_t e = hipEventRecord(fj->fork, st);
@@ -1640,25 +1675,25 @@ hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan,
 {
     if (a.rows.n_tiles <= 0) return hipSuccess;
     if (a.rows.tile != kFastTile || a.rows.n_tiles > INT32_MAX / 2) return hipErrorInvalidValue;
-    const int nt = (int)a.rows.n_tiles;
-    const unsigned grid = (unsigned)((nt + 63) / 64);
-    switch (order) {
-    case 1: hipLaunchKernelGGL(k_plan_fast<1>, dim3(grid), dim3(64), 0, stream, a, plan.rec); break;
-    case 3: hipLaunchKernelGGL(k_plan_fast<3>, dim3(grid), dim3(64), 0, stream, a, plan.rec); break;
-    default: hipLaunchKernelGGL(k_plan_fast<5>, dim3(grid), dim3(64), 0, stream, a, plan.rec); break;
-    }
-    const int nb = (nt + 1023) / 1024;
-    hipLaunchKernelGGL(k_tile_count, dim3(nb), dim3(1024), 0, stream, plan.rec, nt, plan.counts);
-    // the compacted records follow the per-tile ones (fast_plan_bytes)
-    hipLaunchKernelGGL(k_tile_lists, dim3(nb), dim3(1024), 0, stream, plan.rec, nt, plan.counts,
-                       nb, plan.rec + nt, plan.totals);
     StepArgs b = a;
     b.fast = plan;
-    const dim3 gn((unsigned)((nt + kWaves - 1) / kWaves));
+    const int64_t nt = a.rows.n_tiles;
+    const int lists = (int)((nt + kBlock - 1) / kBlock);
+    const int64_t nodes = ((nt + kNodeTiles - 1) / kNodeTiles + 7) / 8 * 8;
+    const dim3 gt((unsigned)plan_groups(nt)), bt(kLanes), gn((unsigned)(lists + nodes)), bn(kBlock);
     switch (order) {
-    case 1: hipLaunchKernelGGL(k_node_plan<1>, gn, dim3(kBlock), 0, stream, b); break;
-    case 3: hipLaunchKernelGGL(k_node_plan<3>, gn, dim3(kBlock), 0, stream, b); break;
-    default: hipLaunchKernelGGL(k_node_plan<5>, gn, dim3(kBlock), 0, stream, b); break;
+    case 1:
+        hipLaunchKernelGGL(k_plan_fast<1>, gt, bt, 0, stream, a, plan);
+        hipLaunchKernelGGL(k_plan_nodes<1>, gn, bn, 0, stream, b, lists);
+        break;
+    case 3:
+        hipLaunchKernelGGL(k_plan_fast<3>, gt, bt, 0, stream, a, plan);
+        hipLaunchKernelGGL(k_plan_nodes<3>, gn, bn, 0, stream, b, lists);
+        break;
+    default:
+        hipLaunchKernelGGL(k_plan_fast<5>, gt, bt, 0, stream, a, plan);
+        hipLaunchKernelGGL(k_plan_nodes<5>, gn, bn, 0, stream, b, lists);
+        break;
     }
     return hipGetLastError();
 }

@@ -6,7 +6,7 @@
 // step with the van Leer slope of Section 3.1) in the FP32 path's streaming
 // layout: one tile of kFastTile destination cells per wave, no workgroup
 // barrier, each tile's window and node data planned once per call
-// (k_plan_fast, k_node_plan).  What FP64 changes:
+// (k_plan_fast).  What FP64 changes:
 //   * no stencil shortcut on uniform runs.  A run counts as uniform when its
 //     cell sizes agree to kUniformTol of their size, far above FP64 rounding
 //     (the bisection-solved meshes here vary by about 1e-11), so every node's

@@ -40,10 +40,10 @@ __device__ inline TilePos tile_pos(int tile, int n, int H)
     return p;
 }
 
-// Record i, read through the constant address space: with a wave-uniform i
-// these are scalar loads (the host pass, which only checks device code, reads
-// it plainly).
-__device__ inline FastTile load_rec(const FastTile *rec, int i)
+// A record, read through the constant address space: with a wave-uniform
+// address these are scalar loads (the host pass, which only checks device
+// code, reads it plainly).
+__device__ inline FastTile load_rec(const FastTile *rec, int64_t i = 0)
 {
     FastTile r;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -56,6 +56,26 @@ __device__ inline FastTile load_rec(const FastTile *rec, int i)
     r = rec[i];
 #endif
     return r;
+}
+
+// A word of a table the same way.
+__device__ inline int load_index(const int32_t *p, int i)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return ((const __attribute__((address_space(4))) int32_t *)p)[i];
+#else
+    return p[i];
+#endif
+}
+
+// The step kernels' grids: the host does not know how the tiles split, so the
+// uniform kernels' has a wave for every tile (the ones past totals[0] return
+// at once), the others' a wave for every fourth (the refined disk has fewer),
+// each stepping through the list by the grid's size.
+inline unsigned uniform_grid(int64_t n_tiles) { return (unsigned)((n_tiles + kWaves - 1) / kWaves); }
+inline unsigned other_grid(int64_t n_tiles)
+{
+    return (unsigned)((n_tiles + 4 * kWaves - 1) / (4 * kWaves));
 }
 
 // Wave index inside the workgroup, in a scalar register (so that what it
