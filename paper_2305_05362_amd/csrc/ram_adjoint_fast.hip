@@ -1403,24 +1403,52 @@ __global__ __launch_bounds__(kBlock) void k_adjf_uni(StepAdjArgs a)
     adj_uniform_tile<P, RES, V0>(a, r, su[wid], (int)threadIdx.x % kLanes);
 }
 
-// The other tiles.
+// The other tiles: wave `wave` of `waves`.
+struct AdjGenLds {
+    __attribute__((aligned(16))) unsigned char su[kWaves][kGenU];
+    __attribute__((aligned(16))) float smb[kWaves][kFT + 8];
+};
 template <int P, bool RES, bool V0>
-__global__ __launch_bounds__(kBlock) void k_adjf_gen(StepAdjArgs a)
+__device__ __forceinline__ void adj_other_tiles(const StepAdjArgs &a, AdjGenLds &lds, int wave,
+                                                int waves)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char su[kWaves][kGenU];
-    __shared__ __attribute__((aligned(16))) float smb[kWaves][kFT + 8];
     const int wid = wave_id();
     const int n = (int)a.rows.n_cols;
     const int t = (int)threadIdx.x % kLanes;
     const int total = a.fast.totals[1];
-    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+    for (int i = wave; i < total; i += waves) {
         const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
         if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n)
-            adj_window_tile<P, RES, V0>(a, r, su[wid], smb[wid], t);
+            adj_window_tile<P, RES, V0>(a, r, lds.su[wid], lds.smb[wid], t);
         else
-            adj_direct_tile<P, RES, V0>(a, r, su[wid], smb[wid], t);
+            adj_direct_tile<P, RES, V0>(a, r, lds.su[wid], lds.smb[wid], t);
         wave_sync();                                 // the next tile reuses the LDS
     }
+}
+
+template <int P, bool RES, bool V0>
+__global__ __launch_bounds__(kBlock) void k_adjf_gen(StepAdjArgs a)
+{
+    __shared__ AdjGenLds lds;
+    adj_other_tiles<P, RES, V0>(a, lds, (int)blockIdx.x * kWaves + wave_id(), (int)gridDim.x * kWaves);
+}
+
+// Both kinds in one launch, as the forward's k_step_both: the first `others`
+// workgroups the other tiles, the rest the uniform ones.
+template <int P, bool RES, bool V0>
+__global__ __launch_bounds__(kBlock) void k_adjf_both(StepAdjArgs a, int others)
+{
+    __shared__ AdjGenLds lds;
+    const int wid = wave_id();
+    if ((int)blockIdx.x < others) {
+        adj_other_tiles<P, RES, V0>(a, lds, (int)blockIdx.x * kWaves + wid, others * kWaves);
+        return;
+    }
+    const int i = ((int)blockIdx.x - others) * kWaves + wid;
+    if (i >= a.fast.totals[0]) return;
+    static_assert(sizeof(lds.su[0]) >= sizeof(float) * 3 * kStage, "a uniform tile's arrays");
+    adj_uniform_tile<P, RES, V0>(a, load_rec(a.fast.urec, i), (float *)lds.su[wid],
+                                 (int)threadIdx.x % kLanes);
 }
 
 template <int P, bool RES, bool V0>
@@ -1429,7 +1457,10 @@ hipError_t adjf_kernels(const StepAdjArgs &a, hipStream_t st)
     const int64_t nt = a.rows.n_tiles;
     const dim3 b(kBlock);
     const dim3 gu(uniform_grid(nt)), gg(other_grid(nt));
-    if (const ForkJoin *fj = capture_fork) {
+    if (nt < kTogether) {
+        const unsigned others = gu.x;                // a wave a tile: it may be any of them
+        hipLaunchKernelGGL((k_adjf_both<P, RES, V0>), dim3(2 * others), b, 0, st, a, (int)others);
+    } else if (const ForkJoin *fj = capture_fork) {
         // inside a captured loop: the two kinds of tile (disjoint outputs and
         // partials) as parallel graph branches, joined before the edges pass
         hipError_t e = hipEventRecord(fj->fork, st);

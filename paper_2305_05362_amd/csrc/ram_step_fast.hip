@@ -190,6 +190,14 @@ __device__ __forceinline__ void residual4(const float *s, const float *dvv, floa
 }
 
 
+// Four consecutive cells at any cell of a row: global loads and stores need
+// only their word's alignment, so rows whose length is not a multiple of four
+// (VEC false below) take 16-byte accesses too, wherever the four cells lie in
+// the row (`full`: the tile and one cell beyond do, for every lane).
+struct f4u {
+    float __attribute__((ext_vector_type(4), aligned(4))) v;
+};
+
 // Residual velocity of faces i0+4l .. i0+4l+4 of a row (face n is face 0);
 // lanes past the tile read its last faces again (every load issued, no
 // branch).
@@ -200,6 +208,12 @@ __device__ __forceinline__ void load_faces(const float *dvp, int n, int i0, int 
     const int cc = min(c4, nd - 1);
     if constexpr (VEC) {
         const float4 v4 = ld_at<float4>(dvp + i0, 4u * (uint32_t)(cc & ~3));
+        dvv[0] = v4.x;
+        dvv[1] = v4.y;
+        dvv[2] = v4.z;
+        dvv[3] = v4.w;
+    } else if (nd == kFT) {                          // cells i0 .. i0 + 255 in the row
+        const auto v4 = ld_at<f4u>(dvp + i0, 4u * (uint32_t)c4).v;
         dvv[0] = v4.x;
         dvv[1] = v4.y;
         dvv[2] = v4.z;
@@ -219,6 +233,12 @@ __device__ __forceinline__ void load_faces(const float *dvp, int n, int i0, int 
 template <bool VEC>
 __device__ __forceinline__ void store_cells(float *qo, int i0, int nd, int c4, const float *o)
 {
+    if constexpr (!VEC) {
+        if (nd == kFT) {
+            st_at<f4u>(qo + i0, 4u * (uint32_t)c4, {{o[0], o[1], o[2], o[3]}});
+            return;
+        }
+    }
     if (c4 >= nd) return;
     if constexpr (VEC) {
         st_at<float4>(qo + i0, 4u * (uint32_t)c4, make_float4(o[0], o[1], o[2], o[3]));
@@ -297,12 +317,7 @@ __device__ __forceinline__ void uniform_tile(const StepArgs &a, const FastTile &
     if constexpr (H == 0) {
         store_cells<VEC>(qo, p.i0, p.nd, c4, s);
     } else {
-        if (a.q_mid && c4 < p.nd) {
-            float *qm = (float *)a.q_mid + qoff;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (c4 + k < p.nd) qm[p.i0 + c4 + k] = s[k + 2];
-        }
+        if (a.q_mid) store_cells<VEC>((float *)a.q_mid + qoff, p.i0, p.nd, c4, s + 2);
         const float2 g = make_float2(r.dx, r.hinv);
         const float dxi = r.dxinv;
         float o[4];
@@ -780,8 +795,8 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 }
 
 // ---------------------------------------------------------------------------
-// A searching tile whose window fits the wave's LDS, on rows of a multiple of
-// four cells (16-byte aligned), with every load of a phase in flight at once:
+// A searching tile whose window fits the wave's LDS, with every load of a phase
+// in flight at once:
 //   1. the nodes' plan (window index, theta), the window's values and cell
 //      sizes in 16-byte groups, the faces' residual velocity;
 //   2. the window masses into LDS; the stencil data of all the lane's
@@ -797,8 +812,14 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 // m mod 64, counted from the tile's first halo node/cell), so that the LDS
 // gathers of neighbouring lanes fall on neighbouring words: four consecutive
 // nodes a lane put their gathers 16 bytes apart, eight lanes on each bank.
-// The window is stored from the 16-byte boundary at or below its start (LDS
-// index j + off for window cell j), so that its groups go in whole.
+// VEC: rows of a multiple of four cells, 16-byte aligned: the window is stored
+// from the 16-byte boundary at or below its start (LDS index j + off for
+// window cell j), so that its groups go in whole, also across the row's end.
+// Other rows read the groups from the window's start (off = 0) at a word's
+// alignment, and cell by cell where a window or a tile's neighbourhood crosses
+// the row's end; their cumulative differences are always summed directly.  At
+// 1000 x 6001 cells, all searching, 58 us a step; with one node's 64-byte record
+// and one word a load (general_tile), 80.
 // ---------------------------------------------------------------------------
 
 // The prefix modes (S other than kSumDirect): the window's exclusive
@@ -837,7 +858,7 @@ __device__ __forceinline__ void wave_prefix(typename Acc<S>::A *sp, const typena
     carry = AC::comb(carry, lane63(inc));
 }
 
-template <int P, int H, int S>
+template <int P, int H, int S, bool VEC>
 __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &ft,
                                             unsigned char *su, float *sell, short *sjc, int t)
 {
@@ -845,6 +866,7 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     using A = typename AC::A;
     using M = typename AC::M;
     constexpr bool kDirect = S == kSumDirect;
+    static_assert(VEC || kDirect, "rows not a multiple of four sum directly");
     constexpr int LO = (P - 1) / 2;
     constexpr int NG = 2;                            // window groups of 4 a lane loads first
     constexpr int NS = (kFT + 2 * H + 1 + kLanes - 1) / kLanes;   // node slots
@@ -860,9 +882,12 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     const float *q = (const float *)a.q_in + qoff;
     float *qo = (float *)a.q_out + qoff;
     const int W = ft.w, base = ft.base;
-    const int a0 = base & ~3, off = base - a0;
+    const int a0 = VEC ? base & ~3 : base, off = base - a0;
     const int gl = (W + off - 1) >> 2;               // last window group
     float *sw = (float *)su;                         // window mass j at sw[j + off]
+    // the window's groups / the tile with its neighbourhood lie in the row
+    const bool groups = VEC || base + 4 * (gl + 1) <= n;
+    const bool full = VEC || (i0 >= 2 && i0 + kFT + 4 <= n);
 
     // ---- 1. node plan, window, faces ------------------------------------------
     const float *thp = a.fast.theta + (int64_t)ft.pad[1] * kFastNodes;
@@ -879,24 +904,56 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     constexpr bool kDx64 = S == kScanF64;
     float4 wq[NG], wd[NG];
     double2 wd2[kDx64 ? NG : 1][2];
-#pragma unroll
-    for (int u = 0; u < NG; ++u) {
-        int c = a0 + 4 * min(t + u * kLanes, gl);
-        c = c >= n ? c - n : c;
-        wq[u] = ld_at<float4>(q, 4u * (uint32_t)c);
-        if constexpr (kDx64) {
-            wd2[u][0] = ld_at<double2>(tb.dx, 8u * (uint32_t)c);
-            wd2[u][1] = ld_at<double2>(tb.dx, 8u * (uint32_t)c + 16u);
+    auto load4 = [&](const float *p, int c) {
+        if constexpr (VEC) {
+            return ld_at<float4>(p, 4u * (uint32_t)c);
         } else {
-            wd[u] = ld_at<float4>(tb.dxf, 4u * (uint32_t)c);
+            const auto v = ld_at<f4u>(p, 4u * (uint32_t)c).v;
+            return make_float4(v.x, v.y, v.z, v.w);
+        }
+    };
+    if (groups) {
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            int c = a0 + 4 * min(t + u * kLanes, gl);
+            c = VEC && c >= n ? c - n : c;
+            wq[u] = load4(q, c);
+            if constexpr (kDx64) {
+                wd2[u][0] = ld_at<double2>(tb.dx, 8u * (uint32_t)c);
+                wd2[u][1] = ld_at<double2>(tb.dx, 8u * (uint32_t)c + 16u);
+            } else {
+                wd[u] = load4(tb.dxf, c);
+            }
         }
     }
     float dvv[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-    if constexpr (H != 0) load_faces<true>((const float *)a.dv + qoff, n, i0, nd, c4, dvv);
+    if constexpr (H != 0) load_faces<VEC>((const float *)a.dv + qoff, n, i0, nd, c4, dvv);
     float4 di4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if constexpr (H == 0) di4 = *(const float4 *)(tb.dxinvf + i0 + min(c4, nd - 4));
+    if constexpr (H == 0) {
+        if (VEC || nd == kFT) {
+            di4 = *(const float4 *)(tb.dxinvf + i0 + (VEC ? min(c4, nd - 4) : c4));
+        } else {
+            float *d = &di4.x;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) d[k] = tb.dxinvf[i0 + min(c4 + k, nd - 1)];
+        }
+    }
     A *sp = (A *)su;                                 // prefix modes: cumulative at j + off
-    if constexpr (kDirect) {
+    if (!groups) {
+        // the window crosses the row's end
+        for (int r0 = 0; r0 < W; r0 += 4 * kLanes) {
+            float vq[4], vd[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                int c = base + min(r0 + t + u * kLanes, W - 1);
+                c = c >= n ? c - n : c;
+                vq[u] = q[c];
+                vd[u] = tb.dxf[c];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sw[min(r0 + t + u * kLanes, W - 1)] = vq[u] * vd[u];
+        }
+    } else if constexpr (kDirect) {
 #pragma unroll
         for (int u = 0; u < NG; ++u) {
             const int g = min(t + u * kLanes, gl);
@@ -907,9 +964,9 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
         for (int u = NG; u * kLanes <= gl; ++u) {
             const int g = min(t + u * kLanes, gl);
             int c = a0 + 4 * g;
-            c = c >= n ? c - n : c;
-            const float4 vq = ld_at<float4>(q, 4u * (uint32_t)c);
-            const float4 vd = ld_at<float4>(tb.dxf, 4u * (uint32_t)c);
+            c = VEC && c >= n ? c - n : c;
+            const float4 vq = load4(q, c);
+            const float4 vd = load4(tb.dxf, c);
             *(float4 *)(sw + 4 * g) = make_float4(vq.x * vd.x, vq.y * vd.y, vq.z * vd.z, vq.w * vd.w);
         }
     } else {
@@ -1046,20 +1103,29 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     float2 rr[8];
     float dxi[8];
     if constexpr (H != 0) {
-        const int cb = i0 + min(c4, nd - 4) - 2;
-        auto wr = [&](int c) { return c < 0 ? c + n : (c >= n ? c - n : c); };
+        if (full) {
+            const int cb = i0 + (VEC ? min(c4, nd - 4) : c4) - 2;
+            auto wr = [&](int c) { return VEC ? (c < 0 ? c + n : (c >= n ? c - n : c)) : c; };
 #pragma unroll
-        for (int pr = 0; pr < 4; ++pr) {
-            const float4 r2 = ld_at<float4>(tb.rrf, 8u * (uint32_t)wr(cb + 2 * pr));
-            rr[2 * pr] = make_float2(r2.x, r2.y);
-            rr[2 * pr + 1] = make_float2(r2.z, r2.w);
+            for (int pr = 0; pr < 4; ++pr) {
+                const float4 r2 = ld_at<float4>(tb.rrf, 8u * (uint32_t)wr(cb + 2 * pr));
+                rr[2 * pr] = make_float2(r2.x, r2.y);
+                rr[2 * pr + 1] = make_float2(r2.z, r2.w);
+            }
+            const float2 d0 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb));
+            const float4 d1 = ld_at<float4>(tb.dxinvf, 4u * (uint32_t)wr(cb + 2));
+            const float2 d2 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb + 6));
+            dxi[0] = d0.x; dxi[1] = d0.y;
+            dxi[2] = d1.x; dxi[3] = d1.y; dxi[4] = d1.z; dxi[5] = d1.w;
+            dxi[6] = d2.x; dxi[7] = d2.y;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int cg = wrap1f(i0 + min(c4, nd - 1) - 2 + c, n);
+                rr[c] = tb.rrf[cg];
+                dxi[c] = tb.dxinvf[cg];
+            }
         }
-        const float2 d0 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb));
-        const float4 d1 = ld_at<float4>(tb.dxinvf, 4u * (uint32_t)wr(cb + 2));
-        const float2 d2 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb + 6));
-        dxi[0] = d0.x; dxi[1] = d0.y;
-        dxi[2] = d1.x; dxi[3] = d1.y; dxi[4] = d1.z; dxi[5] = d1.w;
-        dxi[6] = d2.x; dxi[7] = d2.y;
     }
     wave_sync();                                     // the window is dead
     float *sm = (float *)su;                         // shifted masses, index ci
@@ -1072,19 +1138,18 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
         if constexpr (H == 0) {
             const float4 m4 = *(const float4 *)(sm + c4);
             float o[4] = {m4.x * di4.x, m4.y * di4.y, m4.z * di4.z, m4.w * di4.w};
-            store_cells<true>(qo, i0, nd, c4, o);
+            store_cells<VEC>(qo, i0, nd, c4, o);
         } else {
             const float4 m0 = *(const float4 *)(sm + c4), m1 = *(const float4 *)(sm + c4 + 4);
             const float mv[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
             float sv[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) sv[c] = mv[c] * dxi[c];
-            if (a.q_mid)
-                *(float4 *)((float *)a.q_mid + qoff + i0 + c4) = make_float4(sv[2], sv[3], sv[4], sv[5]);
+            if (a.q_mid) store_cells<VEC>((float *)a.q_mid + qoff, i0, nd, c4, sv + 2);
             float o[4];
             residual4(sv, dvv, (float)a.dt, [&](int c) { return rr[c]; },
                       [&](int kk) { return dxi[kk + 2]; }, o);
-            store_cells<true>(qo, i0, nd, c4, o);
+            store_cells<VEC>(qo, i0, nd, c4, o);
         }
     }
 }
@@ -1098,7 +1163,8 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
 // two kernels on two streams with an event pair around every eager step, 342.
 // Inside a captured step loop the two kernels are parallel branches of the
 // graph (fork / join events, ForkJoin): the latency-bound searching tiles then
-// run beside the HBM-bound uniform ones.
+// run beside the HBM-bound uniform ones.  Fewer than kTogether tiles take one
+// launch for both kinds (k_step_both).
 template <int P, int H, bool VEC>
 __global__ __launch_bounds__(kBlock, 8) void k_step_uni(StepArgs a)
 {
@@ -1106,8 +1172,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_step_uni(StepArgs a)
     const int wid = wave_id();
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= a.fast.totals[0]) return;
-    const FastTile r = load_rec(a.fast.urec, i);
-    uniform_tile<P, H, VEC>(a, r, swin[wid], (int)threadIdx.x % kLanes);
+    uniform_tile<P, H, VEC>(a, load_rec(a.fast.urec, i), swin[wid], (int)threadIdx.x % kLanes);
 }
 
 // A uniform-run tile of the limited step (Section 3.1's PLM / PPM, App. A),
@@ -1205,12 +1270,7 @@ __device__ __forceinline__ void uniform_tile_lim(const StepArgs &a, const FastTi
     if constexpr (H == 0) {
         store_cells<VEC>(qo, p.i0, p.nd, c4, s);
     } else {
-        if (a.q_mid && c4 < p.nd) {
-            float *qm = (float *)a.q_mid + qoff;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (c4 + k < p.nd) qm[p.i0 + c4 + k] = s[k + 2];
-        }
+        if (a.q_mid) store_cells<VEC>((float *)a.q_mid + qoff, p.i0, p.nd, c4, s + 2);
         const float2 g = make_float2(r.dx, r.hinv);
         const float dxi = r.dxinv;
         float o[4];
@@ -1232,30 +1292,65 @@ __global__ __launch_bounds__(kBlock) void k_step_uni_lim(StepArgs a)
 
 // The other tiles.
 
+// LDS of the workgroups that run them.
+template <int S> struct GenLds {
+    __attribute__((aligned(16))) unsigned char su[kWaves][wave_lds_bytes<S>()];
+    __attribute__((aligned(16))) float sell[kWaves][WaveLds::nodes];
+    __attribute__((aligned(16))) short sjc[kWaves][WaveLds::nodes];
+};
+// Wave `wave` of `waves`.
 template <int P, int H, bool VEC, int S>
-__global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
+__device__ __forceinline__ void other_tiles(const StepArgs &a, GenLds<S> &lds, int wave, int waves)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char su[kWaves][wave_lds_bytes<S>()];
-    __shared__ __attribute__((aligned(16))) float sell_[kWaves][WaveLds::nodes];
-    __shared__ __attribute__((aligned(16))) short sjc_[kWaves][WaveLds::nodes];
     const int wid = wave_id();
     const int n = (int)a.rows.n_cols;
     const int t = (int)threadIdx.x % kLanes;
     const int total = a.fast.totals[1];
-    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+    for (int i = wave; i < total; i += waves) {
         const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
-        if (VEC && r.kind == kFastWindow && r.base + r.w + 3 < 2 * n)
-            window_tile<P, H, S>(a, r, su[wid], sell_[wid], sjc_[wid], t);
+        if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n && (VEC || n >= 8))
+            window_tile<P, H, S, VEC>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
         else
-            general_tile<P, H, VEC>(a, r, su[wid], sell_[wid], sjc_[wid], t);
+            general_tile<P, H, VEC>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
         wave_sync();                                 // the next tile reuses the LDS
     }
 }
 
 template <int P, int H, bool VEC, int S>
+__global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
+{
+    __shared__ GenLds<S> lds;
+    other_tiles<P, H, VEC, S>(a, lds, (int)blockIdx.x * kWaves + wave_id(), (int)gridDim.x * kWaves);
+}
+
+// Both kinds in one launch: the first `others` workgroups the other tiles, the
+// rest the uniform ones.
+template <int P, int H, bool VEC, int S>
+__global__ __launch_bounds__(kBlock) void k_step_both(StepArgs a, int others)
+{
+    __shared__ GenLds<S> lds;
+    const int wid = wave_id();
+    if ((int)blockIdx.x < others) {
+        other_tiles<P, H, VEC, S>(a, lds, (int)blockIdx.x * kWaves + wid, others * kWaves);
+        return;
+    }
+    const int i = ((int)blockIdx.x - others) * kWaves + wid;
+    if (i >= a.fast.totals[0]) return;
+    static_assert(sizeof(lds.su[0]) >= sizeof(float) * kUniWin, "a uniform tile's window");
+    uniform_tile<P, H, VEC>(a, load_rec(a.fast.urec, i), (float *)lds.su[wid],
+                            (int)threadIdx.x % kLanes);
+}
+
+template <int P, int H, bool VEC, int S>
 hipError_t step_fast_kernels(const StepArgs &a, hipStream_t st)
 {
-    const dim3 g(uniform_grid(a.rows.n_tiles)), b(kBlock), gg(other_grid(a.rows.n_tiles));
+    const int64_t nt = a.rows.n_tiles;
+    const dim3 g(uniform_grid(nt)), b(kBlock), gg(other_grid(nt));
+    if (nt < kTogether) {
+        const unsigned others = uniform_grid(nt);    // a wave a tile: it may be any of them
+        hipLaunchKernelGGL((k_step_both<P, H, VEC, S>), dim3(others + g.x), b, 0, st, a, (int)others);
+        return hipGetLastError();
+    }
     if (const ForkJoin *fj = capture_fork) {
         // the two kinds of tile write disjoint cells and read only q_in: the
         // searching tiles' kernel on the side stream, between a fork after
@@ -1278,8 +1373,12 @@ hipError_t step_fast_kernels(const StepArgs &a, hipStream_t st)
 template <int P, int S>
 hipError_t step_fast_ps(const StepArgs &a, bool vec, hipStream_t st)
 {
-    if (a.dv) return vec ? step_fast_kernels<P, 2, true, S>(a, st) : step_fast_kernels<P, 2, false, S>(a, st);
-    return vec ? step_fast_kernels<P, 0, true, S>(a, st) : step_fast_kernels<P, 0, false, S>(a, st);
+    if constexpr (S == kSumDirect) {
+        if (!vec)
+            return a.dv ? step_fast_kernels<P, 2, false, S>(a, st)
+                        : step_fast_kernels<P, 0, false, S>(a, st);
+    }
+    return a.dv ? step_fast_kernels<P, 2, true, S>(a, st) : step_fast_kernels<P, 0, true, S>(a, st);
 }
 
 template <int P>
@@ -1289,7 +1388,8 @@ hipError_t step_fast_p(const StepArgs &a, int scan, hipStream_t st)
                      ((uintptr_t)a.q_in % 16) == 0 &&
                      (!a.q_mid || ((uintptr_t)a.q_mid % 16) == 0) &&
                      (!a.dv || ((uintptr_t)a.dv % 16) == 0);
-    switch (scan) {
+    // rows not a multiple of four cells sum directly in every mode
+    switch (vec ? scan : (int)kSumDirect) {
     case kScanF64: return step_fast_ps<P, kScanF64>(a, vec, st);
     case kScanTwoSum: return step_fast_ps<P, kScanTwoSum>(a, vec, st);
     case kScanF32: return step_fast_ps<P, kScanF32>(a, vec, st);
@@ -1300,28 +1400,60 @@ hipError_t step_fast_p(const StepArgs &a, int scan, hipStream_t st)
 // The limited step's other tiles: general_tile with the limited partials, the
 // window tabulated in LDS where it fits, else every node located by the bucket
 // index and its partial integral the limited profile of its cell.
+struct GenLimLds {
+    static constexpr size_t U = kGenLimLds > WaveLds::u ? kGenLimLds : WaveLds::u;
+    __attribute__((aligned(16))) unsigned char su[kWaves][U];
+    __attribute__((aligned(16))) float sell[kWaves][WaveLds::nodes];
+    __attribute__((aligned(16))) short sjc[kWaves][WaveLds::nodes];
+};
 template <int R, int H, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_step_gen_lim(StepArgs a)
+__device__ __forceinline__ void other_tiles_lim(const StepArgs &a, GenLimLds &lds, int wave, int waves)
 {
     constexpr int P = 2 * LimHalo<R>::lo + 1;
-    constexpr size_t U = kGenLimLds > WaveLds::u ? kGenLimLds : WaveLds::u;
-    __shared__ __attribute__((aligned(16))) unsigned char su[kWaves][U];
-    __shared__ __attribute__((aligned(16))) float sell_[kWaves][WaveLds::nodes];
-    __shared__ __attribute__((aligned(16))) short sjc_[kWaves][WaveLds::nodes];
     const int wid = wave_id();
     const int t = (int)threadIdx.x % kLanes;
     const int total = a.fast.totals[1];
-    for (int i = (int)blockIdx.x * kWaves + wid; i < total; i += (int)gridDim.x * kWaves) {
+    for (int i = wave; i < total; i += waves) {
         const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
-        general_tile<P, H, VEC, R>(a, r, su[wid], sell_[wid], sjc_[wid], t);
+        general_tile<P, H, VEC, R>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
         wave_sync();                                 // the next tile reuses the LDS
     }
 }
 
 template <int R, int H, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_step_gen_lim(StepArgs a)
+{
+    __shared__ GenLimLds lds;
+    other_tiles_lim<R, H, VEC>(a, lds, (int)blockIdx.x * kWaves + wave_id(), (int)gridDim.x * kWaves);
+}
+
+// Both kinds in one launch, as k_step_both.
+template <int R, int H, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_step_both_lim(StepArgs a, int others)
+{
+    __shared__ GenLimLds lds;
+    const int wid = wave_id();
+    if ((int)blockIdx.x < others) {
+        other_tiles_lim<R, H, VEC>(a, lds, (int)blockIdx.x * kWaves + wid, others * kWaves);
+        return;
+    }
+    const int i = ((int)blockIdx.x - others) * kWaves + wid;
+    if (i >= a.fast.totals[0]) return;
+    static_assert(sizeof(lds.su[0]) >= sizeof(float) * kUniWin, "a uniform tile's window");
+    uniform_tile_lim<R, H, VEC>(a, load_rec(a.fast.urec, i), (float *)lds.su[wid],
+                                (int)threadIdx.x % kLanes);
+}
+
+template <int R, int H, bool VEC>
 hipError_t step_fast_lim_kernels(const StepArgs &a, hipStream_t st)
 {
-    const dim3 g(uniform_grid(a.rows.n_tiles)), b(kBlock), gg(other_grid(a.rows.n_tiles));
+    const int64_t nt = a.rows.n_tiles;
+    const dim3 g(uniform_grid(nt)), b(kBlock), gg(other_grid(nt));
+    if (nt < kTogether) {
+        const unsigned others = uniform_grid(nt);
+        hipLaunchKernelGGL((k_step_both_lim<R, H, VEC>), dim3(others + g.x), b, 0, st, a, (int)others);
+        return hipGetLastError();
+    }
     if (const ForkJoin *fj = capture_fork) {
         // parallel graph branches, as in step_fast_kernels
         hipError_t e = hipEventRecord(fj->fork, st);
