@@ -19,7 +19,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(HERE, "libram.so")
 ARCH = os.environ.get("RAM_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["ram_kernels.hip", "ram_step_shared.hip", "ram_step_fast.hip", "ram_step_fast64.hip", "ram_adjoint.hip",
+SOURCES = ["ram_kernels.hip", "ram_step_rows.hip", "ram_step_shared.hip", "ram_step_fast.hip", "ram_step_fast64.hip", "ram_adjoint.hip",
            "ram_adjoint_shared.hip", "ram_adjoint_fast.hip", "ram_limited.hip", "ram_reduce.hip", "ram_radial.hip",
            "ram_average4.hip", "ram_noalloc.hip", "ram_api.cpp"]
 
@@ -36,7 +36,7 @@ HIPCC_FLAGS = [
 # sources of the shared-mesh step kernel (the one the traffic counters cover)
 STEP_KERNEL_SOURCES = ["ram_step_shared.hip", "ram_device.h", "ram_internal.h"]
 # sources of each kernel family whose counters are committed
-FAST_SOURCES = ["ram_step_fast.hip", "ram_wave.h", "ram_device.h", "ram_internal.h"]
+FAST_SOURCES = ["ram_step_fast.hip", "ram_rows.h", "ram_wave.h", "ram_device.h", "ram_internal.h"]
 ADJ_FAST_SOURCES = ["ram_adjoint_fast.hip", "ram_adjoint_dev.h", "ram_wave.h", "ram_device.h",
                     "ram_internal.h"]
 KERNEL_SOURCES = {"k_step_sh": STEP_KERNEL_SOURCES,

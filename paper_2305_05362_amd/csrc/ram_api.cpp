@@ -338,6 +338,7 @@ bool use_fast_adjoint(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype,
 int step_tile_of(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype, ram_scan scan,
                  int items, bool fused)
 {
+    if (!L->edges_shared) return ram::rows_tile(fused);
     return use_fast(ctx, L, dtype, scan) ? ram::kFastTile : ram::step_tile_for(items, fused);
 }
 
@@ -828,6 +829,12 @@ ram_status ram_shift_noalloc(ram_ctx *ctx, const ram_layout *layout, ram_dtype d
                     "ram_shift_noalloc needs %zu bytes of device scratch for this layout; "
                     "its static buffer holds %zu",
                     cv.off, ram::kNoAllocBytes);
+    if (!layout->edges_shared) {
+        // per-row meshes run k_rows, four wave tiles a table tile: its table
+        // is smaller than what was reserved above, which stays the limit
+        Carve own;
+        rp = plan_rows(own, layout, 4 * ram::rows_tile(false), order);
+    }
     ram::StepArgs a;
     if ((st = make_rows(ctx, layout, edges, rp, a.rows, mem)) != RAM_OK) return st;
     a.q_in = q_in;
@@ -1337,7 +1344,8 @@ ram_status setup_row_step(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtyp
     const bool fast = recon == 0 ? use_fast(ctx, layout, dtype, scan)
                                  : use_fast_lim(ctx, layout, dtype);
     RowsPlan rp = plan_rows(cv, layout,
-                            fast ? ram::kFastTile : ram::step_tile_for(rs.items, dv != nullptr),
+                            recon ? (fast ? ram::kFastTile : ram::step_tile(dv != nullptr))
+                                  : step_tile_of(ctx, layout, dtype, scan, rs.items, dv != nullptr),
                             plan_order);
     rp.uniform = (dtype == RAM_F32 && (recon != 0 || scan == RAM_SUM_DIRECT)) || fast;
     const int64_t nt = tiles_of(layout, rp.tile);
@@ -1648,7 +1656,7 @@ ram_status ram_step_record(ram_ctx *ctx, const ram_layout *layout,
     const int items = sched_items(ctx, layout, scan);
     const bool fast = use_fast(ctx, layout, dtype, scan);
     RowsPlan rp = plan_rows(cv, layout,
-                            fast ? ram::kFastTile : ram::step_tile_for(items, dv != nullptr),
+                            step_tile_of(ctx, layout, dtype, scan, items, dv != nullptr),
                             order);
     rp.uniform = wants_uniform(dtype, scan) || use_fast(ctx, layout, dtype, scan);
     const int64_t nt = tiles_of(layout, rp.tile);

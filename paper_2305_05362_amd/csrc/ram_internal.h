@@ -224,7 +224,7 @@ inline size_t fast_plan_bytes(int64_t n_tiles)
 // each shifted node's source cell and Lagrange weights are too: planned once
 // per call into a record per tile, per node slot (kFastNodes a tile; the
 // slots past the tile's last node repeat it) the weights other than the own
-// node's (four in wa, the fifth in wb) and the source cell's index in the
+// node's (p of them, 4 p bytes a slot) and the source cell's index in the
 // tile's window, and the row cells' FP32 sizes.
 struct RagTile {
     int32_t kind;        // kFastWindow, or kFastDirect (window beyond the LDS)
@@ -239,10 +239,13 @@ static_assert(sizeof(RagTile) == 64, "one record a cache line half");
 // Cells of a per-row streaming tile: 255, so that its 256 shifted nodes fill
 // four slots of a wave (no residual halo on this path).
 constexpr int kRagTile = 255;
+// Cells per tile of the other per-row step kernel (k_rows): a wave's 256
+// shifted nodes, less the residual's two-cell halo a side.
+inline int rows_tile(bool fused) { return 255 - (fused ? 4 : 0); }
 struct RagPlan {
     RagTile *rec = nullptr;
-    float4 *wa = nullptr;
-    float *wb = nullptr;
+    float *wa = nullptr;       // order 5: four weights a slot, 3: two, 1: one
+    float *wb = nullptr;       // the last one of orders 5 and 3
     int16_t *jc = nullptr;
     float *dx = nullptr;       // FP32 sizes of the row cells, [n_cells]
 };
@@ -261,7 +264,7 @@ inline RagPlan rag_plan_at(void *mem, int64_t n_tiles)
     RagPlan r;
     r.rec = (RagTile *)p;
     p += al(sizeof(RagTile) * (size_t)n_tiles);
-    r.wa = (float4 *)p;
+    r.wa = (float *)p;
     p += al(sizeof(float4) * nn);
     r.wb = (float *)p;
     p += al(sizeof(float) * nn);
@@ -386,6 +389,8 @@ size_t mesh_tab_bytes(int64_t n, int order);
 // uniform-run counts if `uniform`: one launch.
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
                             MeshTab &tab, hipStream_t stream, bool uniform = false);
+// The step on per-row meshes (ram_step_rows.hip): tiles of rows_tile cells, or
+// of a multiple of it.
 hipError_t launch_step(const StepArgs &a, bool f64, int scan, int order,
                        hipStream_t stream);
 // Shared-mesh specialisation: plan the tiles' source windows once per call

@@ -1,30 +1,7 @@
-// ram_kernels.hip -- forward HIP kernels of the RAM advection step (gfx950).
+// ram_kernels.hip -- the residual step alone and the tables of a mesh (gfx950).
 //
-// Rows are independent periodic lines (paper Section 2).  Every kernel works
-// on tiles of consecutive cells of one row, one workgroup (kBlock threads =
-// four wave64) per tile, with row-major coalesced HBM access.
+// Rows are independent periodic lines (paper Section 2).
 //
-//   k_step       bulk shift (Section 3, Steps 1-3) on rows of their own
-//                meshes, optionally fused with the residual upwind step (Eq.
-//                splitting_second).  Per tile:
-//                (A) x~ = x - v0 dt is wrapped into the period and its source
-//                    cell found (Eq. condition_p) by binary search; the
-//                    Lagrange weights of the node's degree-p stencil stay in
-//                    registers;
-//                (B) the tile's source window is staged in LDS as cell masses
-//                    M = Q dx (Eq. Qmass_i) and turned into an exclusive prefix
-//                    (the cumulative integral) by a block scan in FP64,
-//                    compensated FP32 or plain FP32;
-//                (C) each node's partial integral of the reconstruction is the
-//                    Lagrange interpolant of the window cumulative;
-//                (D) destination mass = whole source cells in between + two
-//                    partial integrals (Eq. mass_shift_algo), times 1/dx
-//                    (Eq. step3);
-//                (E-G) fused residual: van Leer slopes (Section 3.1), upwind
-//                    swept-interval face fluxes and the conservative update,
-//                    on the shifted state still in LDS (two-cell halo a side).
-//                Windows wider than the LDS capacity take a direct path that
-//                sums the masses from global memory.
 //   k_residual   the residual step alone.
 //   k_mesh_prep  mesh-only tables of a shared mesh.
 //   k_tiles_prep tile table of a ragged batch.
@@ -39,330 +16,6 @@ namespace {
 
 using namespace dev;
 
-
-// Lagrange weights of the stencil nodes c-LO .. c-LO+P at xh, in WT.
-template <typename WT, int P>
-__device__ inline void stencil_weights(const double *x, int n, double len, int c, double xh,
-                                       WT *w)
-{
-    constexpr int LO = (P - 1) / 2;
-    double X[P + 1], wd[P + 1];
-#pragma unroll
-    for (int a = 0; a <= P; ++a) X[a] = node_x(x, n, len, c - LO + a);
-    lagrange_weights<P>(xh, X, wd);
-#pragma unroll
-    for (int a = 0; a <= P; ++a) w[a] = (WT)wd[a];
-}
-
-
-// ---------------------------------------------------------------------------
-// bulk shift, optionally fused with the residual step
-// ---------------------------------------------------------------------------
-
-constexpr int kWinStep = 1536;      // LDS window capacity of k_step, cells
-
-// LDS of k_step.  The window (masses + prefix) is dead once the destination
-// masses are formed, so the shifted state, slopes and fluxes of the fused
-// residual reuse its bytes; the node indices of the exact-window path use
-// them before the window is loaded.
-template <typename M, typename A, typename D, typename CT>
-struct StepLds {
-    static constexpr size_t win = sizeof(M) * kWinStep + sizeof(A) * (kWinStep + 1);
-    static constexpr size_t res = 3 * sizeof(CT) * kStepNodes;
-    static constexpr size_t nodes = sizeof(int64_t) * kStepNodes;
-    // per-row meshes, before the window is loaded: the window's node
-    // coordinates (FP64) and their periods relative to the first
-    static constexpr size_t stage = (sizeof(double) + sizeof(short)) * (kWinStep + 1);
-    static constexpr size_t uni0 = win > res ? win : res;
-    static constexpr size_t uni1 = uni0 > nodes ? uni0 : nodes;
-    static constexpr size_t uni = uni1 > stage ? uni1 : stage;
-};
-
-template <typename TQ, int P, int S>
-__global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
-{
-    using AC = Acc<S>;
-    using M = typename AC::M;
-    using A = typename AC::A;
-    using D = typename std::conditional<std::is_same<TQ, double>::value, double,
-                                        typename AC::D>::type;
-    using CT = TQ;                     // arithmetic type of the state updates
-    using L = StepLds<M, A, D, CT>;
-    constexpr int LO = (P - 1) / 2;
-    constexpr int NI = kItems;
-
-    __shared__ int sjc[kStepNodes];    // window index of each node's cell
-    __shared__ D sell[kStepNodes];     // partial integral C~(xh) - C(c)
-    __shared__ A swt[kBlock / 64];
-    __shared__ __attribute__((aligned(16))) unsigned char su[L::uni];
-    __shared__ int s_flag;             // 1: window path usable
-    __shared__ long long s_wlo, s_whi;
-    M *sm = (M *)su;                                     // window masses
-    A *sp = (A *)(su + sizeof(M) * kWinStep);            // exclusive prefix
-    int64_t *sg = (int64_t *)su;                         // node indices
-    CT *sq = (CT *)su;                                   // shifted state
-    CT *ssig = sq + kStepNodes;                          // van Leer slopes
-    CT *sf = ssig + kStepNodes;                          // face fluxes
-
-    const Rows &R = a.rows;
-    Tile ti;
-    if (!get_tile(R, blockIdx.x, ti)) return;
-    const int n = ti.n;
-    if (n < P + 1) return;
-    const int H = a.dv ? 2 : 0;                 // residual halo
-    const int i0 = ti.i0;
-    const int nd = min(R.tile, n - i0);         // cells this tile writes
-    const int NC = nd + 2 * H;                  // shifted cells
-    const int NE = NC + 1;                      // shifted nodes (<= kStepNodes)
-    const double *x = ti.x;
-    const TQ *q = (const TQ *)a.q_in + ti.qoff;
-    TQ *qo = (TQ *)a.q_out + ti.qoff;
-    TQ *qmid = a.q_mid ? (TQ *)a.q_mid + ti.qoff : nullptr;
-    const double s = a.v0[ti.row] * a.dt;
-    const double len = x[n] - x[0];
-    const int t = threadIdx.x;
-    const double invlen = 1.0 / len;
-
-    // residual velocity of the faces this thread will need, fetched early
-    const TQ *dv = H ? (const TQ *)a.dv + ti.qoff : nullptr;
-    TQ dvr[NI];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int f = t + k * kBlock;
-        dvr[k] = (H && f < nd + 1) ? dv[wrap_small(i0 + f, n)] : (TQ)0;
-    }
-
-    if (t == 0) s_flag = 1;
-
-    // Per-row meshes: the tile's window from its two end nodes (global
-    // searches by two threads), then the window's node coordinates staged in
-    // LDS, where every node finds its cell and its stencil nodes.
-    double *sxs = (double *)su;                          // window nodes (FP64)
-    short *skq = (short *)(su + sizeof(double) * (kWinStep + 1));   // periods
-    if (t < 2) {
-        int e = t == 0 ? i0 - H : i0 - H + NE - 1;
-        int kx = 0;
-        if (e < 0) { e += n; kx = -1; }
-        while (e >= n) { e -= n; kx += 1; }
-        double xh;
-        int64_t k;
-        shifted_node_inv(x, n, s, e, invlen, len, xh, k);
-        const int64_t gg = (int64_t)find_cell(x, n, xh) + (k + kx) * (int64_t)n;
-        if (t == 0) s_wlo = gg - LO;
-        else s_whi = gg - LO + P;
-    }
-    __syncthreads();
-    const int64_t pwlo = s_wlo;
-    const int64_t pk0 = pwlo >= 0 ? pwlo / n : -((-pwlo + n - 1) / n);   // period of wlo
-    const bool stage = s_whi - pwlo >= P && s_whi - pwlo <= kWinStep;
-    const int pW = stage ? (int)(s_whi - pwlo) : 0;
-    if (stage) {
-        const int pbase = (int)(pwlo - pk0 * n);
-        for (int j = t; j <= pW; j += kBlock) {
-            int m = pbase + j, kq = 0;
-            while (m >= n) { m -= n; ++kq; }
-            sxs[j] = x[m];
-            skq[j] = (short)kq;
-        }
-        __syncthreads();
-    }
-
-    // (A) shifted nodes e = i0 - H + t + k kBlock: cell and stencil weights
-    int64_t g[NI];
-    TQ w[NI][P + 1];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int ei = t + k * kBlock;
-        g[k] = 0;
-        if (ei < NE) {
-            int e = i0 - H + ei;
-            int kx = 0;
-            if (e < 0) { e += n; kx = -1; }
-            while (e >= n) { e -= n; kx += 1; }
-            double xh;
-            int64_t kk;
-            shifted_node_inv(x, n, s, e, invlen, len, xh, kk);
-            bool done = false;
-            if (stage) {
-                // the last window cell whose left node is at or below the
-                // shifted node, comparing (period, coordinate) pairs exactly
-                const int dk = (int)(kk + kx - pk0);
-                auto le = [&](int j) {
-                    const int kj = skq[j];
-                    return kj < dk || (kj == dk && sxs[j] <= xh);
-                };
-                int lo = 0, hi = pW + 1;
-                if (le(0)) {
-                    while (hi - lo > 1) {
-                        const int mid = (lo + hi) >> 1;
-                        if (le(mid)) lo = mid;
-                        else hi = mid;
-                    }
-                    if (lo - LO >= 0 && lo - LO + P <= pW) {
-                        g[k] = pwlo + lo;
-                        const double xc = sxs[lo];
-                        const int kc = skq[lo];
-                        double X[P + 1];
-#pragma unroll
-                        for (int b = 0; b <= P; ++b) {
-                            const int jb = lo - LO + b;
-                            X[b] = (sxs[jb] - xc) + (double)(skq[jb] - kc) * len;
-                        }
-                        lagrange_rel<TQ, P>(xh - xc, X, w[k]);
-                        done = true;
-                    }
-                }
-            }
-            if (!done) {
-                const int c = find_cell(x, n, xh);
-                g[k] = (int64_t)c + (kk + kx) * (int64_t)n;
-                stencil_weights<TQ, P>(x, n, len, c, xh, w[k]);
-            }
-        }
-    }
-    __syncthreads();
-    const int64_t wlo = s_wlo;
-    const int64_t wide = s_whi - s_wlo;
-    // every node's stencil must lie inside the window (else: direct path)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        if (t + k * kBlock < NE) {
-            const int64_t jc = g[k] - wlo;
-            if (jc < LO || jc + P - LO > wide) s_flag = 0;
-        }
-    }
-    if (wide > kWinStep || wide < P) s_flag = 0;
-    __syncthreads();
-    const bool windowed = s_flag != 0;
-
-    if (windowed) {
-        const int W = (int)wide;
-        const int base = wrapi(wlo, n);
-        // (B) window masses and the block scan into the cumulative
-        for (int j = t; j < W; j += kBlock) {
-            const int mm = wrap_small(base + j, n);
-            sm[j] = AC::template mass<TQ>(q[mm], x[mm + 1] - x[mm]);
-        }
-        __syncthreads();
-        const int per = (W + kBlock - 1) / kBlock;
-        const int j0 = min(W, t * per);
-        const int j1 = min(W, j0 + per);
-        A run = AC::zero();
-        for (int j = j0; j < j1; ++j) run = AC::add(run, sm[j]);
-        A total;
-        A acc = block_exscan_dpp<AC>(run, swt, total);
-        for (int j = j0; j < j1; ++j) {
-            sp[j] = acc;
-            acc = AC::add(acc, sm[j]);
-        }
-        if (t == 0) sp[W] = total;
-        __syncthreads();
-        // (C) partial integrals from the interpolated window cumulative
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-            const int ei = t + k * kBlock;
-            if (ei < NE) {
-                const int jc = (int)(g[k] - wlo);
-                const A pc = sp[jc];
-                D ell = (D)0;
-#pragma unroll
-                for (int b = 0; b <= P; ++b)
-                    if (b != LO) ell += (D)w[k][b] * (D)AC::diff(sp[jc - LO + b], pc);
-                sell[ei] = ell;
-                sjc[ei] = jc;
-            }
-        }
-    } else {
-        // direct path: masses summed from global memory in FP64
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-            const int ei = t + k * kBlock;
-            if (ei < NE) {
-                sg[ei] = g[k];
-                sell[ei] = (D)direct_partial<TQ, P>(x, q, n, len, s, invlen,
-                                                    i0 - H + ei, g[k]);
-            }
-        }
-    }
-    __syncthreads();
-
-    // (D) destination masses and Step 3
-    CT qs[NI];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int ci = t + k * kBlock;
-        qs[k] = (CT)0;
-        if (ci < NC) {
-            const int cell = wrap_small(i0 - H + ci, n);
-            D mp;
-            if (windowed) {
-                const int ja = sjc[ci], jb = sjc[ci + 1];
-                const D whole = (jb - ja == 1) ? (D)sm[ja] : (D)AC::diff(sp[jb], sp[ja]);
-                mp = whole + (sell[ci + 1] - sell[ci]);
-            } else {
-                const double wh = direct_whole<TQ>(x, q, n, sg[ci], sg[ci + 1]);
-                mp = (D)(wh + ((double)sell[ci + 1] - (double)sell[ci]));
-            }
-            qs[k] = (CT)(mp / (D)(x[cell + 1] - x[cell]));
-            if (H == 0) qo[cell] = (TQ)qs[k];
-            else if (qmid && ci >= H && ci < H + nd) qmid[cell] = (TQ)qs[k];
-        }
-    }
-    if (H == 0) return;
-    __syncthreads();   // the window bytes become the residual's arrays
-#pragma unroll
-    for (int k = 0; k < NI; ++k)
-        if (t + k * kBlock < NC) sq[t + k * kBlock] = qs[k];
-    __syncthreads();
-
-    // (E) van Leer slopes of cells i0-1 .. i0+nd (state index +1)
-    const CT dt = (CT)a.dt;
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int u = t + k * kBlock;
-        if (u < nd + 2) {
-            const int cm = wrap_small(i0 - 2 + u, n);
-            const int c0 = wrap_small(i0 - 1 + u, n);
-            const CT hp = (CT)(1.0 / centre_gap(x, n, len, c0));
-            const CT hm = (CT)(1.0 / centre_gap(x, n, len, cm));
-            const CT dp = (sq[u + 2] - sq[u + 1]) * hp;
-            const CT dm = (sq[u + 1] - sq[u]) * hm;
-            ssig[u] = (dp * dm <= (CT)0) ? (CT)0 : harmonic2(dp, dm);
-        }
-    }
-    __syncthreads();
-    // (F) fluxes on faces i0 .. i0+nd (face f between cells f-1 and f)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int u = t + k * kBlock;
-        if (u < nd + 1) {
-            const int f = wrap_small(i0 + u, n);
-            const CT v = (CT)dvr[k];
-            CT qf;
-            if (v >= (CT)0) {
-                const int c = wrap_small(i0 + u - 1, n);
-                const CT dxu = (CT)(x[c + 1] - x[c]);
-                qf = sq[u + 1] + (CT)0.5 * ssig[u] * (dxu - v * dt);
-            } else {
-                const CT dxu = (CT)(x[f + 1] - x[f]);
-                qf = sq[u + 2] - (CT)0.5 * ssig[u + 1] * (dxu + v * dt);
-            }
-            sf[u] = v * qf;
-        }
-    }
-    __syncthreads();
-    // (G) conservative update of the tile's own cells
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int u = t + k * kBlock;
-        if (u < nd) {
-            const int i = i0 + u;
-            const CT inv = (CT)(1.0 / (x[i + 1] - x[i]));
-            qo[i] = (TQ)(sq[u + 2] - dt * (sf[u + 1] - sf[u]) * inv);
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // residual step alone
@@ -835,56 +488,65 @@ __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTab
 // tile_row[t] = row of tile t.  One workgroup of 1024 threads.
 // ---------------------------------------------------------------------------
 
+// Every workgroup scans all the rows' tile counts (consecutive rows a thread;
+// the same first tiles written by each), then fills in its own share of the
+// tiles' rows, kFillRows rows a wave, a row at a time with consecutive tiles on
+// the lanes: the fill is instruction issue, too much for one CU.  4096 rows of
+// 17 tiles on average: 10 us; 48 as one workgroup, each thread writing its own
+// rows' tiles one after the other.
+constexpr int kFillRows = 8;
 __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
                                                      int64_t n_rows, int tile,
                                                      int64_t *tile_ptr,
                                                      int32_t *tile_row)
 {
-    __shared__ int64_t stot[1024];
+    __shared__ int64_t swt[16];
+    const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6;
     const int64_t per = (n_rows + 1023) / 1024;
-    const int64_t r0 = min(n_rows, (int64_t)threadIdx.x * per);
+    const int64_t r0 = min(n_rows, (int64_t)t * per);
     const int64_t r1 = min(n_rows, r0 + per);
-    int64_t run = 0;
-    for (int64_t r = r0; r < r1; ++r)
-        run += (row_ptr[r + 1] - row_ptr[r] + tile - 1) / tile;
-    stot[threadIdx.x] = run;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const int64_t o = threadIdx.x >= (unsigned)d ? stot[threadIdx.x - d] : 0;
-        __syncthreads();
-        stot[threadIdx.x] += o;
-        __syncthreads();
-    }
-    int64_t acc = stot[threadIdx.x] - run;
+    int64_t run = 0, p0 = r0 < r1 ? row_ptr[r0] : 0;
     for (int64_t r = r0; r < r1; ++r) {
+        const int64_t p1 = row_ptr[r + 1];
+        run += (p1 - p0 + tile - 1) / tile;
+        p0 = p1;
+    }
+    int64_t inc = run;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t o = __shfl_up(inc, d);
+        if (lane >= d) inc += o;
+    }
+    if (lane == 63) swt[wv] = inc;
+    __syncthreads();
+    int64_t acc = inc - run, total = 0;
+    for (int w = 0; w < 16; ++w) {
+        acc += w < wv ? swt[w] : 0;
+        total += swt[w];
+    }
+    p0 = r0 < r1 ? row_ptr[r0] : 0;
+    for (int64_t r = r0; r < r1; ++r) {
+        const int64_t p1 = row_ptr[r + 1];
         tile_ptr[r] = acc;
-        const int64_t nt = (row_ptr[r + 1] - row_ptr[r] + tile - 1) / tile;
-        for (int64_t k = 0; k < nt; ++k) tile_row[acc + k] = (int32_t)r;
-        acc += nt;
+        acc += (p1 - p0 + tile - 1) / tile;
+        p0 = p1;
     }
-    if (threadIdx.x == 1023) tile_ptr[n_rows] = stot[1023];
-}
-
-template <typename TQ, int P>
-hipError_t step_scan(const StepArgs &a, int scan, hipStream_t st)
-{
-    const dim3 g((unsigned)a.rows.n_tiles), b(kBlock);
-    switch (scan) {
-    case kScanF64:
-    case kSumDirect: hipLaunchKernelGGL((k_step<TQ, P, kScanF64>), g, b, 0, st, a); break;
-    case kScanTwoSum: hipLaunchKernelGGL((k_step<TQ, P, kScanTwoSum>), g, b, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_step<TQ, P, kScanF32>), g, b, 0, st, a); break;
-    }
-    return hipGetLastError();
-}
-
-template <typename TQ>
-hipError_t step_order(const StepArgs &a, int scan, int order, hipStream_t st)
-{
-    switch (order) {
-    case 1: return step_scan<TQ, 1>(a, scan, st);
-    case 3: return step_scan<TQ, 3>(a, scan, st);
-    default: return step_scan<TQ, 5>(a, scan, st);
+    if (t == 1023) tile_ptr[n_rows] = total;
+    __threadfence_block();
+    __syncthreads();
+    const int64_t wave = (int64_t)blockIdx.x * 16 + wv;
+    for (int64_t c = kFillRows * wave; c < n_rows; c += kFillRows * 16 * (int64_t)gridDim.x) {
+        // the rows' first tiles at once, then one row after the other
+        const int64_t r = c + min(lane, kFillRows - 1);
+        const int64_t base = tile_ptr[c];
+        const int first = (int)(tile_ptr[min(r, n_rows)] - base);
+        const int end = (int)(tile_ptr[min(r + 1, n_rows)] - base);
+        const int m = (int)min((int64_t)kFillRows, n_rows - c);
+        int32_t *to = tile_row + base;
+        for (int k = 0; k < m; ++k) {
+            const int a = __builtin_amdgcn_readlane(first, k), b = __builtin_amdgcn_readlane(end, k);
+            for (int i = a + lane; i < b; i += 64) to[i] = (int32_t)(c + k);
+        }
     }
 }
 
@@ -969,21 +631,11 @@ hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
                              int64_t *tile_ptr, int32_t *tile_row,
                              hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_tiles_prep, dim3(1), dim3(1024), 0, stream, row_ptr,
-                       n_rows, tile, tile_ptr, tile_row);
+    // (more than 64 workgroups only repeat the scan)
+    const unsigned g = (unsigned)std::min<int64_t>((n_rows + 16 * kFillRows - 1) / (16 * kFillRows), 64);
+    hipLaunchKernelGGL(k_tiles_prep, dim3(g), dim3(1024), 0, stream, row_ptr, n_rows, tile, tile_ptr,
+                       tile_row);
     return hipGetLastError();
-}
-
-hipError_t launch_step(const StepArgs &a, bool f64, int scan, int order,
-                       hipStream_t stream)
-{
-    if (a.rows.n_tiles <= 0) return hipSuccess;
-    if (a.rag.rec) {
-        if (f64) return hipErrorInvalidValue;
-        return launch_step_rag(a, order, scan, stream);
-    }
-    if (f64) return step_order<double>(a, kScanF64, order, stream);
-    return step_order<float>(a, scan, order, stream);
 }
 
 hipError_t launch_residual(const ResidualArgs &a, bool f64, hipStream_t stream)

@@ -30,8 +30,7 @@
 //     sums from global memory.
 // Tiles of 256 cells keep the searching tiles to the cells near the mesh's
 // non-uniform stretches.
-#include "ram_device.h"
-#include "ram_wave.h"
+#include "ram_rows.h"
 
 #include <type_traits>
 
@@ -822,42 +821,6 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 // and one word a load (general_tile), 80.
 // ---------------------------------------------------------------------------
 
-// The prefix modes (S other than kSumDirect): the window's exclusive
-// cumulative of the masses, in the mode's precision (Acc<S>), at LDS index
-// j + off for window cell j and one past the window's last group; partial
-// integrals and whole-cell sums are then its differences (only differences:
-// the cells below the window start in the first group cancel).  Masses of
-// groups g = l + 64 s (s = 0, 1, ...), four a lane: each group's lane totals
-// scanned across the wave, the groups before carried on.
-template <int S>
-__device__ __forceinline__ void wave_prefix(typename Acc<S>::A *sp, const typename Acc<S>::M (&m)[4],
-                                            int g, int gl, typename Acc<S>::A &carry)
-{
-    using AC = Acc<S>;
-    using A = typename AC::A;
-    const int lane = (int)threadIdx.x % kLanes;
-    const bool live = g <= gl;
-    A tot = AC::zero();
-    if (live) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) tot = AC::add(tot, m[k]);
-    }
-    // inclusive scan of the lane totals over the wave
-    const A inc = wave_inclusive<AC>(tot);
-    A ex = AC::template dpp<kDppWaveShr1, 0xf, 0xf>(inc);
-    if (lane == 0) ex = AC::zero();
-    A e = AC::comb(carry, ex);
-    if (live) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            sp[4 * g + k] = e;
-            e = AC::add(e, m[k]);
-        }
-        if (g == gl) sp[4 * g + 4] = e;
-    }
-    carry = AC::comb(carry, lane63(inc));
-}
-
 template <int P, int H, int S, bool VEC>
 __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &ft,
                                             unsigned char *su, float *sell, short *sjc, int t)
@@ -1511,14 +1474,21 @@ __device__ inline RagTile load_rag(const RagTile *rec, int64_t i)
     return r;
 }
 
+// The plan, one wave a tile: the window's nodes once into LDS, every node
+// located and weighted there (rows_locate, rows_weights).  VALU issue bounds it
+// (815 instructions a tile at order 3).  16.9 M cells, order 3: 172 us; 418
+// with a binary search of the row and the stencil's nodes from global
+// memory a node.
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_plan_rag(StepArgs a, RagPlan pl)
 {
-    constexpr int LO = (P - 1) / 2;
-    constexpr int NS = (kFastNodes + kLanes - 1) / kLanes;
+    constexpr int NS = (kRagTile + 1) / kLanes;
+    static_assert(NS * kLanes == kRagTile + 1, "whole node slots");
+    __shared__ double xs_[kWaves][kFastWin + 8];
     const Rows &R = a.rows;
     const int t = (int)threadIdx.x % kLanes;
-    const int64_t tile = (int64_t)blockIdx.x * kWaves + wave_id();
+    const int wid = wave_id();
+    const int64_t tile = (int64_t)blockIdx.x * kWaves + wid;
     if (tile >= R.n_tiles) return;
     RagTile rt;
     rt.kind = -1;
@@ -1534,66 +1504,65 @@ __global__ __launch_bounds__(kBlock) void k_plan_rag(StepArgs a, RagPlan pl)
     const int nd = min(R.tile, n - i0);
     const int NE = nd + 1;
     const double *x = ti.x;
-    const double len = x[n] - x[0];
+    const double x0 = x[0], xN = x[n];
+    const double len = xN - x0;
     const double invlen = 1.0 / len;
-    const double s = a.v0[ti.row] * a.dt;
-    for (int c = t; c < nd; c += kLanes)
-        pl.dx[ti.qoff + i0 + c] = (float)(x[i0 + c + 1] - x[i0 + c]);
-    // extended source index g = c + k n of row node e (node n: node 0 one
-    // period on) and the wrapped shifted position
-    auto locate = [&](int e, double &xh) -> int64_t {
-        int kx = 0;
-        if (e >= n) {
-            e -= n;
-            kx = 1;
-        }
-        int64_t k;
-        shifted_node_inv(x, n, s, e, invlen, len, xh, k);
-        return (int64_t)find_cell(x, n, xh) + (k + kx) * (int64_t)n;
-    };
-    double xh0, xh1;
-    const int64_t g0 = locate(i0, xh0);
-    const int64_t g1 = locate(i0 + nd, xh1);
-    const int64_t wlo = g0 - LO;
-    const int64_t wide = g1 - g0 + P;
-    bool ok = wide >= P && wide <= kFastWin;
-    const int64_t slot = tile * kFastNodes;
+    const double s = rows_shift(a.v0[ti.row], a.dt);
+    double xe[NS], xr[NS];
+    int kx[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        const int m = t + u * kLanes;
-        if (m < kFastNodes) {
-            double xh;
-            const int64_t g = locate(i0 + min(m, NE - 1), xh);
-            const int c = (int)(g - (g >= 0 ? g / n : -((-g + n - 1) / n)) * (int64_t)n);
-            double X[P + 1];
+        const int m = min(t + u * kLanes, NE - 1);
+        kx[u] = i0 + m >= n ? 1 : 0;
+        const int e = i0 + m - (kx[u] ? n : 0);
+        xe[u] = x[e];
+        xr[u] = x[e + 1];
+    }
 #pragma unroll
-            for (int b = 0; b <= P; ++b) X[b] = node_x(x, n, len, c - LO + b) - x[c];
-            float w[P + 1];
-            lagrange_rel<float, P>(xh - x[c], X, w);
-            float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < NS; ++u)
+        if (t + u * kLanes < nd) pl.dx[ti.qoff + i0 + t + u * kLanes] = (float)(xr[u] - xe[u]);
+    double *xs = xs_[wid];
+    RowsWindow win;
+    double xh[NS];
+    int j[NS];
+    const bool all = n >= P + 1 && rows_locate<P, NS>(x, n, s, x0, xN, len, invlen, NE, t, kFastWin, xe,
+                                                      kx, xs, win, xh, j);
+    const int64_t slot = tile * kFastNodes;
+    if (all) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            constexpr int LO = (P - 1) / 2;
+            const int m = t + u * kLanes;
+            float w[P + 1], v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+            if (win.seam > win.w) rows_weights<float, P, false>(xs, win, len, xh[u], j[u], w);
+            else rows_weights<float, P, true>(xs, win, len, xh[u], j[u], w);
             int k = 0;
 #pragma unroll
             for (int b = 0; b <= P; ++b)
                 if (b != LO) v[k++] = w[b];
-            pl.wa[slot + m] = make_float4(v[0], v[1], v[2], v[3]);
-            pl.wb[slot + m] = v[4];
-            const int64_t j = g - wlo;
-            ok = ok && j >= LO && j + P - LO <= wide;
-            pl.jc[slot + m] = (int16_t)min(max(j, (int64_t)0), (int64_t)kFastWin);
+            if constexpr (P == 5) {
+                ((float4 *)pl.wa)[slot + m] = make_float4(v[0], v[1], v[2], v[3]);
+                pl.wb[slot + m] = v[4];
+            } else if constexpr (P == 3) {
+                ((float2 *)pl.wa)[slot + m] = make_float2(v[0], v[1]);
+                pl.wb[slot + m] = v[2];
+            } else {
+                pl.wa[slot + m] = v[0];
+            }
+            pl.jc[slot + m] = (int16_t)j[u];
         }
     }
-    const bool all = __all(ok ? 1 : 0) != 0;
     if (t == 0) {
         rt.kind = all ? kFastWindow : kFastDirect;
         rt.row = (int32_t)ti.row;
         rt.i0 = i0;
         rt.nd = nd;
         rt.n = n;
-        rt.w = all ? (int32_t)wide : 0;
-        rt.base = (int32_t)(wlo - (wlo >= 0 ? wlo / n : -((-wlo + n - 1) / n)) * (int64_t)n);
+        rt.w = all ? win.w : 0;
+        rt.base = n >= P + 1 ? win.base : 0;
         rt.qoff = ti.qoff;
         rt.eoff = (int64_t)(x - R.edges);
-        rt.wlo = wlo;
+        rt.wlo = n >= P + 1 ? win.wlo : 0;
         pl.rec[tile] = rt;
     }
 }
@@ -1640,15 +1609,27 @@ __device__ __forceinline__ void rag_tile(const StepArgs &a, const RagTile &r, in
     A *sp = (A *)su;                                 // prefix modes: the cumulative
 
     // ---- plan of the nodes, sizes of the destination cells -------------------
-    float4 wa[NS];
-    float wb[NS];
+    float wv[NS][5];
     int jv[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        const int m = min(t + u * kLanes, kFastNodes - 1);
-        wa[u] = a.rag.wa[slot + m];
-        wb[u] = a.rag.wb[slot + m];
-        jv[u] = a.rag.jc[slot + m];
+        const int64_t m = slot + t + u * kLanes;
+        if constexpr (P == 5) {
+            const float4 w4 = ((const float4 *)a.rag.wa)[m];
+            wv[u][0] = w4.x;
+            wv[u][1] = w4.y;
+            wv[u][2] = w4.z;
+            wv[u][3] = w4.w;
+            wv[u][4] = a.rag.wb[m];
+        } else if constexpr (P == 3) {
+            const float2 w2 = ((const float2 *)a.rag.wa)[m];
+            wv[u][0] = w2.x;
+            wv[u][1] = w2.y;
+            wv[u][2] = a.rag.wb[m];
+        } else {
+            wv[u][0] = a.rag.wa[m];
+        }
+        jv[u] = a.rag.jc[m];
     }
     float dxd[NCS];
 #pragma unroll
@@ -1658,6 +1639,10 @@ __device__ __forceinline__ void rag_tile(const StepArgs &a, const RagTile &r, in
     // up to 320 cells in one batch); the FP64 prefix widens the FP32 masses
     const bool once = base + W <= 2 * n;             // the window wraps the row at most once
     A carry = AC::zero();
+    // the prefix modes: a window of one batch goes through LDS to NB consecutive
+    // masses a lane, whose sums one scan of the wave accumulates (two-sum on the
+    // 16.9 M cell batch at order 3: 90 us a step, 104 with a scan a slot)
+    const bool batch = !kDirect && W <= NB * kLanes;
     for (int s0 = 0; s0 * kLanes < W; s0 += NB) {
         float vq[NB], vd[NB];
 #pragma unroll
@@ -1672,24 +1657,45 @@ __device__ __forceinline__ void rag_tile(const StepArgs &a, const RagTile &r, in
         for (int u = 0; u < NB; ++u) {
             if ((s0 + u) * kLanes >= W) break;
             const int j = t + (s0 + u) * kLanes;
-            if constexpr (kDirect) {
+            if (kDirect || batch) {
                 if (j < W) sw[j] = vq[u] * vd[u];
-            } else {
+            } else if constexpr (!kDirect) {
                 const M m = (M)(vq[u] * vd[u]);
                 wave_prefix1<S == kSumDirect ? kScanF32 : S>(sp, m, j, W, carry);
             }
         }
     }
     wave_sync();
+    if constexpr (!kDirect) {
+        if (batch) {
+            M m[NB];
+            A tot = AC::zero();
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                m[k] = NB * t + k < W ? (M)sw[NB * t + k] : (M)0;
+                tot = AC::add(tot, m[k]);
+            }
+            wave_sync();                             // the cumulative takes the masses' place
+            const A inc = wave_inclusive<AC>(tot);
+            A e = AC::template dpp<kDppWaveShr1, 0xf, 0xf>(inc);
+            if (t == 0) e = AC::zero();
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                if (NB * t + k <= W) sp[NB * t + k] = e;
+                e = AC::add(e, m[k]);
+            }
+            if (t == kLanes - 1 && W == NB * kLanes) sp[W] = e;
+            wave_sync();
+        }
+    }
 
     // ---- partial integrals C~(x) - C(c) of the nodes ---------------------------
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        const float v[5] = {wa[u].x, wa[u].y, wa[u].z, wa[u].w, wb[u]};
         float wk[P + 1];
         int k = 0;
 #pragma unroll
-        for (int b = 0; b <= P; ++b) wk[b] = b == LO ? 0.0f : v[k++];
+        for (int b = 0; b <= P; ++b) wk[b] = b == LO ? 0.0f : wv[u][k++];
         const int j = jv[u];
         float e = 0.0f;
         if constexpr (kDirect) {

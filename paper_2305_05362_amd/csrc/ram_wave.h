@@ -135,6 +135,42 @@ __device__ __forceinline__ double lane63(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// The prefix modes (S other than kSumDirect): the window's exclusive
+// cumulative of the masses, in the mode's precision (Acc<S>), at LDS index
+// j + off for window cell j and one past the window's last group; partial
+// integrals and whole-cell sums are then its differences (only differences:
+// the cells below the window start in the first group cancel).  Masses of
+// groups g = l + 64 s (s = 0, 1, ...), four a lane: each group's lane totals
+// scanned across the wave, the groups before carried on.
+template <int S>
+__device__ __forceinline__ void wave_prefix(typename Acc<S>::A *sp, const typename Acc<S>::M (&m)[4],
+                                            int g, int gl, typename Acc<S>::A &carry)
+{
+    using AC = Acc<S>;
+    using A = typename AC::A;
+    const int lane = (int)threadIdx.x % kLanes;
+    const bool live = g <= gl;
+    A tot = AC::zero();
+    if (live) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tot = AC::add(tot, m[k]);
+    }
+    // inclusive scan of the lane totals over the wave
+    const A inc = wave_inclusive<AC>(tot);
+    A ex = AC::template dpp<kDppWaveShr1, 0xf, 0xf>(inc);
+    if (lane == 0) ex = AC::zero();
+    A e = AC::comb(carry, ex);
+    if (live) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sp[4 * g + k] = e;
+            e = AC::add(e, m[k]);
+        }
+        if (g == gl) sp[4 * g + 4] = e;
+    }
+    carry = AC::comb(carry, lane63(inc));
+}
+
 // Moves a small per-lane array down one slot (v[0] = v[1], ...), for loops
 // over slots that are not unrolled: they read slot 0 each trip, since an
 // array indexed at run time is placed in scratch memory, whose stores reach
@@ -145,6 +181,24 @@ __device__ __forceinline__ void slot_down(T (&v)[N])
 #pragma unroll
     for (int i = 0; i + 1 < N; ++i) v[i] = v[i + 1];
 }
+template <class T, int N, int M>
+__device__ __forceinline__ void slot_down(T (&v)[N][M])
+{
+#pragma unroll
+    for (int i = 0; i + 1 < N; ++i)
+#pragma unroll
+        for (int k = 0; k < M; ++k) v[i][k] = v[i + 1][k];
+}
 
+// The same, the first slot's value going to the last (after N turns every slot
+// is back in its place).
+template <class T, int N>
+__device__ __forceinline__ void slot_turn(T (&v)[N])
+{
+    const T first = v[0];
+#pragma unroll
+    for (int i = 0; i + 1 < N; ++i) v[i] = v[i + 1];
+    v[N - 1] = first;
+}
 } // namespace dev
 } // namespace ram
