@@ -20,7 +20,7 @@ LIB_PATH = os.path.join(HERE, "libram.so")
 ARCH = os.environ.get("RAM_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["ram_kernels.hip", "ram_step_rows.hip", "ram_step_shared.hip", "ram_step_fast.hip", "ram_step_fast64.hip", "ram_adjoint.hip",
-           "ram_adjoint_shared.hip", "ram_adjoint_fast.hip", "ram_limited.hip", "ram_reduce.hip", "ram_radial.hip",
+           "ram_adjoint_shared.hip", "ram_adjoint_fast.hip", "ram_adjoint_tile.hip", "ram_limited.hip", "ram_reduce.hip", "ram_radial.hip",
            "ram_average4.hip", "ram_noalloc.hip", "ram_api.cpp"]
 
 HIPCC_FLAGS = [
@@ -37,7 +37,7 @@ HIPCC_FLAGS = [
 STEP_KERNEL_SOURCES = ["ram_step_shared.hip", "ram_device.h", "ram_internal.h"]
 # sources of each kernel family whose counters are committed
 FAST_SOURCES = ["ram_step_fast.hip", "ram_rows.h", "ram_wave.h", "ram_device.h", "ram_internal.h"]
-ADJ_FAST_SOURCES = ["ram_adjoint_fast.hip", "ram_adjoint_dev.h", "ram_wave.h", "ram_device.h",
+ADJ_FAST_SOURCES = ["ram_adjoint_fast.hip", "ram_adjoint_wave.h", "ram_adjoint_dev.h", "ram_wave.h", "ram_device.h",
                     "ram_internal.h"]
 KERNEL_SOURCES = {"k_step_sh": STEP_KERNEL_SOURCES,
                   "k_step_uni": FAST_SOURCES,
@@ -45,7 +45,7 @@ KERNEL_SOURCES = {"k_step_sh": STEP_KERNEL_SOURCES,
                   "k_step_rag": FAST_SOURCES,
                   "k_step_uni_lim": FAST_SOURCES,
                   "k_step_gen_lim": FAST_SOURCES,
-                  "k_step64": ["ram_step_fast64.hip", "ram_kernels.hip", "ram_wave.h", "ram_device.h",
+                  "k_step64": ["ram_step_fast64.hip", "ram_node64.h", "ram_kernels.hip", "ram_wave.h", "ram_device.h",
                                "ram_internal.h"],
                   "k_adjf_uni": ADJ_FAST_SOURCES,
                   "k_adjf_gen": ADJ_FAST_SOURCES,

@@ -23,6 +23,7 @@
 // upwind face states and van Leer slopes are transposed cell by cell; the
 // limiter's derivative is taken as zero where the one-sided slopes do not
 // have the same sign, and dv = 0 uses the dv >= 0 branch.
+#include "ram_adjoint_dev.h"
 #include "ram_device.h"
 
 namespace ram {
@@ -659,26 +660,9 @@ hipError_t launch_edge_sum(const Rows &R, const int64_t *wstart, const void *edg
 
 namespace {
 
-// One wave per row: lane l sums the row's tile terms l, l + 64, ... in order,
-// then the lanes combine in a fixed butterfly (the same sum in every run).
 __global__ __launch_bounds__(256) void k_v0_reduce(Rows R, const double *part, double *v0bar)
 {
-    const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
-    const int lane = (int)threadIdx.x % 64;
-    if (row >= R.n_rows) return;
-    int64_t t0, t1;
-    if (R.n_cols > 0) {
-        const int64_t tpr = (R.n_cols + R.tile - 1) / R.tile;
-        t0 = row * tpr;
-        t1 = t0 + tpr;
-    } else {
-        t0 = R.tile_ptr[row];
-        t1 = R.tile_ptr[row + 1];
-    }
-    double s = 0.0;
-    for (int64_t t = t0 + lane; t < t1; t += 64) s += part[t];
-    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
-    if (lane == 0) v0bar[row] += s;
+    v0_reduce_row(R, part, v0bar, (int64_t)blockIdx.x * 4 + threadIdx.x / 64);
 }
 
 } // namespace

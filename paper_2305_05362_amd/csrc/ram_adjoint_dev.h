@@ -78,5 +78,27 @@ __device__ __attribute__((noinline)) double direct_qtilde(
     return dq;
 }
 
+// v0bar of one row, by a wave: lane l sums the row's tile terms l, l + 64, ...
+// in order, then the lanes combine in a fixed butterfly (the same sum in every
+// run).
+__device__ inline void v0_reduce_row(const Rows &R, const double *part, double *v0bar, int64_t row)
+{
+    const int lane = (int)threadIdx.x % 64;
+    if (row >= R.n_rows) return;
+    int64_t t0, t1;
+    if (R.n_cols > 0) {
+        const int64_t tpr = (R.n_cols + R.tile - 1) / R.tile;
+        t0 = row * tpr;
+        t1 = t0 + tpr;
+    } else {
+        t0 = R.tile_ptr[row];
+        t1 = R.tile_ptr[row + 1];
+    }
+    double s = 0.0;
+    for (int64_t t = t0 + lane; t < t1; t += 64) s += part[t];
+    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
+    if (lane == 0) v0bar[row] += s;
+}
+
 } // namespace dev
 } // namespace ram

@@ -37,6 +37,7 @@
 // path).
 #include "ram_device.h"
 #include "ram_adjoint_dev.h"
+#include "ram_adjoint_wave.h"
 #include "ram_wave.h"
 
 namespace ram {
@@ -68,13 +69,6 @@ __device__ __forceinline__ void lds8(const float *s, int i, float (&o)[8])
 __device__ __forceinline__ void f4(const float4 &v, float *o)
 {
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-}
-
-// Sum of a double over the wave.
-__device__ __forceinline__ double wave_sum(double v)
-{
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    return v;
 }
 
 // The residual step's transpose on four consecutive cells a .. a+3 (Section
@@ -192,20 +186,6 @@ __device__ __forceinline__ void res_stage(const ResIn &r, float *st, int cl, int
     lds8(sqh, cl + 2, q);
     lds8(sqb, cl + 2, qb);
     lds8(sdv, cl + 2, v8);
-}
-
-// Store the gradient v of window cell j (of W; row cell `cell`): a cell only
-// this tile's window holds goes to the state, the window's first p cells
-// (head) and its last p (tail; the two overlap-free when W < 2p) to the
-// tile's side buffer, for k_adjf_edges.  One store a lane, whichever it is.
-template <int P>
-__device__ __forceinline__ void put_cell(float *qbi, float *edge, int cell, int j, int W, float v)
-{
-    float *dst;
-    if (j >= P && j < W - P) dst = qbi + cell;
-    else if (j < P) dst = edge + j;
-    else dst = edge + P + (j - max(P, W - P));
-    *dst = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -407,28 +387,6 @@ __device__ __forceinline__ void load_geom(const MeshTab &tb, int n, int cb, floa
     dxi[0] = d0.x; dxi[1] = d0.y;
     dxi[2] = d1.x; dxi[3] = d1.y; dxi[4] = d1.z; dxi[5] = d1.w;
     dxi[6] = d2.x; dxi[7] = d2.y;
-}
-
-// v0bar of a tile from q~ at its nodes (node m = t + 64u in slot u) and Mbar'
-// in smb: -dt sum_i Mbar'_i (q~_{i+1} - q~_i), one term a tile.
-template <int NS, typename MT>
-__device__ __forceinline__ void v0_term(const StepAdjArgs &a, int tile, const double (&qt)[NS],
-                                        const MT *smb, int nd, int t)
-{
-    double vp = 0.0;
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int m = t + u * kLanes;
-        // q~ of node m + 1: the next lane's, lane 63 the next slot's lane 0
-        double qn = __shfl_down(qt[u], 1);
-        if (u + 1 < NS) {
-            const double q0 = __shfl(qt[u + 1 < NS ? u + 1 : u], 0);
-            if (t == kLanes - 1) qn = q0;
-        }
-        if (m < nd) vp -= (double)smb[1 + m] * (qn - qt[u]);
-    }
-    vp = wave_sum(vp);
-    if (t == 0) a.v0part[tile] = a.dt * vp;
 }
 
 // ---------------------------------------------------------------------------
@@ -657,48 +615,15 @@ __device__ __forceinline__ void adj_window_tile(const StepAdjArgs &a, const Fast
 // gradient telescoped from the tile's Vbar down to one Mbar' plus the
 // stencils that straddle the cell, q~ from global memory.
 // ---------------------------------------------------------------------------
-// The reconstruction q~ at a node in cell c from global memory: the weights'
-// x-derivatives dw on the cumulative differences C(c - lo + b) - C(c), from
-// the masses of cells c-lo .. c+p-lo-1 (FP64).
-template <int P>
-__device__ __forceinline__ double qtilde_global(const double *x, const float *q, int n,
-                                                const double (&dw)[P + 1], int c)
-{
-    constexpr int LO = (P - 1) / 2;
-    double m[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) m[k] = cell_mass(x, q, n, (int64_t)c - LO + k);
-    double dq = 0.0, up = 0.0, dn = 0.0;
-#pragma unroll
-    for (int b = LO + 1; b <= P; ++b) {
-        up += m[b - 1];
-        dq += dw[b] * up;
-    }
-#pragma unroll
-    for (int b = LO - 1; b >= 0; --b) {
-        dn += m[b];
-        dq -= dw[b] * dn;
-    }
-    return dq;
-}
-
 template <int P, bool RES, bool V0>
 __device__ __forceinline__ void adj_direct_tile(const StepAdjArgs &a, const FastTile &ft,
                                                 unsigned char *su, float *smb, int t)
 {
-    constexpr int LO = (P - 1) / 2;
-    constexpr int NS = (kFastNodes + kLanes - 1) / kLanes;
-    const Rows &R = a.rows;
-    const MeshTab &tb = R.tab;
-    const int n = (int)R.n_cols;
-    const int tile = ft.pad[0];
-    const TilePos p = tile_pos(tile, n, 0);
-    const int i0 = p.i0, nd = p.nd, NE = nd + 1, cl = min(4 * t, nd - 4);
+    const MeshTab &tb = a.rows.tab;
+    const int n = (int)a.rows.n_cols;
+    const TilePos p = tile_pos(ft.pad[0], n, 0);
+    const int i0 = p.i0, nd = p.nd, cl = min(4 * t, nd - 4);
     const int64_t qoff = (int64_t)p.row * n;
-    float *qbi = (float *)a.qbar_in + qoff;
-    const double *x = R.edges;
-    const double len = x[n] - x[0];
-    const RowShift rs = row_shift(a.v0[p.row] * a.dt, len, tb.scal[1]);
     const bool want_dvb = RES && a.dvbar != nullptr;
 
     const ResIn ri = res_load<RES>(a, qoff, n, i0, nd, cl, want_dvb);
@@ -710,131 +635,7 @@ __device__ __forceinline__ void adj_direct_tile(const StepAdjArgs &a, const Fast
                      [&](const float (&gs)[4]) { store_mb(smb, gs, dxi, nd, t); });
     wave_sync();
 
-    int64_t *sgd = (int64_t *)su;                    // node m's extended source index
-    double *svb = (double *)(sgd + kFastNodes);      // and its Vbar
-    double qt[NS];
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int m = t + u * kLanes;
-        qt[u] = 0.0;
-        if (m < NE) {
-            const int en = i0 + m;
-            const int kx = en >= n ? 1 : 0;
-            float w[P + 1];
-            double xh;
-            int c;
-            sgd[m] = node_eval_adj<float, P>(x, n, tb, rs, len, x[en - kx * n], kx, w, c, xh);
-            svb[m] = (double)smb[m] - (double)smb[m + 1];
-            if constexpr (V0) {
-                double dwd[P + 1];
-                node_dweights<float, P>(tb, c, xh, dwd);
-                qt[u] = qtilde_global<P>(x, (const float *)a.q_fwd + qoff, n, dwd, c);
-            }
-        }
-    }
-    wave_sync();
-    // the window: this tile's first node's stencil up to the next tile's
-    // (the row's first tile one period on, for the last tile of a row)
-    const int tpr = (n + kFT - 1) / kFT;
-    const bool last = i0 + nd >= n;
-    auto wlo_of = [&](int k) {
-        const FastTile &r = a.fast.rec[k];
-        return (int64_t)(((uint64_t)(uint32_t)r.wlo_hi << 32) | (uint32_t)r.wlo_lo);
-    };
-    const int64_t wl = wlo_of(tile);
-    const int64_t wend = (last ? wlo_of(tile - (tpr - 1)) + n : wlo_of(tile + 1)) + P;
-    const int Wd = (int)(wend - wl);
-    float *edge = (float *)a.edge + (int64_t)tile * (2 * P);
-    for (int j = t; j < Wd; j += kLanes) {
-        const int64_t target = wl + j + LO;
-        int lo = 0, hi = NE;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (sgd[mid] > target) hi = mid; else lo = mid + 1;
-        }
-        // nodes lo.. lie wholly above the cell: their Vbar telescopes to Mbar'_{lo-1}
-        double S = (lo >= 1 && lo <= nd) ? (double)smb[lo] : 0.0;
-        for (int e = lo - 1; e >= 0 && sgd[e] > target - P; --e) {
-            const int en = i0 + e;
-            const int kx = en >= n ? 1 : 0;
-            double ww[P + 1], xh2;
-            int c2;
-            node_eval_adj<double, P>(x, n, tb, rs, len, x[en - kx * n], kx, ww, c2, xh2);
-            // the share of the node's weights on cumulative nodes above the
-            // cell, the own weight taken as one minus the others
-            const int bmin = (int)min((int64_t)P, max((int64_t)1, target - sgd[e] + 1));
-            double h = 0.0;
-            if (bmin > LO) {
-                for (int b = P; b >= bmin; --b) h += ww[b];
-            } else {
-                for (int b = 0; b < bmin; ++b) h += ww[b];
-                h = 1.0 - h;
-            }
-            S += svb[e] * h;
-        }
-        const int mm = wrapi(wl + j, n);
-        put_cell<P>(qbi, edge, mm, j, Wd, (float)(S * (double)tb.dxf[mm]));
-    }
-    if constexpr (V0) v0_term<NS>(a, tile, qt, smb, nd, t);
-}
-
-// The window cells that several tiles add into: the first p of every tile's
-// window (a tile's window ends p cells past the next tile's start).  Boundary
-// T (one thread) writes the cells from its window start up to p cells on or
-// the next tile's start, each the sum, tile T first and then down, of the
-// terms the tiles whose windows hold it stored (head or tail; tile k's window
-// is [A_k, A_{k+1} + p), and across the row's ends the row's tiles one period
-// away).  Usually two terms; more where a tile's nodes fall in fewer than p
-// source cells.
-template <int P>
-__global__ __launch_bounds__(256) void k_adjf_edges(StepAdjArgs a)
-{
-    const int64_t tile = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (tile >= a.rows.n_tiles) return;
-    const int n = (int)a.rows.n_cols;
-    const int tpr = (n + kFT - 1) / kFT;
-    const int64_t row = tile / tpr;
-    const int k0 = (int)(tile - row * tpr);
-    // window start of the row's k-th tile, any k (k mod tpr, one period per wrap)
-    auto start = [&](int k, int64_t &id) {
-        const int q = k >= 0 ? k / tpr : -((-k + tpr - 1) / tpr);
-        id = row * tpr + (k - q * tpr);
-        const FastTile &r = a.fast.rec[id];
-        const int64_t w = (int64_t)(((uint64_t)(uint32_t)r.wlo_hi << 32) | (uint32_t)r.wlo_lo);
-        return w + (int64_t)q * n;
-    };
-    int64_t idp, id0, idn;
-    const int64_t ap = start(k0 - 1, idp), a0 = start(k0, id0), a1 = start(k0 + 1, idn);
-    float *qbi = (float *)a.qbar_in + row * n;
-    if (a1 - a0 >= P && a0 - ap >= P) {
-        // two terms a cell: this tile's head and the previous tile's tail
-        // (its window [ap, a0 + p) of at least 2p cells ends its tail there)
-        const float *e0 = (const float *)a.edge + id0 * (2 * P);
-        const float *ep = (const float *)a.edge + idp * (2 * P);
-        float v[P];
-#pragma unroll
-        for (int k = 0; k < P; ++k) v[k] = (0.0f + e0[k]) + ep[P + k];
-#pragma unroll
-        for (int k = 0; k < P; ++k) qbi[wrapi(a0 + k, n)] = v[k];
-        return;
-    }
-    const int64_t mend = min(a0 + P, a1);
-    for (int64_t m = a0; m < mend; ++m) {
-        float sum = 0.0f;
-        int64_t at = a0, an = a1, id = id0;
-        for (int k = k0; k > k0 - tpr - 1; --k) {
-            if (k != k0) {
-                an = at;
-                at = start(k, id);
-            }
-            const int64_t W = an - at + P;
-            if (at + W <= m) break;
-            const int pos = (int)(m - at);
-            const float *e = (const float *)a.edge + id * (2 * P);
-            sum += pos < P ? e[pos] : e[P + pos - (int)max((int64_t)P, W - P)];
-        }
-        qbi[wrapi(m, n)] = sum;
-    }
+    direct_shift<float, P, V0>(a, ft, su, smb, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -1232,6 +1033,8 @@ __device__ __forceinline__ void lim_tile(const StepAdjArgs &a, const FastTile &f
     // ---- 2. every node's window index, cell and FP64 position in the cell ---------
     const int16_t *jcp =
         planned && !uniform ? a.fast.jc + (int64_t)ft.pad[1] * kFastNodes : nullptr;
+    // (only a uniform tile's node may lie beside its cell, and then over the seam)
+    const double seam = uniform ? 0.5 * len : __builtin_huge_val();
     int kv[NS], cv[NS];
     double thv[NS], hv[NS];
 #pragma unroll
@@ -1254,7 +1057,7 @@ __device__ __forceinline__ void lim_tile(const StepAdjArgs &a, const FastTile &f
         }
         const double h = tb.dx[c];
         double d = np.xt - x[c];
-        d = d > 0.5 * len ? d - len : (d < -0.5 * len ? d + len : d);
+        d = d > seam ? d - len : (d < -seam ? d + len : d);
         kv[u] = k;
         cv[u] = c;
         thv[u] = d * tb.dxinv[c];
@@ -1377,10 +1180,7 @@ hipError_t ladj_kernels(const StepAdjArgs &a, hipStream_t st)
     constexpr int P = 2 * LimHalo<R>::lo + 1;
     const int64_t nt = a.rows.n_tiles;
     hipLaunchKernelGGL((k_ladj<R, RES, V0>), dim3((unsigned)nt), dim3(kLanes), 0, st, a);
-    hipLaunchKernelGGL((k_adjf_edges<P>), dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !V0) return e;
-    return launch_v0_reduce(a.rows, a.v0part, a.v0bar, st);
+    return launch_edges<float, P>(a, V0, st);
 }
 
 template <int R>
@@ -1475,10 +1275,7 @@ hipError_t adjf_kernels(const StepAdjArgs &a, hipStream_t st)
         hipLaunchKernelGGL((k_adjf_uni<P, RES, V0>), gu, b, 0, st, a);
         hipLaunchKernelGGL((k_adjf_gen<P, RES, V0>), gg, b, 0, st, a);
     }
-    hipLaunchKernelGGL((k_adjf_edges<P>), dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !V0) return e;
-    return launch_v0_reduce(a.rows, a.v0part, a.v0bar, st);
+    return launch_edges<float, P>(a, V0, st);
 }
 
 template <int P>

@@ -351,12 +351,15 @@ size_t plan_w_bytes(int64_t nt)
 
 // Plan the tiles of a shared-mesh step once per call: the fast kernels'
 // records, tile lists and node data, or the general kernel's window plan.
-hipError_t plan_shared(ram::StepArgs &a, int plan_order, bool fast, void *wlo_p, void *w_p,
-                       hipStream_t st)
+// nodes = false: a single FP64 step, whose tiles locate their nodes themselves.
+hipError_t plan_shared(ram::StepArgs &a, int plan_order, bool fast, bool nodes, void *wlo_p,
+                       void *w_p, hipStream_t st)
 {
     if (fast) {
         a.fast = ram::fast_plan_at(w_p, a.rows.n_tiles);
-        return ram::launch_plan_fast(a, plan_order, a.fast, st);
+        const hipError_t e = ram::launch_plan_fast(a, plan_order, a.fast, nodes, st);
+        if (!nodes) a.fast.jc = nullptr;
+        return e;
     }
     a.plan_wlo = (const int64_t *)wlo_p;
     a.plan_w = (const int32_t *)w_p;
@@ -485,7 +488,7 @@ ram_status launch_steps(ram_ctx *ctx, ram::StepArgs a, ram_dtype dtype,
         const int plan_order = recon == 0 ? order : (recon == RAM_RECON_PLM ? 3 : 5);
         const bool fast = (recon == 0 || dtype == RAM_F32) && allow_fast &&
                           use_fast_shape(ctx, a.rows.shared != 0, a.rows.n_cols, dtype, scan);
-        e = plan_shared(a, plan_order, fast, mem + wlo_off, mem + w_off, ctx->stream);
+        e = plan_shared(a, plan_order, fast, !f64 || n_steps > 1, mem + wlo_off, mem + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     } else if (rag_off >= 0) {
         a.rag = ram::rag_plan_at(mem + rag_off, a.rows.n_tiles);
@@ -523,12 +526,26 @@ ram_status launch_steps(ram_ctx *ctx, ram::StepArgs a, ram_dtype dtype,
     return run_graphed(ctx, key_of(a, extra), n_steps, loop);
 }
 
+// The step adjoint on a shared mesh at the default schedule otherwise runs a
+// tile of 256 cells a wave too, one cell a lane (FP64; FP32 rows the streaming
+// kernels do not take), on rows of at least a tile and a halo: 45 us against
+// the general adjoint's 99 for one FP64 step back at 512 x 2048 cells, 28.9 and
+// 30.5 at 8 x 264, FP32 131 and 153 at 1000 x 6001, 25.9 and 31.5 at 8 x 265.
+// Shorter rows (windows that wrap the row more than
+// once) and the other schedules stay with the general shared-mesh adjoint.
+bool use_tile_adjoint(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype)
+{
+    return use_fast_shape(ctx, L->edges_shared != 0, L->n_cols, dtype, RAM_SCAN_F64) &&
+           L->n_cols >= ram::kFastTile + 8 && tiles_of(L, ram::kFastTile) <= INT32_MAX / 2;
+}
+
 // The streaming adjoint's per-call set-up: mesh tables, the shift's tile plan
 // without halo (records, tile lists, node data), the v0bar and edge buffers;
 // the per-step pointers (states, gradients) are left to the caller.
-ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, const double *edges,
-                             const double *v0, double dt, int order, const void *dv,
-                             void *dvbar, double *v0bar, ram::StepAdjArgs &a)
+ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtype,
+                             const double *edges, const double *v0, double dt, int order,
+                             const void *dv, void *dvbar, double *v0bar, bool nodes,
+                             ram::StepAdjArgs &a)
 {
     ram_status st;
     Carve cv;
@@ -537,14 +554,14 @@ ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, const doubl
     const int64_t nt = tiles_of(layout, rp.tile);
     const size_t rec_off = cv.take(ram::fast_plan_bytes(nt));
     const size_t v0_off = cv.take(v0bar ? sizeof(double) * nt : 0);
-    const size_t edge_off = cv.take(sizeof(float) * 2 * (size_t)order * nt);
+    const size_t edge_off = cv.take(ram::adj_edge_bytes(nt, order, elem_size(dtype)));
     if ((st = ensure_scratch(ctx, cv.off)) != RAM_OK) return st;
     ram::StepArgs p;
     if ((st = make_rows(ctx, layout, edges, rp, p.rows)) != RAM_OK) return st;
     p.v0 = v0;
     p.dt = dt;
     const ram::FastPlan fp = ram::fast_plan_at((char *)ctx->scratch + rec_off, nt);
-    const hipError_t e = ram::launch_plan_fast(p, order, fp, ctx->stream);
+    const hipError_t e = ram::launch_plan_fast(p, order, fp, nodes, ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "tile plan launch");
     a = ram::StepAdjArgs();
     a.rows = p.rows;
@@ -555,7 +572,8 @@ ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, const doubl
     a.v0 = v0;
     a.dt = dt;
     a.fast = fp;
-    a.edge = (float *)((char *)ctx->scratch + edge_off);
+    if (!nodes) a.fast.jc = nullptr;
+    a.edge = (char *)ctx->scratch + edge_off;
     return RAM_OK;
 }
 
@@ -569,16 +587,21 @@ ram_status step_adjoint_shared(ram_ctx *ctx, const ram_layout *layout, ram_dtype
 {
     ram_status st;
     Carve cv;
-    if (use_fast_adjoint(ctx, layout, dtype, {q_fwd, q_half, dv, qbar_out, qbar_in, dvbar})) {
+    const bool fast =
+        use_fast_adjoint(ctx, layout, dtype, {q_fwd, q_half, dv, qbar_out, qbar_in, dvbar});
+    if (fast || use_tile_adjoint(ctx, layout, dtype)) {
         ram::StepAdjArgs a;
-        if ((st = plan_adjoint_fast(ctx, layout, edges, v0, dt, order, dv, dvbar, v0bar, a)) !=
+        if ((st = plan_adjoint_fast(ctx, layout, dtype, edges, v0, dt, order, dv, dvbar, v0bar,
+                                    fast, a)) !=
             RAM_OK)
             return st;
         a.q_fwd = q_fwd;
         a.q_half = q_half;
         a.qbar_out = qbar_out;
         a.qbar_in = qbar_in;
-        const hipError_t e = ram::launch_step_adjoint_fast(a, order, ctx->stream);
+        const hipError_t e =
+            fast ? ram::launch_step_adjoint_fast(a, order, ctx->stream)
+                 : ram::launch_step_adjoint_tile(a, dtype == RAM_F64, order, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "step adjoint launch");
         return RAM_OK;
     }
@@ -1087,7 +1110,7 @@ ram_status ram_step_limited_record(ram_ctx *ctx, const ram_layout *layout,
     hipError_t e;
     if (shared) {
         a.dv = dv;
-        e = plan_shared(a, recon == RAM_RECON_PLM ? 3 : 5, fast, (char *)ctx->scratch + wlo_off,
+        e = plan_shared(a, recon == RAM_RECON_PLM ? 3 : 5, fast, true, (char *)ctx->scratch + wlo_off,
                         (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     }
@@ -1171,7 +1194,8 @@ ram_status limited_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, ram_reco
     ram_status st;
     const int order = recon == RAM_RECON_PLM ? 3 : 5;
     ram::StepAdjArgs a;
-    if ((st = plan_adjoint_fast(ctx, layout, edges, v0, dt, order, dv, dvbar, v0bar, a)) !=
+    if ((st = plan_adjoint_fast(ctx, layout, RAM_F32, edges, v0, dt, order, dv, dvbar, v0bar,
+                                true, a)) !=
         RAM_OK)
         return st;
     a.q_fwd = q_fwd;
@@ -1358,7 +1382,7 @@ ram_status setup_row_step(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtyp
     rs.a.dt = dt;
     rs.shared = rs.a.rows.has_tab != 0 && rs.a.rows.n_cols > 0;
     if (rs.shared) {
-        hipError_t e = plan_shared(rs.a, plan_order, fast, (char *)ctx->scratch + wlo_off,
+        hipError_t e = plan_shared(rs.a, plan_order, fast, true, (char *)ctx->scratch + wlo_off,
                                    (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
         if (scan == RAM_SUM_DIRECT && recon == 0)
@@ -1529,7 +1553,7 @@ ram_status ram_step_tile_paths(ram_ctx *ctx, const ram_layout *layout, const dou
     // only its being non-null matters to the plan (the halo)
     a.dv = with_residual ? (const void *)edges : nullptr;
     const ram::FastPlan fp = ram::fast_plan_at((char *)ctx->scratch + rec_off, nt);
-    hipError_t e = ram::launch_plan_fast(a, order, fp, ctx->stream);
+    hipError_t e = ram::launch_plan_fast(a, order, fp, true, ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "tile plan launch");
     // the kind is the record's first word
     e = hipMemcpy2DAsync(paths, sizeof(int32_t), fp.rec, sizeof(ram::FastTile), sizeof(int32_t),
@@ -1671,7 +1695,7 @@ ram_status ram_step_record(ram_ctx *ctx, const ram_layout *layout,
     const bool shared = a.rows.has_tab != 0 && a.rows.n_cols > 0;
     hipError_t e;
     if (shared) {
-        e = plan_shared(a, order, fast, (char *)ctx->scratch + wlo_off,
+        e = plan_shared(a, order, fast, !f64 || n_steps > 1, (char *)ctx->scratch + wlo_off,
                         (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     }
@@ -1789,20 +1813,23 @@ ram_status ram_step_adjoint_steps(ram_ctx *ctx, const ram_layout *layout,
     auto at = [&](const void *base, int64_t k) {
         return base ? (const void *)((const char *)base + (size_t)k * state_bytes) : nullptr;
     };
-    if (layout->edges_shared &&
-        use_fast_adjoint(ctx, layout, dtype, {q_traj, q_half, dv, qbar, qbar_work, dvbar_accum}) &&
-        state_bytes % 16 == 0) {
+    const bool fast =
+        layout->edges_shared && state_bytes % 16 == 0 &&
+        use_fast_adjoint(ctx, layout, dtype, {q_traj, q_half, dv, qbar, qbar_work, dvbar_accum});
+    if (fast || (layout->edges_shared && use_tile_adjoint(ctx, layout, dtype))) {
         // one plan for every step: the shift is the same at each
         ram::StepAdjArgs a;
-        if ((st = plan_adjoint_fast(ctx, layout, edges, v0, dt, order, dv, dvbar_accum,
-                                    v0bar_accum, a)) != RAM_OK)
+        if ((st = plan_adjoint_fast(ctx, layout, dtype, edges, v0, dt, order, dv, dvbar_accum,
+                                    v0bar_accum, fast || n_steps > 1, a)) != RAM_OK)
             return st;
         for (int64_t k = n_steps - 1; k >= 0; --k) {
             a.q_fwd = at(q_traj, k);
             a.q_half = dv ? at(q_half, k) : nullptr;
             a.qbar_out = cur;
             a.qbar_in = oth;
-            const hipError_t e = ram::launch_step_adjoint_fast(a, order, ctx->stream);
+            const hipError_t e =
+                fast ? ram::launch_step_adjoint_fast(a, order, ctx->stream)
+                     : ram::launch_step_adjoint_tile(a, dtype == RAM_F64, order, ctx->stream);
             if (e != hipSuccess) return hip_fail(e, "step adjoint launch");
             std::swap(cur, oth);
         }

@@ -404,8 +404,9 @@ hipError_t launch_step_shared(const StepArgs &a, bool f64, int scan, int order,
                               int items, hipStream_t stream);
 // The FP32 direct-sum step on a shared mesh: plan the tiles into `plan`
 // (R.tile == kFastTile, tables with the uniform-run counts), then per step the
-// uniform-tile and the searching-tile kernels (a.fast set).
-hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan,
+// uniform-tile and the searching-tile kernels (a.fast set).  nodes: with the
+// tile lists and the searching tiles' node data; without, the records only.
+hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan, bool nodes,
                             hipStream_t stream);
 hipError_t launch_step_fast(const StepArgs &a, int order, int scan, hipStream_t stream);
 // A second stream and two events of a context: while a step loop is being
@@ -458,6 +459,9 @@ hipError_t launch_step_adjoint_shared(const StepAdjArgs &a, bool f64, int order,
 // uniform-run tiles, the other tiles, the sums of the window cells that
 // neighbouring tiles share (a.edge), the v0bar sums.
 hipError_t launch_step_adjoint_fast(const StepAdjArgs &a, int order, hipStream_t stream);
+// The same on tiles of one cell a lane, FP64 or FP32, any row of at least a
+// tile and a halo and any array.
+hipError_t launch_step_adjoint_tile(const StepAdjArgs &a, bool f64, int order, hipStream_t stream);
 // The limited (PLM / PPM) step backwards on the same tiles (plan of order
 // 2 lo + 1, a.q_fwd the state the shift read; a.dv null: the shift alone).
 hipError_t launch_step_limited_adjoint_fast(const StepAdjArgs &a, int recon,

@@ -30,6 +30,7 @@
 //     sums from global memory.
 // Tiles of 256 cells keep the searching tiles to the cells near the mesh's
 // non-uniform stretches.
+#include "ram_node64.h"
 #include "ram_rows.h"
 
 #include <type_traits>
@@ -445,37 +446,10 @@ __global__ __launch_bounds__(kBlock) void k_plan_nodes(StepArgs a, int lists)
         const int jbase = (int)(rs.kf0 * (int64_t)n - wlo);
         float *th = a.fast.theta + (int64_t)tile * kFastNodes;
         int16_t *jcw = a.fast.jc + (int64_t)tile * kFastNodes;
-        // each load of all the lane's nodes before the next one's: x, the
-        // bucket, the cell's geometry (lanes past the last slot repeat it)
+        // (lanes past the last slot repeat it)
         int ce[NS], kx[NS];
         double xt[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int m = min(t + s * kLanes, kFastNodes - 1);
-            const int en = tp.i0 - H + min(m, NE - 1);
-            kx[s] = en < 0 ? -n : (en >= n ? n : 0);
-            xt[s] = x[en - kx[s]];
-        }
-        double2 nx[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const NodePos np = node_pos(xt[s], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
-            ce[s] = tb.bucket[np.b];
-            nx[s] = tb.bnext[np.b];
-            xt[s] = np.xt;
-            kx[s] += np.dk * n;
-        }
-        bool walk = false;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            ce[s] = cell_from_bucket(ce[s], nx[s], xt[s]);
-            walk = walk || xt[s] >= nx[s].y;
-        }
-        if (__any(walk ? 1 : 0)) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                if (xt[s] >= nx[s].y) ce[s] = cell_walk(x, n, ce[s], xt[s]);
-        }
+        locate_nodes<NS>(x, n, tb, rs, x0, xN, tp.i0 - H, NE, t, ce, kx, xt);
         double xc[NS], di[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -1808,7 +1782,7 @@ hipError_t step_rag_p(const StepArgs &a, int scan, hipStream_t st)
 
 } // namespace
 
-hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan,
+hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan, bool nodes,
                             hipStream_t stream)
 {
     if (a.rows.n_tiles <= 0) return hipSuccess;
@@ -1817,20 +1791,20 @@ hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan,
     b.fast = plan;
     const int64_t nt = a.rows.n_tiles;
     const int lists = (int)((nt + kBlock - 1) / kBlock);
-    const int64_t nodes = ((nt + kNodeTiles - 1) / kNodeTiles + 7) / 8 * 8;
-    const dim3 gt((unsigned)plan_groups(nt)), bt(kLanes), gn((unsigned)(lists + nodes)), bn(kBlock);
+    const int64_t groups = ((nt + kNodeTiles - 1) / kNodeTiles + 7) / 8 * 8;
+    const dim3 gt((unsigned)plan_groups(nt)), bt(kLanes), gn((unsigned)(lists + groups)), bn(kBlock);
     switch (order) {
     case 1:
         hipLaunchKernelGGL(k_plan_fast<1>, gt, bt, 0, stream, a, plan);
-        hipLaunchKernelGGL(k_plan_nodes<1>, gn, bn, 0, stream, b, lists);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<1>, gn, bn, 0, stream, b, lists);
         break;
     case 3:
         hipLaunchKernelGGL(k_plan_fast<3>, gt, bt, 0, stream, a, plan);
-        hipLaunchKernelGGL(k_plan_nodes<3>, gn, bn, 0, stream, b, lists);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<3>, gn, bn, 0, stream, b, lists);
         break;
     default:
         hipLaunchKernelGGL(k_plan_fast<5>, gt, bt, 0, stream, a, plan);
-        hipLaunchKernelGGL(k_plan_nodes<5>, gn, bn, 0, stream, b, lists);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<5>, gn, bn, 0, stream, b, lists);
         break;
     }
     return hipGetLastError();

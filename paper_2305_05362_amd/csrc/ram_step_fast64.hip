@@ -27,6 +27,7 @@
 // Tiles whose window exceeds the LDS buffer take the nodes' cells from the
 // bucket index and sum from global memory.
 #include "ram_device.h"
+#include "ram_node64.h"
 #include "ram_wave.h"
 
 namespace ram {
@@ -74,112 +75,9 @@ __device__ __forceinline__ void residual4d(const double *s, const double *dvv, d
     for (int k = 0; k < 4; ++k) out[k] = s[k + 2] - dt * (F[k + 1] - F[k]) * dxi(k);
 }
 
-// Lagrange weights of the cumulative at theta through source cell c's nodes,
-// from the mesh's FP64 stencil planes (pairs 1 .. P of stpd: node offsets th_b
-// in units of dx_c other than the cell's own edges, 0 and 1, then reciprocal
-// denominators rd_b other than the own node's, whose weight no partial
-// integral uses), as prefix and suffix products of (theta - th_b).
-// Neighbouring lanes read neighbouring cells' pairs: 16 bytes a lane a load.
-template <int P>
-__device__ __forceinline__ void node_weights(const double2 *stpd, int n, int c, double th,
-                                             double (&wk)[P + 1])
-{
-    constexpr int LO = (P - 1) / 2;
-    double v[2 * P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-        const double2 pr = stpd[(k + 1) * n + c];
-        v[2 * k] = pr.x;
-        v[2 * k + 1] = pr.y;
-    }
-    double rth[P + 1], rrd[P + 1];
-    int k = 0;
-#pragma unroll
-    for (int b = 0; b <= P; ++b) rth[b] = b == LO ? 0.0 : (b == LO + 1 ? 1.0 : v[k++]);
-#pragma unroll
-    for (int b = 0; b <= P; ++b) rrd[b] = b == LO ? 0.0 : v[k++];
-    double tt[P + 1], pre[P + 1], suf[P + 1];
-#pragma unroll
-    for (int b = 0; b <= P; ++b) tt[b] = th - rth[b];
-    pre[0] = 1.0;
-#pragma unroll
-    for (int b = 1; b <= P; ++b) pre[b] = pre[b - 1] * tt[b - 1];
-    suf[P] = 1.0;
-#pragma unroll
-    for (int b = P - 1; b >= 0; --b) suf[b] = suf[b + 1] * tt[b + 1];
-#pragma unroll
-    for (int b = 0; b <= P; ++b) wk[b] = rrd[b] * (pre[b] * suf[b]);
-}
-
-// Reciprocal Lagrange denominator of node a among P+1 equally spaced nodes.
-template <int P>
-__host__ __device__ constexpr double eq_denominator_inv(int a)
-{
-    double d = 1.0;
-    for (int b = 0; b <= P; ++b)
-        if (b != a) d *= (double)(a - b);
-    return 1.0 / d;
-}
-
-// The same weights for a cell of a uniform run, from the FP32 deviations of
-// its offsets and denominators from those of equally spaced nodes (stdv:
-// float4, float4, float planes): 36 bytes a node instead of 80.
-template <int P>
-__device__ __forceinline__ void node_weights_uni(const float *stdv, int n, int c, double th,
-                                                 double (&wk)[P + 1])
-{
-    constexpr int LO = (P - 1) / 2;
-    float v[12];
-    const float4 A = ((const float4 *)stdv)[c];
-    v[0] = A.x; v[1] = A.y; v[2] = A.z; v[3] = A.w;
-    if constexpr (2 * P - 1 > 4) {
-        const float4 B = ((const float4 *)stdv)[n + c];
-        v[4] = B.x; v[5] = B.y; v[6] = B.z; v[7] = B.w;
-    }
-    if constexpr (2 * P - 1 > 8) v[8] = stdv[8 * n + c];
-    double rth[P + 1], rrd[P + 1];
-    int k = 0;
-#pragma unroll
-    for (int b = 0; b <= P; ++b)
-        rth[b] = b == LO ? 0.0 : (b == LO + 1 ? 1.0 : (double)(b - LO) + (double)v[k++]);
-#pragma unroll
-    for (int b = 0; b <= P; ++b)
-        rrd[b] = b == LO ? 0.0 : eq_denominator_inv<P>(b) * (1.0 + (double)v[k++]);
-    double tt[P + 1], pre[P + 1], suf[P + 1];
-#pragma unroll
-    for (int b = 0; b <= P; ++b) tt[b] = th - rth[b];
-    pre[0] = 1.0;
-#pragma unroll
-    for (int b = 1; b <= P; ++b) pre[b] = pre[b - 1] * tt[b - 1];
-    suf[P] = 1.0;
-#pragma unroll
-    for (int b = P - 1; b >= 0; --b) suf[b] = suf[b + 1] * tt[b + 1];
-#pragma unroll
-    for (int b = 0; b <= P; ++b) wk[b] = rrd[b] * (pre[b] * suf[b]);
-}
-
-// A node's shifted coordinate wrapped into [x0, xN), as node_pos forms it
-// (the bucket, which a planned node does not need, left out).
-__device__ __forceinline__ double shifted_xt(double xe, const RowShift &rs, double x0, double xN)
-{
-    const double xs = xe - rs.s;
-    const double v0 = xs - rs.p0, vp = xs - rs.pp, vm = xs - rs.pm;
-    return v0 >= xN ? vp : (v0 < x0 ? vm : v0);
-}
-
-// Position in cell c (pair 0 of stpd: its left edge and 1/dx) of a node at
-// xt, taken across the period seam when c is the neighbour over it.
-__device__ __forceinline__ double cell_theta(const double2 *stpd, int c, double xt, double len)
-{
-    const double2 g = stpd[c];
-    double d = xt - g.x;
-    d = d > 0.5 * len ? d - len : (d < -0.5 * len ? d + len : d);
-    return d * g.y;
-}
-
 // One tile.  S: kSumDirect (partials and whole cells summed from the window
 // masses) or kScanF64 (differences of the window's FP64 cumulative).
-template <int P, int H, int S, bool VEC>
+template <int P, int H, int S, bool VEC, bool PLAN>
 __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, double *sw,
                                        double *sp, double *sell, short *sjc, int t)
 {
@@ -282,8 +180,6 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
             }
         }
         // ---- each node's window index and position in its cell ---------------------
-        const int16_t *jcp =
-            ft.kind == kFastWindow ? a.fast.jc + (int64_t)ft.pad[1] * kFastNodes : nullptr;
         // (a window wraps the row at most once unless the row is shorter than it)
         const bool wrapw = W + base > 2 * n;
         auto wcell = [&](int j) {
@@ -292,26 +188,9 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
         };
         int jv[NS], cv[NS];
         double thv[NS];
+        tile_nodes<P, NS, PLAN>(a.fast, ft, x, n, tb, rs, x0, xN, i0 - H, NE, wcell, t, jv, thv);
 #pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            const int m = min(t + u * kLanes, NE - 1);
-            int e = i0 - H + m;
-            e = e < 0 ? e + n : (e >= n ? e - n : e);
-            const double xt = shifted_xt(x[e], rs, x0, xN);
-            int j = jcp ? (int)jcp[m] : LO + m;
-            int c = wcell(j);
-            double th = cell_theta(tb.stpd, c, xt, len);
-            // a uniform tile's inner node that the mesh's rounding puts in a
-            // neighbouring cell (the end nodes' cells came from the search)
-            if (!jcp && m > 0 && m < NE - 1 && (th < 0.0 || th >= 1.0)) {
-                j += th < 0.0 ? -1 : 1;
-                c = wcell(j);
-                th = cell_theta(tb.stpd, c, xt, len);
-            }
-            jv[u] = j;
-            cv[u] = c;
-            thv[u] = th;
-        }
+        for (int u = 0; u < NS; ++u) cv[u] = wcell(jv[u]);
         wave_sync();                                 // the window masses
         if constexpr (kPre) {
             // exclusive FP64 cumulative of the masses into sp: LDS cells 4g ..
@@ -347,11 +226,12 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
             const int m = min(t + u * kLanes, NE - 1);
-            double wk[P + 1];
+            double rth[P + 1], rrd[P + 1], wk[P + 1];
             if (uniform)
-                node_weights_uni<P>(tb.stdv, n, cv[u], thv[u], wk);
+                node_stencil_uni<P>(tb.stdv, n, cv[u], rth, rrd);
             else
-                node_weights<P>(tb.stpd, n, cv[u], thv[u], wk);
+                node_stencil<P>(tb.stpd, n, cv[u], rth, rrd);
+            node_weights<P>(rth, rrd, thv[u], wk);
             const int j = jv[u] + off;
             double ell = 0.0;
             if constexpr (kPre) {
@@ -489,7 +369,7 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
 // Every tile in tile order, one a wave; LDS of one wave: the window (masses,
 // cumulative, or the direct tiles' node cells, then the shifted values), the
 // nodes' partial integrals and window indices.
-template <int P, int H, int S, bool VEC>
+template <int P, int H, int S, bool VEC, bool PLAN>
 __global__ __launch_bounds__(kBlock) void k_step64(StepArgs a)
 {
     constexpr int WC = win64_cells<S>() + 8;
@@ -501,20 +381,20 @@ __global__ __launch_bounds__(kBlock) void k_step64(StepArgs a)
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= (int)a.rows.n_tiles) return;
     const FastTile r = load_rec(a.fast.rec, i);
-    tile64<P, H, S, VEC>(a, r, sw_[wid], sp_[wid], sell_[wid], sjc_[wid],
+    tile64<P, H, S, VEC, PLAN>(a, r, sw_[wid], sp_[wid], sell_[wid], sjc_[wid],
                          (int)threadIdx.x % kLanes);
 }
 
-template <int P, int S>
+template <int P, int S, bool PLAN>
 hipError_t step64_ps(const StepArgs &a, bool vec, hipStream_t st)
 {
     const dim3 g((unsigned)((a.rows.n_tiles + kWaves - 1) / kWaves)), b(kBlock);
     if (a.dv) {
-        if (vec) hipLaunchKernelGGL((k_step64<P, 2, S, true>), g, b, 0, st, a);
-        else hipLaunchKernelGGL((k_step64<P, 2, S, false>), g, b, 0, st, a);
+        if (vec) hipLaunchKernelGGL((k_step64<P, 2, S, true, PLAN>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((k_step64<P, 2, S, false, PLAN>), g, b, 0, st, a);
     } else {
-        if (vec) hipLaunchKernelGGL((k_step64<P, 0, S, true>), g, b, 0, st, a);
-        else hipLaunchKernelGGL((k_step64<P, 0, S, false>), g, b, 0, st, a);
+        if (vec) hipLaunchKernelGGL((k_step64<P, 0, S, true, PLAN>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((k_step64<P, 0, S, false, PLAN>), g, b, 0, st, a);
     }
     return hipGetLastError();
 }
@@ -525,8 +405,11 @@ hipError_t step64_p(const StepArgs &a, int scan, hipStream_t st)
     // 16-byte pairs: rows of a multiple of four cells, 16-byte aligned states
     const bool vec = (a.rows.n_cols % 4) == 0 && ((uintptr_t)a.q_out % 16) == 0 &&
                      ((uintptr_t)a.q_in % 16) == 0 && (!a.dv || ((uintptr_t)a.dv % 16) == 0);
-    return scan == kSumDirect ? step64_ps<P, kSumDirect>(a, vec, st)
-                              : step64_ps<P, kScanF64>(a, vec, st);
+    const bool plan = a.fast.jc != nullptr;
+    if (scan == kSumDirect)
+        return plan ? step64_ps<P, kSumDirect, true>(a, vec, st)
+                    : step64_ps<P, kSumDirect, false>(a, vec, st);
+    return plan ? step64_ps<P, kScanF64, true>(a, vec, st) : step64_ps<P, kScanF64, false>(a, vec, st);
 }
 
 } // namespace
