@@ -244,9 +244,11 @@ RowsPlan plan_rows(Carve &cv, const ram_layout *L, int tile, int tab_order)
 }
 
 // Fill the kernel-side row description (after ensure_scratch): ragged
-// batches get their tile table, shared meshes their tables.
+// batches get their tile table, shared meshes their tables.  copy: made beside
+// them.
 ram_status make_rows(ram_ctx *ctx, const ram_layout *L, const double *edges,
-                     const RowsPlan &p, ram::Rows &R, char *base_mem = nullptr)
+                     const RowsPlan &p, ram::Rows &R, char *base_mem = nullptr,
+                     const ram::CopyJob &copy = ram::CopyJob())
 {
     char *mem = base_mem ? base_mem : (char *)ctx->scratch;
     R.n_rows = L->n_rows;
@@ -264,14 +266,18 @@ ram_status make_rows(ram_ctx *ctx, const ram_layout *L, const double *edges,
         R.tile_row = (const int32_t *)(base + align_up(sizeof(int64_t) * (L->n_rows + 1)));
         hipError_t e = ram::launch_tiles_prep(L->row_ptr, L->n_rows, p.tile,
                                               (int64_t *)R.tile_ptr,
-                                              (int32_t *)R.tile_row, ctx->stream);
+                                              (int32_t *)R.tile_row, ctx->stream, copy);
         if (e != hipSuccess) return hip_fail(e, "tile table launch");
     }
     if (p.order > 0) {
         hipError_t e = ram::launch_mesh_prep(edges, L->n_cols, p.order, mem + p.tab_off,
-                                             R.tab, ctx->stream, p.uniform);
+                                             R.tab, ctx->stream, p.uniform,
+                                             L->n_cols > 0 ? copy : ram::CopyJob());
         if (e != hipSuccess) return hip_fail(e, "mesh table launch");
         R.has_tab = 1;
+    } else if (L->n_cols > 0) {
+        hipError_t e = ram::launch_copy(copy.src, copy.dst, copy.bytes, ctx->stream);
+        if (e != hipSuccess) return hip_fail(e, "copy launch");
     }
     return RAM_OK;
 }
@@ -351,15 +357,27 @@ size_t plan_w_bytes(int64_t nt)
 
 // Plan the tiles of a shared-mesh step once per call: the fast kernels'
 // records, tile lists and node data, or the general kernel's window plan.
-// nodes = false: a single FP64 step, whose tiles locate their nodes themselves.
-hipError_t plan_shared(ram::StepArgs &a, int plan_order, bool fast, bool nodes, void *wlo_p,
-                       void *w_p, hipStream_t st)
+// A single unlimited step has no plan: its waves make their tiles' records and
+// locate their nodes, which costs what the plan's kernels do without their
+// launches and their passes over memory.  Only FP32 batches from kAloneTiles
+// tiles up have one: their uniform tiles run faster in a kernel of their own,
+// which needs the lists.  With and without a plan, us a call, FP32 | FP64:
+//                      stretched mesh         uniform mesh           bump
+//   1024 x 4096        67 50 | 100 77         32 27 | 75 71          41 35 | 81 73
+//   2048 x 8192        209 173 | 356 304      70 75 | 268 270        97 97 | 303 300
+//   2048 x 16384       418 376 | 703 600      147 182 | 533 545      201 224 | 595 586
+constexpr int64_t kAloneTiles = 65536;
+hipError_t plan_shared(ram::StepArgs &a, int plan_order, bool fast, bool one, bool f64,
+                       void *wlo_p, void *w_p, hipStream_t st)
 {
+    if (fast && one && (f64 || a.rows.n_tiles < kAloneTiles)) {
+        a.fast = ram::FastPlan();
+        a.fast.alone = 1;
+        return hipSuccess;
+    }
     if (fast) {
         a.fast = ram::fast_plan_at(w_p, a.rows.n_tiles);
-        const hipError_t e = ram::launch_plan_fast(a, plan_order, a.fast, nodes, st);
-        if (!nodes) a.fast.jc = nullptr;
-        return e;
+        return ram::launch_plan_fast(a, plan_order, a.fast, true, st);
     }
     a.plan_wlo = (const int64_t *)wlo_p;
     a.plan_w = (const int32_t *)w_p;
@@ -465,9 +483,16 @@ std::vector<unsigned char> key_of(const T &...parts)
     return k;
 }
 
+// The copy of a state an odd number of in-place steps starts from.
+ram::CopyJob odd_steps_copy(const void *q, void *tmp, size_t bytes, int64_t n_steps)
+{
+    return n_steps % 2 != 0 ? ram::CopyJob{q, tmp, (int64_t)bytes} : ram::CopyJob();
+}
+
 // n_steps launches of the bulk-shift kernel (fused with the residual when
-// a.dv is set).  n_steps == 1 writes a.q_out; n_steps > 1 updates a.q_in in
-// place, ping-ponging with `tmp`.  Shared meshes take the specialised kernel
+// a.dv is set).  With a.q_out one step writes it; else a.q_in is updated in
+// place, ping-ponging with `tmp`, where an odd number of steps starts (the
+// caller has the state copied there).  Shared meshes take the specialised kernel
 // after planning the tiles' windows once; recon != 0 (shared meshes only)
 // selects its limited-reconstruction mode, whose window halo is that of order
 // 3 (PLM) or 5 (PPM).
@@ -488,7 +513,8 @@ ram_status launch_steps(ram_ctx *ctx, ram::StepArgs a, ram_dtype dtype,
         const int plan_order = recon == 0 ? order : (recon == RAM_RECON_PLM ? 3 : 5);
         const bool fast = (recon == 0 || dtype == RAM_F32) && allow_fast &&
                           use_fast_shape(ctx, a.rows.shared != 0, a.rows.n_cols, dtype, scan);
-        e = plan_shared(a, plan_order, fast, !f64 || n_steps > 1, mem + wlo_off, mem + w_off, ctx->stream);
+        e = plan_shared(a, plan_order, fast, recon == 0 && n_steps == 1, f64, mem + wlo_off,
+                        mem + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     } else if (rag_off >= 0) {
         a.rag = ram::rag_plan_at(mem + rag_off, a.rows.n_tiles);
@@ -508,16 +534,15 @@ ram_status launch_steps(ram_ctx *ctx, ram::StepArgs a, ram_dtype dtype,
     // the ping-pong loop, on stream st
     auto loop = [&](hipStream_t st) -> hipError_t {
         ram::StepArgs b = a;
-        void *q = const_cast<void *>(a.q_in);
-        void *cur = q, *oth = tmp;
+        void *cur = const_cast<void *>(a.q_in), *oth = tmp;
+        if (n_steps % 2 != 0) std::swap(cur, oth);
         for (int64_t k = 0; k < n_steps; ++k) {
             b.q_in = cur;
             b.q_out = oth;
             hipError_t r = one(b, st);
             if (r != hipSuccess) return r;
-            void *t = cur; cur = oth; oth = t;
+            std::swap(cur, oth);
         }
-        if (cur != q) return ram::launch_copy(cur, q, (int64_t)state_bytes, st);
         return hipSuccess;
     };
     const int64_t extra[4] = {(int64_t)dtype * 16 + (int64_t)scan + 256 * (int64_t)recon +
@@ -545,7 +570,7 @@ bool use_tile_adjoint(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype)
 ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtype,
                              const double *edges, const double *v0, double dt, int order,
                              const void *dv, void *dvbar, double *v0bar, bool nodes,
-                             ram::StepAdjArgs &a)
+                             ram::StepAdjArgs &a, const ram::CopyJob &copy = ram::CopyJob())
 {
     ram_status st;
     Carve cv;
@@ -557,7 +582,7 @@ ram_status plan_adjoint_fast(ram_ctx *ctx, const ram_layout *layout, ram_dtype d
     const size_t edge_off = cv.take(ram::adj_edge_bytes(nt, order, elem_size(dtype)));
     if ((st = ensure_scratch(ctx, cv.off)) != RAM_OK) return st;
     ram::StepArgs p;
-    if ((st = make_rows(ctx, layout, edges, rp, p.rows)) != RAM_OK) return st;
+    if ((st = make_rows(ctx, layout, edges, rp, p.rows, nullptr, copy)) != RAM_OK) return st;
     p.v0 = v0;
     p.dt = dt;
     const ram::FastPlan fp = ram::fast_plan_at((char *)ctx->scratch + rec_off, nt);
@@ -927,12 +952,14 @@ ram_status ram_step(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtype,
     if ((st = ensure_scratch(ctx, cv.off)) != RAM_OK) return st;
     ram::StepArgs a;
     std::memset(&a, 0, sizeof(a));        // the graph key compares raw bytes
-    if ((st = make_rows(ctx, layout, edges, rp, a.rows)) != RAM_OK) return st;
+    void *tmp = (char *)ctx->scratch + tmp_off;
+    if ((st = make_rows(ctx, layout, edges, rp, a.rows, nullptr,
+                        odd_steps_copy(q, tmp, state_bytes, n_steps))) != RAM_OK)
+        return st;
     a.q_in = q;
     a.v0 = v0;
     a.dv = dv;
     a.dt = dt;
-    void *tmp = (char *)ctx->scratch + tmp_off;
     if ((st = launch_steps(ctx, a, dtype, scan, order, n_steps, tmp, wlo_off, w_off,
                            state_bytes, items, 0, nullptr, true, rag_off)) != RAM_OK)
         return st;
@@ -1004,14 +1031,16 @@ ram_status ram_step_limited(ram_ctx *ctx, const ram_layout *layout, ram_dtype dt
         if ((st = ensure_scratch(ctx, cv.off)) != RAM_OK) return st;
         ram::StepArgs a;
         std::memset(&a, 0, sizeof(a));    // the graph key compares raw bytes
-        if ((st = make_rows(ctx, layout, edges, rp, a.rows)) != RAM_OK) return st;
+        void *tmp = (char *)ctx->scratch + tmp_off;
+        if ((st = make_rows(ctx, layout, edges, rp, a.rows, nullptr,
+                            odd_steps_copy(q, tmp, state_bytes, n_steps))) != RAM_OK)
+            return st;
         a.q_in = q;
         a.v0 = v0;
         a.dv = dv;
         a.dt = dt;
-        return launch_steps(ctx, a, dtype, RAM_SUM_DIRECT, 0, n_steps,
-                            (char *)ctx->scratch + tmp_off, wlo_off, w_off, state_bytes,
-                            ram::kItems, (int)recon);
+        return launch_steps(ctx, a, dtype, RAM_SUM_DIRECT, 0, n_steps, tmp, wlo_off, w_off,
+                            state_bytes, ram::kItems, (int)recon);
     }
     Carve cv;
     const size_t tmp_off = cv.take(state_bytes);
@@ -1110,7 +1139,7 @@ ram_status ram_step_limited_record(ram_ctx *ctx, const ram_layout *layout,
     hipError_t e;
     if (shared) {
         a.dv = dv;
-        e = plan_shared(a, recon == RAM_RECON_PLM ? 3 : 5, fast, true, (char *)ctx->scratch + wlo_off,
+        e = plan_shared(a, recon == RAM_RECON_PLM ? 3 : 5, fast, false, f64, (char *)ctx->scratch + wlo_off,
                         (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     }
@@ -1382,7 +1411,7 @@ ram_status setup_row_step(ram_ctx *ctx, const ram_layout *layout, ram_dtype dtyp
     rs.a.dt = dt;
     rs.shared = rs.a.rows.has_tab != 0 && rs.a.rows.n_cols > 0;
     if (rs.shared) {
-        hipError_t e = plan_shared(rs.a, plan_order, fast, true, (char *)ctx->scratch + wlo_off,
+        hipError_t e = plan_shared(rs.a, plan_order, fast, false, false, (char *)ctx->scratch + wlo_off,
                                    (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
         if (scan == RAM_SUM_DIRECT && recon == 0)
@@ -1695,7 +1724,7 @@ ram_status ram_step_record(ram_ctx *ctx, const ram_layout *layout,
     const bool shared = a.rows.has_tab != 0 && a.rows.n_cols > 0;
     hipError_t e;
     if (shared) {
-        e = plan_shared(a, order, fast, !f64 || n_steps > 1, (char *)ctx->scratch + wlo_off,
+        e = plan_shared(a, order, fast, n_steps == 1, f64, (char *)ctx->scratch + wlo_off,
                         (char *)ctx->scratch + w_off, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "window plan launch");
     }
@@ -1820,8 +1849,11 @@ ram_status ram_step_adjoint_steps(ram_ctx *ctx, const ram_layout *layout,
         // one plan for every step: the shift is the same at each
         ram::StepAdjArgs a;
         if ((st = plan_adjoint_fast(ctx, layout, dtype, edges, v0, dt, order, dv, dvbar_accum,
-                                    v0bar_accum, fast || n_steps > 1, a)) != RAM_OK)
+                                    v0bar_accum, fast || n_steps > 1, a,
+                                    odd_steps_copy(qbar, qbar_work, state_bytes, n_steps))) !=
+            RAM_OK)
             return st;
+        if (n_steps % 2 != 0) std::swap(cur, oth);
         for (int64_t k = n_steps - 1; k >= 0; --k) {
             a.q_fwd = at(q_traj, k);
             a.q_half = dv ? at(q_half, k) : nullptr;

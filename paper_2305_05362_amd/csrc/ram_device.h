@@ -467,6 +467,35 @@ __device__ inline RowShift row_shift(double s, double len, double invlen)
     return {s, kf * len, (kf + 1.0) * len, (kf - 1.0) * len, (int64_t)kf};
 }
 
+// Workgroup `block` of `blocks`' share of a copy: 16-byte words, four a thread
+// in flight, or 4-byte words where the arrays are not aligned to them (states
+// are 4- or 8-byte elements).
+__device__ inline void copy_part(const CopyJob &c, unsigned block, unsigned blocks)
+{
+    const int64_t stride = (int64_t)blocks * blockDim.x;
+    const int64_t i0 = (int64_t)block * blockDim.x + threadIdx.x;
+    if ((((uintptr_t)c.src | (uintptr_t)c.dst) & 15) != 0) {
+        const uint32_t *s = (const uint32_t *)c.src;
+        uint32_t *d = (uint32_t *)c.dst;
+        for (int64_t i = i0; i < c.bytes / 4; i += stride) d[i] = s[i];
+        return;
+    }
+    const int64_t nw = c.bytes / 16;
+    const uint4 *s = (const uint4 *)c.src;
+    uint4 *d = (uint4 *)c.dst;
+    int64_t i = i0;
+    for (; i + 3 * stride < nw; i += 4 * stride) {
+        const uint4 v0 = s[i], v1 = s[i + stride], v2 = s[i + 2 * stride], v3 = s[i + 3 * stride];
+        d[i] = v0;
+        d[i + stride] = v1;
+        d[i + 2 * stride] = v2;
+        d[i + 3 * stride] = v3;
+    }
+    for (; i < nw; i += stride) d[i] = s[i];
+    for (int64_t k = nw * 4 + i0; k < c.bytes / 4; k += stride)
+        ((uint32_t *)c.dst)[k] = ((const uint32_t *)c.src)[k];
+}
+
 // Node x (a coordinate of the row's own nodes) shifted by s: its position
 // wrapped into [x0, xN), the period it took beyond kf0 (0, 1, or -1 through
 // rounding) and its bucket.
@@ -485,6 +514,29 @@ __device__ inline NodePos node_pos(double xe, const RowShift &rs, double x0, dou
     const bool hi = v0 >= xN, lo = v0 < x0;
     const double v = hi ? vp : (lo ? vm : v0);
     const int d = hi ? 1 : (lo ? -1 : 0);
+    int b = (int)(v * bsc - bx0);
+    b = min(max(b, 0), nb - 1);
+    return {v, d, b};
+}
+
+// The same with the position not contracted: s and the periods are products,
+// and a compiler that fused one kernel's differences and not another's would
+// let a streaming call's plan and its steps, or calls of one step and of
+// several, disagree in the last place.
+__device__ inline double node_wrap(double xe, const RowShift &rs, double x0, double xN, int &d)
+{
+#pragma clang fp contract(off)
+    const double xs = xe - rs.s;
+    const double v0 = xs - rs.p0, vp = xs - rs.pp, vm = xs - rs.pm;
+    const bool hi = v0 >= xN, lo = v0 < x0;
+    d = hi ? 1 : (lo ? -1 : 0);
+    return hi ? vp : (lo ? vm : v0);
+}
+__device__ inline NodePos node_pos_same(double xe, const RowShift &rs, double x0, double xN,
+                                        double bsc, double bx0, int nb)
+{
+    int d;
+    const double v = node_wrap(xe, rs, x0, xN, d);
     int b = (int)(v * bsc - bx0);
     b = min(max(b, 0), nb - 1);
     return {v, d, b};
@@ -623,6 +675,7 @@ __device__ inline void uniform_dweights(CT th, double dxinv, double *dw)
 // node is wrapped into the row with its period count kx).  The plan uses it
 // for the two end nodes of every tile; the step kernel evaluates the same
 // arithmetic inline, in batches.
+template <bool SAME = false>
 __device__ inline int64_t node_locate(const double *x, int n, const MeshTab &tb,
                                       const RowShift &rs, int e, double &xt, int &cell)
 {
@@ -630,7 +683,8 @@ __device__ inline int64_t node_locate(const double *x, int n, const MeshTab &tb,
     if (e < 0) { e += n; kx = -1; }
     while (e >= n) { e -= n; kx += 1; }
     const double bsc = tb.scal[0], bx0 = tb.scal[2];
-    const NodePos np = node_pos(x[e], rs, x[0], x[n], bsc, bx0, tb.nb);
+    const NodePos np = SAME ? node_pos_same(x[e], rs, x[0], x[n], bsc, bx0, tb.nb)
+                            : node_pos(x[e], rs, x[0], x[n], bsc, bx0, tb.nb);
     int c = cell_from_bucket(tb.bucket[np.b], tb.bnext[np.b], np.xt);
     if (np.xt >= tb.bnext[np.b].y) c = cell_walk(x, n, c, np.xt);
     xt = np.xt;

@@ -186,7 +186,8 @@ struct FastPlan {
     int32_t *totals = nullptr;
     uint32_t *mask = nullptr;
     float *theta = nullptr;
-    int16_t *jc = nullptr;
+    int16_t *jc = nullptr;           // null: the tiles locate their nodes themselves
+    int64_t alone = 0;               // 1: no plan at all, each wave makes its tile's record
 };
 inline int64_t plan_groups(int64_t n_tiles) { return (n_tiles + kPlanGroup - 1) / kPlanGroup; }
 // The plan of n_tiles tiles in mem (each piece 256-byte aligned), and its size.
@@ -380,15 +381,35 @@ constexpr size_t kNoAllocBytes = size_t(16) << 20;
 hipError_t noalloc_setup(int device);
 void *noalloc_scratch(int device);
 
+// A copy of `bytes` that a call's first kernel (the mesh tables, the tile table)
+// makes beside its own work, in workgroups after its few: that kernel is bound by
+// latency and leaves HBM idle.  It is the state of a call with an odd number of
+// in-place steps, which then ends in place (134 MB copied back afterwards took 41
+// us; beside the tables of 16384 cells they take 46 instead of 12.  Shared
+// out over the plan's kernels too, whose own workgroups fill the chip, it took as
+// long again as by itself).
+struct CopyJob {
+    const void *src = nullptr;
+    void *dst = nullptr;
+    int64_t bytes = 0;
+    unsigned blocks(int threads) const
+    {
+        const int64_t per = 64 * (int64_t)threads;
+        return (unsigned)((bytes + per - 1) / per < 4096 ? (bytes + per - 1) / per : 4096);
+    }
+};
+
+
 hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
                              int64_t *tile_ptr, int32_t *tile_row,
-                             hipStream_t stream);
+                             hipStream_t stream, const CopyJob &copy = CopyJob());
 // Bytes of scratch the shared-mesh tables of an n-cell mesh need.
 size_t mesh_tab_bytes(int64_t n, int order);
 // Build the tables in `mem` (mesh_tab_bytes) and point `tab` at them, with the
 // uniform-run counts if `uniform`: one launch.
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
-                            MeshTab &tab, hipStream_t stream, bool uniform = false);
+                            MeshTab &tab, hipStream_t stream, bool uniform = false,
+                            const CopyJob &copy = CopyJob());
 // The step on per-row meshes (ram_step_rows.hip): tiles of rows_tile cells, or
 // of a multiple of it.
 hipError_t launch_step(const StepArgs &a, bool f64, int scan, int order,
@@ -402,6 +423,14 @@ hipError_t launch_plan(const StepArgs &a, int order, int64_t *wlo, int32_t *w,
                        hipStream_t stream);
 hipError_t launch_step_shared(const StepArgs &a, bool f64, int scan, int order,
                               int items, hipStream_t stream);
+// Batches of fewer tiles than this (8 Mi cells) run both kinds in one launch,
+// the others first.  The parallel branches cost about 5 us a step in fork and
+// join, one launch costs the uniform tiles their occupancy (they get the other
+// kind's registers), which only counts where they are bound by HBM: one launch
+// against branches 5.3 and 12.0 us a step at 64 x 2048 cells, 6.1 and 12.3 at
+// 512 x 2048, 16.2 and 19.8 at 1024 x 4096, 20.4 and 23.4 at 1000 x 6000, 48.6
+// and 45.2 at 2048 x 8192, 110 and 98 at 2048 x 16384.
+constexpr int64_t kTogether = 32768;
 // The FP32 direct-sum step on a shared mesh: plan the tiles into `plan`
 // (R.tile == kFastTile, tables with the uniform-run counts), then per step the
 // uniform-tile and the searching-tile kernels (a.fast set).  nodes: with the

@@ -450,8 +450,9 @@ __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *no
 
 template <int P, int B>
 __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTabW T,
-                                                 int uniform)
+                                                 int uniform, unsigned groups, CopyJob copy)
 {
+    if (blockIdx.x >= groups) return copy_part(copy, blockIdx.x - groups, gridDim.x - groups);
     __shared__ double sx[B];
     __shared__ double swin[B / 64][kPrepWin];
     const int t = (int)threadIdx.x;
@@ -498,8 +499,10 @@ constexpr int kFillRows = 8;
 __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
                                                      int64_t n_rows, int tile,
                                                      int64_t *tile_ptr,
-                                                     int32_t *tile_row)
+                                                     int32_t *tile_row, unsigned groups,
+                                                     CopyJob copy)
 {
+    if (blockIdx.x >= groups) return copy_part(copy, blockIdx.x - groups, gridDim.x - groups);
     __shared__ int64_t swt[16];
     const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6;
     const int64_t per = (n_rows + 1023) / 1024;
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
     __threadfence_block();
     __syncthreads();
     const int64_t wave = (int64_t)blockIdx.x * 16 + wv;
-    for (int64_t c = kFillRows * wave; c < n_rows; c += kFillRows * 16 * (int64_t)gridDim.x) {
+    for (int64_t c = kFillRows * wave; c < n_rows; c += kFillRows * 16 * (int64_t)groups) {
         // the rows' first tiles at once, then one row after the other
         const int64_t r = c + min(lane, kFillRows - 1);
         const int64_t base = tile_ptr[c];
@@ -552,15 +555,16 @@ __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
 
 template <int B>
 hipError_t mesh_prep_launch(const double *x, int64_t n, int order, const MeshTabW &w, bool uniform,
-                            hipStream_t st)
+                            const CopyJob &c, hipStream_t st)
 {
     const int64_t nc = (n + B - 1) / B;
-    const dim3 g((unsigned)(2 * nc + ((int64_t)w.nb + B - 1) / B + (uniform ? 1 : 0))), b(B);
+    const unsigned gp = (unsigned)(2 * nc + ((int64_t)w.nb + B - 1) / B + (uniform ? 1 : 0));
+    const dim3 g(gp + c.blocks(B)), b(B);
     const int u = uniform ? 1 : 0;
     switch (order) {
-    case 1: hipLaunchKernelGGL((k_mesh_prep<1, B>), g, b, 0, st, x, (int)n, w, u); break;
-    case 3: hipLaunchKernelGGL((k_mesh_prep<3, B>), g, b, 0, st, x, (int)n, w, u); break;
-    default: hipLaunchKernelGGL((k_mesh_prep<5, B>), g, b, 0, st, x, (int)n, w, u); break;
+    case 1: hipLaunchKernelGGL((k_mesh_prep<1, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
+    case 3: hipLaunchKernelGGL((k_mesh_prep<3, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
+    default: hipLaunchKernelGGL((k_mesh_prep<5, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
     }
     return hipGetLastError();
 }
@@ -581,7 +585,7 @@ size_t mesh_tab_bytes(int64_t n, int order)
 }
 
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
-                            MeshTab &tab, hipStream_t stream, bool uniform)
+                            MeshTab &tab, hipStream_t stream, bool uniform, const CopyJob &copy)
 {
     char *p = (char *)mem;
     MeshTabW w;
@@ -623,18 +627,18 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     tab.ppmf = w.ppmf;
     tab.nonu = uniform ? w.nonu : nullptr;
     tab.nonu_min = uniform ? w.nonu_min : nullptr;
-    if (n <= kPrepShort) return mesh_prep_launch<256>(x, n, order, w, uniform, stream);
-    return mesh_prep_launch<512>(x, n, order, w, uniform, stream);
+    if (n <= kPrepShort) return mesh_prep_launch<256>(x, n, order, w, uniform, copy, stream);
+    return mesh_prep_launch<512>(x, n, order, w, uniform, copy, stream);
 }
 
 hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
                              int64_t *tile_ptr, int32_t *tile_row,
-                             hipStream_t stream)
+                             hipStream_t stream, const CopyJob &copy)
 {
     // (more than 64 workgroups only repeat the scan)
     const unsigned g = (unsigned)std::min<int64_t>((n_rows + 16 * kFillRows - 1) / (16 * kFillRows), 64);
-    hipLaunchKernelGGL(k_tiles_prep, dim3(g), dim3(1024), 0, stream, row_ptr, n_rows, tile, tile_ptr,
-                       tile_row);
+    hipLaunchKernelGGL(k_tiles_prep, dim3(g + copy.blocks(1024)), dim3(1024), 0, stream, row_ptr,
+                       n_rows, tile, tile_ptr, tile_row, g, copy);
     return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "ram_device.h"
+#include "ram_wave.h"
 
 namespace ram {
 namespace dev {
@@ -134,15 +135,6 @@ __device__ __forceinline__ void node_dweights(const WT (&rth)[P + 1], const WT (
     for (int b = 0; b <= P; ++b) dw[b] = rrd[b] * (dpre[b] * suf[b] + pre[b] * dsuf[b]);
 }
 
-// A node's shifted coordinate wrapped into [x0, xN), as node_pos forms it
-// (the bucket, which a planned node does not need, left out).
-__device__ __forceinline__ double shifted_xt(double xe, const RowShift &rs, double x0, double xN)
-{
-    const double xs = xe - rs.s;
-    const double v0 = xs - rs.p0, vp = xs - rs.pp, vm = xs - rs.pm;
-    return v0 >= xN ? vp : (v0 < x0 ? vm : v0);
-}
-
 // The source cells of nodes e0 + min(t + 64 s, NE - 1) (s = 0 .. NS - 1, lane t)
 // of a row: the wrapped coordinate xt, the cell ce that holds it (bucket index,
 // Eq. condition_p) and the cells to add for the periods between them, kx, beside
@@ -161,7 +153,7 @@ __device__ __forceinline__ void locate_nodes(const double *x, int n, const MeshT
     double2 nx[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const NodePos np = node_pos(xt[s], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
+        const NodePos np = node_pos_same(xt[s], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
         ce[s] = tb.bucket[np.b];
         nx[s] = tb.bnext[np.b];
         xt[s] = np.xt;
@@ -195,21 +187,109 @@ __device__ __forceinline__ int window_index(int ce, int kx, const RowShift &rs, 
 // xt.  A uniform tile's node may lie in its window by counting and beside c by
 // the mesh's rounding, also across the period's seam (near: taken there; its
 // cells are far smaller than half the period).  A planned node's cell holds xt,
-// whatever the cell's size.
+// whatever the cell's size.  Not contracted, as node_wrap: theta is the same in
+// every kernel, whatever it goes on to.
 __device__ __forceinline__ double cell_theta(const double2 *stpd, int c, double xt, double len,
                                              bool near)
 {
+#pragma clang fp contract(off)
     const double2 g = stpd[c];
     double d = xt - g.x;
     if (near) d = d > 0.5 * len ? d - len : (d < -0.5 * len ? d + len : d);
     return d * g.y;
 }
 
+// The record of a tile (H halo cells a side): which path, its window, and for a
+// tile in a uniform run the stencil and the run's geometry.  Two neighbouring
+// lanes a tile, one for either end node (bucket index, Eq. condition_p), which
+// then look the tile's cells and its window up in one run count each (coarse
+// and fine); the even lane's record counts.
+//
+// uniform: the cells on both sides of the tile's nodes and its whole source
+// window lie in one uniform run of the mesh, and the window holds one source
+// cell per node plus the stencil, so node i0 - H + k sits in window cell LO + k
+// at the first node's theta (rows shorter than a full tile's window stay with
+// the other kernel, whose windows may wrap many times).
+template <int P>
+__device__ __forceinline__ FastTile plan_tile(const StepArgs &a, int tile, int H, int t)
+{
+    constexpr int LO = (P - 1) / 2;
+    const Rows &R = a.rows;
+    const MeshTab &tb = R.tab;
+    const int n = (int)R.n_cols;
+    const double *x = R.edges;
+    const TilePos p = tile_pos(tile, n, H);
+    const int i0 = p.i0, nd = p.nd;
+    const RowShift rs = row_shift(a.v0[p.row] * a.dt, x[n] - x[0], tb.scal[1]);
+    double xt;
+    int c;
+    const int64_t g = node_locate<true>(x, n, tb, rs, (t & 1) ? i0 + nd + H : i0 - H, xt, c);
+    const int64_t g0 = __shfl(g, t & ~1), g1 = __shfl(g, t | 1);
+    const int c0 = __shfl(c, t & ~1);
+    const int64_t wide = g1 - g0 + P;
+    const int64_t wlo = g0 - LO;
+    const bool fits = wide >= P && wide <= kFastWin;
+    int base = c0 - LO;
+    while (base < 0) base += n;
+    bool run = false;
+    if (fits && tb.nonu && wide == nd + 2 * H + P && n >= kFastTile + 2 * H + P) {
+        const int32_t *pre = (t & 1) ? tb.nonu_min : tb.nonu;
+        const int all = pre[n];
+        // cells of no run before cell i of the row and its neighbouring periods
+        auto upto = [&](int i) {
+            int k = 0;
+            if (i < 0) { i += n; k = -all; }
+            while (i >= n) { i -= n; k += all; }
+            return k + pre[i];
+        };
+        run = upto(i0 + nd + H + 1) == upto(i0 - H - 1) && upto(base + (int)wide) == upto(base);
+    }
+    const int other = __shfl_xor(run ? 1 : 0, 1);
+    const bool uni = run || other != 0;
+    FastTile ft;
+    ft.kind = uni ? kFastUniform : (fits ? kFastWindow : kFastDirect);
+    ft.w = fits ? (int)wide : -1;
+    ft.base = base;
+    ft.wlo_lo = (int32_t)(uint32_t)((uint64_t)wlo & 0xffffffffull);
+    ft.wlo_hi = (int32_t)((uint64_t)wlo >> 32);
+    for (int d = 0; d < 6; ++d) ft.cc[d] = 0.0f;
+    ft.dx = ft.hinv = ft.dxinv = 0.0f;
+    ft.pad[0] = ft.pad[1] = tile;
+    if (uni) {
+        double th;
+        {
+#pragma clang fp contract(off)
+            th = (xt - x[c]) * tb.dxinv[c];
+        }
+        double cc[P + 1];
+        uniform_stencil<double, P>(th, cc);
+        for (int d = 0; d <= P; ++d) ft.cc[d] = (float)cc[d];
+        ft.pad[1] = __float_as_int((float)th);
+        const float2 rr = tb.rrf[i0];
+        ft.dx = rr.x;
+        ft.hinv = rr.y;
+        ft.dxinv = tb.dxinvf[i0];
+    }
+    return ft;
+}
+
+// The same by a wave for its own tile, every field in scalar registers.
+template <int P>
+__device__ __forceinline__ FastTile plan_wave(const StepArgs &a, int tile, int H, int t)
+{
+    FastTile ft = plan_tile<P>(a, tile, H, t);
+    int32_t *w = (int32_t *)&ft;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(FastTile) / 4); ++k) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+    return ft;
+}
+
 // Each node's window index and FP64 position in its cell, for a tile whose
 // window fits: a uniform tile's by counting, another's from the call's node
 // plan, or located here where the call has none (one step: the plan's launch
 // costs more than the search: one FP64 step of a row of 256 cells 17 us
-// against 20, an FP32 step back over 24,000 searching tiles 131 against 157).  wcell: window index -> cell of the row.
+// against 20, an FP32 step back over 24,000 searching tiles 131 against 157).  wcell: window
+// index -> cell of the row.
 template <int P, int NS, bool PLAN, class Cell>
 __device__ __forceinline__ void tile_nodes(const FastPlan &pl, const FastTile &ft, const double *x,
                                            int n, const MeshTab &tb, const RowShift &rs, double x0,
@@ -236,7 +316,8 @@ __device__ __forceinline__ void tile_nodes(const FastPlan &pl, const FastTile &f
         const int m = min(t + u * 64, NE - 1);
         int e = e0 + m;
         e = e < 0 ? e + n : (e >= n ? e - n : e);
-        const double xt = shifted_xt(x[e], rs, x0, xN);
+        int dk;
+        const double xt = node_wrap(x[e], rs, x0, xN, dk);
         int j = jcp ? (int)jcp[m] : LO + m;
         int c = wcell(j);
         double th = cell_theta(tb.stpd, c, xt, len, uniform);

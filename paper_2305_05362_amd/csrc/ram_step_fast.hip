@@ -67,75 +67,20 @@ template <int S> constexpr size_t wave_lds_bytes()
 
 // The record of each tile: which path, its window, and for a uniform tile the
 // stencil and the run's geometry; and of each group which tiles are in no run.
-// A wave plans kPlanGroup tiles, two lanes each: one for either end node
-// (bucket index, Eq. condition_p), which then look the tile's cells and window
-// up in one run count each (coarse and fine).  About six dependent loads bound
-// it, whatever the size.
+// A wave plans kPlanGroup tiles, two lanes each (plan_tile).  About six
+// dependent loads bound it, whatever the size.
 template <int P>
 __global__ __launch_bounds__(kLanes) void k_plan_fast(StepArgs a, FastPlan pl)
 {
-    constexpr int LO = (P - 1) / 2;
     static_assert(2 * kPlanGroup == kLanes, "two lanes a tile");
     __shared__ FastTile srec[kPlanGroup];
-    const Rows &R = a.rows;
-    const MeshTab &tb = R.tab;
-    const int nt = (int)R.n_tiles;
-    const int n = (int)R.n_cols;
-    const int H = a.dv ? 2 : 0;
-    const double *x = R.edges;
-    const double len = x[n] - x[0];
+    const int nt = (int)a.rows.n_tiles;
     const int first = (int)blockIdx.x * kPlanGroup;
     const int t = (int)threadIdx.x;
     const bool valid = first + (t >> 1) < nt;
-    const int tile = min(first + (t >> 1), nt - 1);
-    const TilePos p = tile_pos(tile, n, H);
-    const int i0 = p.i0, nd = p.nd;
-    const RowShift rs = row_shift(a.v0[p.row] * a.dt, len, tb.scal[1]);
-    double xt;
-    int c;
-    const int64_t g = node_locate(x, n, tb, rs, (t & 1) ? i0 + nd + H : i0 - H, xt, c);
-    const int64_t g0 = __shfl(g, t & ~1), g1 = __shfl(g, t | 1);
-    const int64_t wide = g1 - g0 + P;
-    const int64_t wlo = g0 - LO;
-    const bool fits = wide >= P && wide <= kFastWin;
-    // uniform: the cells on both sides of the tile's nodes and its whole source
-    // window lie in one uniform run of the mesh, and the window holds one
-    // source cell per node plus the stencil, so node i0 - H + k sits in window
-    // cell LO + k at the first node's theta (rows shorter than a full tile's
-    // window stay with the other kernel, whose windows may wrap many times)
-    bool run = false;
-    if (fits && tb.nonu && wide == nd + 2 * H + P && n >= kFT + 2 * H + P) {
-        const int32_t *pre = (t & 1) ? tb.nonu_min : tb.nonu;
-        run = nonu_count(pre, n, i0 - H - 1, i0 + nd + H + 1) == 0 &&
-              nonu_count(pre, n, wlo, wlo + wide) == 0;
-    }
-    const int other = __shfl_xor(run ? 1 : 0, 1);
-    const bool uni = run || other != 0;
-    if ((t & 1) == 0) {
-        FastTile ft;
-        ft.kind = uni ? kFastUniform : (fits ? kFastWindow : kFastDirect);
-        ft.w = fits ? (int)wide : -1;
-        const int64_t kk = wlo >= 0 ? wlo / n : -((-wlo + n - 1) / n);
-        ft.base = (int)(wlo - kk * n);
-        ft.wlo_lo = (int32_t)(uint32_t)((uint64_t)wlo & 0xffffffffull);
-        ft.wlo_hi = (int32_t)((uint64_t)wlo >> 32);
-        for (int d = 0; d < 6; ++d) ft.cc[d] = 0.0f;
-        ft.dx = ft.hinv = ft.dxinv = 0.0f;
-        ft.pad[0] = ft.pad[1] = tile;
-        if (uni) {
-            const double th = (xt - x[c]) * tb.dxinv[c];
-            double cc[P + 1];
-            uniform_stencil<double, P>(th, cc);
-            for (int d = 0; d <= P; ++d) ft.cc[d] = (float)cc[d];
-            ft.pad[1] = __float_as_int((float)th);
-            const float2 rr = tb.rrf[i0];
-            ft.dx = rr.x;
-            ft.hinv = rr.y;
-            ft.dxinv = tb.dxinvf[i0];
-        }
-        srec[t >> 1] = ft;
-    }
-    uint64_t mo = __ballot(!uni && valid);           // bits 2 u and 2 u + 1: tile first + u
+    const FastTile ft = plan_tile<P>(a, min(first + (t >> 1), nt - 1), a.dv ? 2 : 0, t);
+    if ((t & 1) == 0) srec[t >> 1] = ft;
+    uint64_t mo = __ballot(ft.kind != kFastUniform && valid);           // bits 2 u and 2 u + 1: tile first + u
     mo &= 0x5555555555555555ull;
 #pragma unroll
     for (int d = 1; d < 32; d <<= 1) {               // even bits together
@@ -469,6 +414,37 @@ __global__ __launch_bounds__(kBlock) void k_plan_nodes(StepArgs a, int lists)
     }
 }
 
+// The window index and FP32 theta of a searching tile's nodes: the call's node
+// plan, or (PLAN false: one step) located here by the same arithmetic.
+template <int P, int NS, bool PLAN>
+__device__ __forceinline__ void node_data(const StepArgs &a, const FastTile &ft, int n, int row, int e0,
+                                          int NE, int t, float (&thv)[NS], int (&jv)[NS])
+{
+    if constexpr (PLAN) {
+        const float *thp = a.fast.theta + (int64_t)ft.pad[1] * kFastNodes;
+        const int16_t *jcp = a.fast.jc + (int64_t)ft.pad[1] * kFastNodes;
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int m = min(t + u * kLanes, kFastNodes - 1);
+            thv[u] = thp[m];
+            jv[u] = jcp[m];
+        }
+    } else {
+        const MeshTab &tb = a.rows.tab;
+        const double *x = a.rows.edges;
+        const double x0 = x[0], xN = x[n];
+        const RowShift rs = row_shift(a.v0[row] * a.dt, xN - x0, tb.scal[1]);
+        int ce[NS], kx[NS];
+        double xt[NS];
+        locate_nodes<NS>(x, n, tb, rs, x0, xN, e0, NE, t, ce, kx, xt);
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            thv[u] = (float)((xt[u] - x[ce[u]]) * tb.dxinv[ce[u]]);
+            jv[u] = window_index<P>(ce[u], kx[u], rs, n, ft);
+        }
+    }
+}
+
 // LDS window of the limited step's searching tiles, in cells: four arrays of
 // it (masses; averages, later the cubics' C; slopes or PLM kappa, later A;
 // PPM interface values).  Wider windows take the global-memory path.
@@ -561,7 +537,7 @@ __device__ __forceinline__ void lim_window_partials(const StepArgs &a, const Mes
 // window of at most kGenLimWin cells is tabulated in LDS (lim_window_partials,
 // su then holds kGenLimLds bytes); wider ones take the global-memory path,
 // each node's partial integral the limited profile of its cell (Section 3.1).
-template <int P, int H, bool VEC, int LR = 0>
+template <int P, int H, bool VEC, int LR = 0, bool PLAN = true>
 __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &ft,
                                              unsigned char *su, float *sell, short *sjc, int t)
 {
@@ -573,7 +549,6 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
     float *sw = (float *)su;                         // window masses
     int64_t *sg = (int64_t *)su;                     // direct path: node indices
     float *sq = (float *)su;                         // shifted state
-    const int k = ft.pad[1];                         // the tile's node data
     const MeshTab &tb = R.tab;
     const int n = (int)R.n_cols;
     const int c4 = 4 * t;
@@ -593,16 +568,9 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 
     if (windowed) {
         // ---- round trip 1: window masses, the nodes' window index and theta
-        const float *thp = a.fast.theta + (int64_t)k * kFastNodes;
-        const int16_t *jcp = a.fast.jc + (int64_t)k * kFastNodes;
         float thv[NS];
         int jv[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int m = min(t + s * kLanes, NE - 1);
-            thv[s] = thp[m];
-            jv[s] = jcp[m];
-        }
+        node_data<P, NS, PLAN>(a, ft, n, row, i0 - H, NE, t, thv, jv);
         if constexpr (LR != 0) {
             lim_window_partials<LR, NS>(a, tb, n, base, W, NE, qoff, t, thv, jv, (float *)su,
                                         sell, sjc);
@@ -689,7 +657,7 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
             int e = i0 - H + m;
             const int kx = e < 0 ? -n : (e >= n ? n : 0);
             e -= kx;
-            const NodePos np = node_pos(x[e], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
+            const NodePos np = node_pos_same(x[e], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
             const double2 nx = tb.bnext[np.b];
             int c = cell_from_bucket(tb.bucket[np.b], nx, np.xt);
             if (np.xt >= nx.y) c = cell_walk(x, n, c, np.xt);
@@ -795,7 +763,7 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 // and one word a load (general_tile), 80.
 // ---------------------------------------------------------------------------
 
-template <int P, int H, int S, bool VEC>
+template <int P, int H, int S, bool VEC, bool PLAN>
 __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &ft,
                                             unsigned char *su, float *sell, short *sjc, int t)
 {
@@ -827,16 +795,9 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     const bool full = VEC || (i0 >= 2 && i0 + kFT + 4 <= n);
 
     // ---- 1. node plan, window, faces ------------------------------------------
-    const float *thp = a.fast.theta + (int64_t)ft.pad[1] * kFastNodes;
-    const int16_t *jcp = a.fast.jc + (int64_t)ft.pad[1] * kFastNodes;
     float thv[NS];
     int jv[NS];
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int m = min(t + u * kLanes, kFastNodes - 1);
-        thv[u] = thp[m];
-        jv[u] = jcp[m];
-    }
+    node_data<P, NS, PLAN>(a, ft, n, tp.row, i0 - H, NC + 1, t, thv, jv);
     // window values and cell sizes (FP64 sizes for the FP64 prefix)
     constexpr bool kDx64 = S == kScanF64;
     float4 wq[NG], wd[NG];
@@ -1235,20 +1196,24 @@ template <int S> struct GenLds {
     __attribute__((aligned(16))) float sell[kWaves][WaveLds::nodes];
     __attribute__((aligned(16))) short sjc[kWaves][WaveLds::nodes];
 };
+template <int P, int H, bool VEC, int S, bool PLAN>
+__device__ __forceinline__ void other_tile(const StepArgs &a, const FastTile &r, GenLds<S> &lds, int t)
+{
+    const int wid = wave_id();
+    const int n = (int)a.rows.n_cols;
+    if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n && (VEC || n >= 8))
+        window_tile<P, H, S, VEC, PLAN>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+    else
+        general_tile<P, H, VEC, 0, PLAN>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+}
 // Wave `wave` of `waves`.
 template <int P, int H, bool VEC, int S>
 __device__ __forceinline__ void other_tiles(const StepArgs &a, GenLds<S> &lds, int wave, int waves)
 {
-    const int wid = wave_id();
-    const int n = (int)a.rows.n_cols;
-    const int t = (int)threadIdx.x % kLanes;
     const int total = a.fast.totals[1];
     for (int i = wave; i < total; i += waves) {
-        const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
-        if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n && (VEC || n >= 8))
-            window_tile<P, H, S, VEC>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
-        else
-            general_tile<P, H, VEC>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+        other_tile<P, H, VEC, S, true>(a, load_rec(a.fast.rec, load_index(a.fast.oid, i)), lds,
+                                       (int)threadIdx.x % kLanes);
         wave_sync();                                 // the next tile reuses the LDS
     }
 }
@@ -1278,11 +1243,33 @@ __global__ __launch_bounds__(kBlock) void k_step_both(StepArgs a, int others)
                             (int)threadIdx.x % kLanes);
 }
 
+// One step of a call that has no plan: a wave takes a tile in tile order, makes
+// its record and locates its nodes, by the arithmetic of the plan's kernels.  The
+// call is then the mesh tables (with the copy of the state beside them) and this:
+// 512 x 2048 cells on the refined disk 17 us (6.5 and 10.8), 26 with the plan's
+// two launches, the lists' one and the copy of the result back.  Latency bounds
+// it there, VALU issue on large searching batches.
+template <int P, int H, bool VEC, int S>
+__global__ __launch_bounds__(kBlock) void k_step_one(StepArgs a)
+{
+    __shared__ GenLds<S> lds;
+    const int i = spread8((int)blockIdx.x) * kWaves + wave_id();
+    if (i >= (int)a.rows.n_tiles) return;
+    const int t = (int)threadIdx.x % kLanes;
+    const FastTile r = plan_wave<P>(a, i, H, t);
+    if (r.kind == kFastUniform) uniform_tile<P, H, VEC>(a, r, (float *)lds.su[wave_id()], t);
+    else other_tile<P, H, VEC, S, false>(a, r, lds, t);
+}
+
 template <int P, int H, bool VEC, int S>
 hipError_t step_fast_kernels(const StepArgs &a, hipStream_t st)
 {
     const int64_t nt = a.rows.n_tiles;
     const dim3 g(uniform_grid(nt)), b(kBlock), gg(other_grid(nt));
+    if (a.fast.alone) {
+        hipLaunchKernelGGL((k_step_one<P, H, VEC, S>), dim3((g.x + 7) / 8 * 8), b, 0, st, a);
+        return hipGetLastError();
+    }
     if (nt < kTogether) {
         const unsigned others = uniform_grid(nt);    // a wave a tile: it may be any of them
         hipLaunchKernelGGL((k_step_both<P, H, VEC, S>), dim3(others + g.x), b, 0, st, a, (int)others);
@@ -1792,19 +1779,19 @@ hipError_t launch_plan_fast(const StepArgs &a, int order, const FastPlan &plan, 
     const int64_t nt = a.rows.n_tiles;
     const int lists = (int)((nt + kBlock - 1) / kBlock);
     const int64_t groups = ((nt + kNodeTiles - 1) / kNodeTiles + 7) / 8 * 8;
-    const dim3 gt((unsigned)plan_groups(nt)), bt(kLanes), gn((unsigned)(lists + groups)), bn(kBlock);
+    const dim3 g0((unsigned)plan_groups(nt)), b0(kLanes), g1((unsigned)(lists + groups)), b1(kBlock);
     switch (order) {
     case 1:
-        hipLaunchKernelGGL(k_plan_fast<1>, gt, bt, 0, stream, a, plan);
-        if (nodes) hipLaunchKernelGGL(k_plan_nodes<1>, gn, bn, 0, stream, b, lists);
+        hipLaunchKernelGGL(k_plan_fast<1>, g0, b0, 0, stream, a, plan);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<1>, g1, b1, 0, stream, b, lists);
         break;
     case 3:
-        hipLaunchKernelGGL(k_plan_fast<3>, gt, bt, 0, stream, a, plan);
-        if (nodes) hipLaunchKernelGGL(k_plan_nodes<3>, gn, bn, 0, stream, b, lists);
+        hipLaunchKernelGGL(k_plan_fast<3>, g0, b0, 0, stream, a, plan);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<3>, g1, b1, 0, stream, b, lists);
         break;
     default:
-        hipLaunchKernelGGL(k_plan_fast<5>, gt, bt, 0, stream, a, plan);
-        if (nodes) hipLaunchKernelGGL(k_plan_nodes<5>, gn, bn, 0, stream, b, lists);
+        hipLaunchKernelGGL(k_plan_fast<5>, g0, b0, 0, stream, a, plan);
+        if (nodes) hipLaunchKernelGGL(k_plan_nodes<5>, g1, b1, 0, stream, b, lists);
         break;
     }
     return hipGetLastError();

@@ -264,7 +264,7 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
             int e = i0 - H + m;
             const int kx = e < 0 ? -n : (e >= n ? n : 0);
             e -= kx;
-            const NodePos np = node_pos(x[e], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
+            const NodePos np = node_pos_same(x[e], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
             const double2 nx = tb.bnext[np.b];
             int c = cell_from_bucket(tb.bucket[np.b], nx, np.xt);
             if (np.xt >= nx.y) c = cell_walk(x, n, c, np.xt);
@@ -368,7 +368,8 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
 
 // Every tile in tile order, one a wave; LDS of one wave: the window (masses,
 // cumulative, or the direct tiles' node cells, then the shifted values), the
-// nodes' partial integrals and window indices.
+// nodes' partial integrals and window indices.  PLAN: the tiles' records and
+// node data planned, or (one step, as k_step_one) made here.
 template <int P, int H, int S, bool VEC, bool PLAN>
 __global__ __launch_bounds__(kBlock) void k_step64(StepArgs a)
 {
@@ -380,13 +381,13 @@ __global__ __launch_bounds__(kBlock) void k_step64(StepArgs a)
     const int wid = wave_id();
     const int i = (int)blockIdx.x * kWaves + wid;
     if (i >= (int)a.rows.n_tiles) return;
-    const FastTile r = load_rec(a.fast.rec, i);
-    tile64<P, H, S, VEC, PLAN>(a, r, sw_[wid], sp_[wid], sell_[wid], sjc_[wid],
-                         (int)threadIdx.x % kLanes);
+    const int t = (int)threadIdx.x % kLanes;
+    const FastTile r = PLAN ? load_rec(a.fast.rec, i) : plan_wave<P>(a, i, H, t);
+    tile64<P, H, S, VEC, PLAN>(a, r, sw_[wid], sp_[wid], sell_[wid], sjc_[wid], t);
 }
 
 template <int P, int S, bool PLAN>
-hipError_t step64_ps(const StepArgs &a, bool vec, hipStream_t st)
+hipError_t step64_pm(const StepArgs &a, bool vec, hipStream_t st)
 {
     const dim3 g((unsigned)((a.rows.n_tiles + kWaves - 1) / kWaves)), b(kBlock);
     if (a.dv) {
@@ -399,17 +400,20 @@ hipError_t step64_ps(const StepArgs &a, bool vec, hipStream_t st)
     return hipGetLastError();
 }
 
+template <int P, int S>
+hipError_t step64_ps(const StepArgs &a, bool vec, hipStream_t st)
+{
+    return a.fast.alone ? step64_pm<P, S, false>(a, vec, st) : step64_pm<P, S, true>(a, vec, st);
+}
+
 template <int P>
 hipError_t step64_p(const StepArgs &a, int scan, hipStream_t st)
 {
     // 16-byte pairs: rows of a multiple of four cells, 16-byte aligned states
     const bool vec = (a.rows.n_cols % 4) == 0 && ((uintptr_t)a.q_out % 16) == 0 &&
                      ((uintptr_t)a.q_in % 16) == 0 && (!a.dv || ((uintptr_t)a.dv % 16) == 0);
-    const bool plan = a.fast.jc != nullptr;
-    if (scan == kSumDirect)
-        return plan ? step64_ps<P, kSumDirect, true>(a, vec, st)
-                    : step64_ps<P, kSumDirect, false>(a, vec, st);
-    return plan ? step64_ps<P, kScanF64, true>(a, vec, st) : step64_ps<P, kScanF64, false>(a, vec, st);
+    return scan == kSumDirect ? step64_ps<P, kSumDirect>(a, vec, st)
+                              : step64_ps<P, kScanF64>(a, vec, st);
 }
 
 } // namespace

@@ -75,14 +75,6 @@ __device__ inline int load_index(const int32_t *p, int i)
 // second and one takes 66, 57 and 58 us a step (whole rounds of the chip's
 // waves are left over); on the 2048 x 16384 disk, one tile in six searching,
 // 1995, 1990 and 2032 us for twenty steps (waves without a tile).
-// Batches of fewer tiles than this (8 Mi cells) run both kinds in one launch,
-// the others first.  The parallel branches cost about 5 us a step in fork and
-// join, one launch costs the uniform tiles their occupancy (they get the other
-// kind's registers), which only counts where they are bound by HBM: one launch
-// against branches 5.3 and 12.0 us a step at 64 x 2048 cells, 6.1 and 12.3 at
-// 512 x 2048, 16.2 and 19.8 at 1024 x 4096, 20.4 and 23.4 at 1000 x 6000, 48.6
-// and 45.2 at 2048 x 8192, 110 and 98 at 2048 x 16384.
-constexpr int64_t kTogether = 32768;
 inline unsigned uniform_grid(int64_t n_tiles) { return (unsigned)((n_tiles + kWaves - 1) / kWaves); }
 inline unsigned other_grid(int64_t n_tiles)
 {
