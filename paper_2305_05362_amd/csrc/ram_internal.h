@@ -36,6 +36,8 @@ enum ScanMode { kScanF64 = 0, kScanTwoSum = 1, kScanF32 = 2, kSumDirect = 3 };
 // Leer slope, PPM with the interface values and constraints of App. A.
 enum Recon { kReconPLM = 1, kReconPPM = 2 };
 
+constexpr int kMeshPad = 16;
+
 // Mesh-only tables for a mesh shared by every row (built once per call by
 // launch_mesh_prep): cell sizes and their reciprocals, reciprocal centre gaps
 // for the slopes, reciprocal Lagrange denominators of every source cell's
@@ -45,8 +47,8 @@ struct MeshTab {
     const double *dx = nullptr;
     const double *dxinv = nullptr;
     const double *hinv = nullptr;     // 1 / (centre_{j+1} - centre_j), periodic
-    const float *dxf = nullptr;
-    const float *dxinvf = nullptr;
+    const float *dxf = nullptr;       // dxf, dxinvf and rrf: kMeshPad cells past the row's
+    const float *dxinvf = nullptr;    // end too (the next period's), for loads of several
     const float *hinvf = nullptr;
     const int32_t *bucket = nullptr;  // largest j with x_j <= x0 + b L / nb
     const double2 *bnext = nullptr;   // per bucket: the next two nodes (or +inf)

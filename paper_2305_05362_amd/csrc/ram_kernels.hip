@@ -162,10 +162,13 @@ __device__ __forceinline__ void prep_sizes(const double *x, int n, int j, const 
     T.dx[j] = dx;
     T.dxinv[j] = dxi;
     T.hinv[j] = hi;
-    T.dxf[j] = (float)dx;
-    T.dxinvf[j] = (float)dxi;
+    // (the FP32 sizes, their reciprocals and (dx, 1/gap) go on past the row's end)
+    for (int k = j; k < n + kMeshPad; k += n) {
+        T.dxf[k] = (float)dx;
+        T.dxinvf[k] = (float)dxi;
+        T.rrf[k] = make_float2((float)dx, (float)hi);
+    }
     T.hinvf[j] = (float)hi;
-    T.rrf[j] = make_float2((float)dx, (float)hi);
     T.rrd[j] = make_double2(dx, hi);
     const PpmW pw = ppm_weights(x[wrap_small(j - 1, n) + 1] - x[wrap_small(j - 1, n)], dx,
                                 x[wrap_small(j + 1, n) + 1] - x[wrap_small(j + 1, n)],
@@ -592,8 +595,8 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     w.dx = (double *)p; p += al256(8 * n);
     w.dxinv = (double *)p; p += al256(8 * n);
     w.hinv = (double *)p; p += al256(8 * n);
-    w.dxf = (float *)p; p += al256(4 * n);
-    w.dxinvf = (float *)p; p += al256(4 * n);
+    w.dxf = (float *)p; p += al256(4 * (n + kMeshPad));
+    w.dxinvf = (float *)p; p += al256(4 * (n + kMeshPad));
     w.hinvf = (float *)p; p += al256(4 * n);
     w.bucket = (int32_t *)p; p += al256(4 * 4 * n);
     w.nb = (int32_t)(4 * n);
@@ -601,7 +604,7 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     w.scal = (double *)p; p += al256(24);
     w.crf = (CellRec<float> *)p; p += al256(sizeof(CellRec<float>) * n);
     w.crd = (CellRec<double> *)p; p += al256(sizeof(CellRec<double>) * n);
-    w.rrf = (float2 *)p; p += al256(8 * n);
+    w.rrf = (float2 *)p; p += al256(8 * (n + kMeshPad));
     w.stp = (float *)p; p += al256(36 * n);
     w.rrd = (double2 *)p; p += al256(16 * n);
     w.stpd = (double2 *)p; p += al256(96 * n);

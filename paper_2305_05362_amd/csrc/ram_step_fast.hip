@@ -142,6 +142,9 @@ __device__ __forceinline__ void residual4(const float *s, const float *dvv, floa
 struct f4u {
     float __attribute__((ext_vector_type(4), aligned(4))) v;
 };
+struct f2u {
+    float __attribute__((ext_vector_type(2), aligned(4))) v;
+};
 
 // Residual velocity of faces i0+4l .. i0+4l+4 of a row (face n is face 0);
 // lanes past the tile read its last faces again (every load issued, no
@@ -757,10 +760,16 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 // from the 16-byte boundary at or below its start (LDS index j + off for
 // window cell j), so that its groups go in whole, also across the row's end.
 // Other rows read the groups from the window's start (off = 0) at a word's
-// alignment, and cell by cell where a window or a tile's neighbourhood crosses
-// the row's end; their cumulative differences are always summed directly.  At
-// 1000 x 6001 cells, all searching, 58 us a step; with one node's 64-byte record
-// and one word a load (general_tile), 80.
+// alignment, the group that straddles the row's end cell by cell beside them, and
+// the mesh's sizes past its end from their continuation there; their cumulative
+// differences are always summed directly.  At 1000 x 6001 cells, all searching,
+// 39 us a step (38 at 6000); 58 with the whole window cell by cell, a round of
+// loads after the other, where it crosses the row's end, and 80 with one node's
+// 64-byte record and one word a load (general_tile).
+//
+// Latency bounds it (four round trips), so registers count: at five waves a SIMD
+// (96 registers at order 5) 1000 x 6000 cells take 36 us a step, at four 40; at
+// six the rows not a multiple of four spill (70 against 58).
 // ---------------------------------------------------------------------------
 
 template <int P, int H, int S, bool VEC, bool PLAN>
@@ -790,9 +799,10 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     const int a0 = VEC ? base & ~3 : base, off = base - a0;
     const int gl = (W + off - 1) >> 2;               // last window group
     float *sw = (float *)su;                         // window mass j at sw[j + off]
-    // the window's groups / the tile with its neighbourhood lie in the row
-    const bool groups = VEC || base + 4 * (gl + 1) <= n;
-    const bool full = VEC || (i0 >= 2 && i0 + kFT + 4 <= n);
+    // rows not a multiple of four: the one group that straddles the row's end
+    // (its cells are put in one by one afterwards)
+    const int left = n - base, split = left & ~3;
+    const bool cross = !VEC && split != left && split <= 4 * gl;
 
     // ---- 1. node plan, window, faces ------------------------------------------
     float thv[NS];
@@ -810,19 +820,23 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
             return make_float4(v.x, v.y, v.z, v.w);
         }
     };
-    if (groups) {
 #pragma unroll
-        for (int u = 0; u < NG; ++u) {
-            int c = a0 + 4 * min(t + u * kLanes, gl);
-            c = VEC && c >= n ? c - n : c;
-            wq[u] = load4(q, c);
-            if constexpr (kDx64) {
-                wd2[u][0] = ld_at<double2>(tb.dx, 8u * (uint32_t)c);
-                wd2[u][1] = ld_at<double2>(tb.dx, 8u * (uint32_t)c + 16u);
-            } else {
-                wd[u] = load4(tb.dxf, c);
-            }
+    for (int u = 0; u < NG; ++u) {
+        int c = a0 + 4 * min(t + u * kLanes, gl);
+        c = c >= n ? c - n : c;
+        wq[u] = load4(q, VEC ? c : min(c, n - 4));
+        if constexpr (kDx64) {
+            wd2[u][0] = ld_at<double2>(tb.dx, 8u * (uint32_t)c);
+            wd2[u][1] = ld_at<double2>(tb.dx, 8u * (uint32_t)c + 16u);
+        } else {
+            wd[u] = load4(tb.dxf, c);
         }
+    }
+    float over = 0.0f;
+    if (cross) {
+        int c = base + split + (t & 3);
+        c = c >= n ? c - n : c;
+        over = q[c] * tb.dxf[c];
     }
     float dvv[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (H != 0) load_faces<VEC>((const float *)a.dv + qoff, n, i0, nd, c4, dvv);
@@ -837,21 +851,7 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
         }
     }
     A *sp = (A *)su;                                 // prefix modes: cumulative at j + off
-    if (!groups) {
-        // the window crosses the row's end
-        for (int r0 = 0; r0 < W; r0 += 4 * kLanes) {
-            float vq[4], vd[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                int c = base + min(r0 + t + u * kLanes, W - 1);
-                c = c >= n ? c - n : c;
-                vq[u] = q[c];
-                vd[u] = tb.dxf[c];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sw[min(r0 + t + u * kLanes, W - 1)] = vq[u] * vd[u];
-        }
-    } else if constexpr (kDirect) {
+    if constexpr (kDirect) {
 #pragma unroll
         for (int u = 0; u < NG; ++u) {
             const int g = min(t + u * kLanes, gl);
@@ -862,11 +862,12 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
         for (int u = NG; u * kLanes <= gl; ++u) {
             const int g = min(t + u * kLanes, gl);
             int c = a0 + 4 * g;
-            c = VEC && c >= n ? c - n : c;
-            const float4 vq = load4(q, c);
+            c = c >= n ? c - n : c;
+            const float4 vq = load4(q, VEC ? c : min(c, n - 4));
             const float4 vd = load4(tb.dxf, c);
             *(float4 *)(sw + 4 * g) = make_float4(vq.x * vd.x, vq.y * vd.y, vq.z * vd.z, vq.w * vd.w);
         }
+        if (cross && t < 4) sw[split + t] = over;
     } else {
         A carry = AC::zero();
         auto masses = [&](const float4 &vq, const float4 &vd, const double2 (&v2)[2], M (&m)[4]) {
@@ -1001,29 +1002,31 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     float2 rr[8];
     float dxi[8];
     if constexpr (H != 0) {
-        if (full) {
-            const int cb = i0 + (VEC ? min(c4, nd - 4) : c4) - 2;
-            auto wr = [&](int c) { return VEC ? (c < 0 ? c + n : (c >= n ? c - n : c)) : c; };
+        const int cb = i0 + min(c4, (nd - 1) & ~3) - 2;
+        auto wr = [&](int c) { return VEC ? (c < 0 ? c + n : (c >= n ? c - n : c)) : c; };
 #pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
-                const float4 r2 = ld_at<float4>(tb.rrf, 8u * (uint32_t)wr(cb + 2 * pr));
-                rr[2 * pr] = make_float2(r2.x, r2.y);
-                rr[2 * pr + 1] = make_float2(r2.z, r2.w);
-            }
-            const float2 d0 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb));
-            const float4 d1 = ld_at<float4>(tb.dxinvf, 4u * (uint32_t)wr(cb + 2));
-            const float2 d2 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb + 6));
-            dxi[0] = d0.x; dxi[1] = d0.y;
-            dxi[2] = d1.x; dxi[3] = d1.y; dxi[4] = d1.z; dxi[5] = d1.w;
-            dxi[6] = d2.x; dxi[7] = d2.y;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const int cg = wrap1f(i0 + min(c4, nd - 1) - 2 + c, n);
-                rr[c] = tb.rrf[cg];
-                dxi[c] = tb.dxinvf[cg];
-            }
+        for (int pr = VEC ? 0 : 1; pr < 4; ++pr) {
+            const float4 r2 = ld_at<float4>(tb.rrf, 8u * (uint32_t)wr(cb + 2 * pr));
+            rr[2 * pr] = make_float2(r2.x, r2.y);
+            rr[2 * pr + 1] = make_float2(r2.z, r2.w);
         }
+        float2 d0;
+        if constexpr (VEC) {
+            d0 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb));
+        } else {
+            // (the first pair may lie before the row's start, at any word there)
+            const int c0 = cb < 0 ? cb + n : cb;
+            const auto r0 = ld_at<f4u>(tb.rrf, 8u * (uint32_t)c0).v;
+            const auto i0 = ld_at<f2u>(tb.dxinvf, 4u * (uint32_t)c0).v;
+            rr[0] = make_float2(r0.x, r0.y);
+            rr[1] = make_float2(r0.z, r0.w);
+            d0 = make_float2(i0.x, i0.y);
+        }
+        const float4 d1 = ld_at<float4>(tb.dxinvf, 4u * (uint32_t)wr(cb + 2));
+        const float2 d2 = ld_at<float2>(tb.dxinvf, 4u * (uint32_t)wr(cb + 6));
+        dxi[0] = d0.x; dxi[1] = d0.y;
+        dxi[2] = d1.x; dxi[3] = d1.y; dxi[4] = d1.z; dxi[5] = d1.w;
+        dxi[6] = d2.x; dxi[7] = d2.y;
     }
     wave_sync();                                     // the window is dead
     float *sm = (float *)su;                         // shifted masses, index ci
@@ -1219,7 +1222,7 @@ __device__ __forceinline__ void other_tiles(const StepArgs &a, GenLds<S> &lds, i
 }
 
 template <int P, int H, bool VEC, int S>
-__global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
+__global__ __launch_bounds__(kBlock, 5) void k_step_gen(StepArgs a)
 {
     __shared__ GenLds<S> lds;
     other_tiles<P, H, VEC, S>(a, lds, (int)blockIdx.x * kWaves + wave_id(), (int)gridDim.x * kWaves);
@@ -1228,7 +1231,7 @@ __global__ __launch_bounds__(kBlock) void k_step_gen(StepArgs a)
 // Both kinds in one launch: the first `others` workgroups the other tiles, the
 // rest the uniform ones.
 template <int P, int H, bool VEC, int S>
-__global__ __launch_bounds__(kBlock) void k_step_both(StepArgs a, int others)
+__global__ __launch_bounds__(kBlock, 5) void k_step_both(StepArgs a, int others)
 {
     __shared__ GenLds<S> lds;
     const int wid = wave_id();
@@ -1250,7 +1253,7 @@ __global__ __launch_bounds__(kBlock) void k_step_both(StepArgs a, int others)
 // two launches, the lists' one and the copy of the result back.  Latency bounds
 // it there, VALU issue on large searching batches.
 template <int P, int H, bool VEC, int S>
-__global__ __launch_bounds__(kBlock) void k_step_one(StepArgs a)
+__global__ __launch_bounds__(kBlock, 5) void k_step_one(StepArgs a)
 {
     __shared__ GenLds<S> lds;
     const int i = spread8((int)blockIdx.x) * kWaves + wave_id();
