@@ -126,16 +126,24 @@ __global__ __launch_bounds__(kRadBlock) void k_radial(RadialArgs a)
 hipError_t launch_radial(const RadialArgs &a, bool f64, hipStream_t stream)
 {
     if (a.n_rows <= 0 || a.n_cols <= 0) return hipSuccess;
+    // strips of 8 rows; of 4 where those leave fewer than kRadFill workgroups (the
+    // chain of a strip's loads and arithmetic is then all there is to hide).  A
+    // 2D split step (FP32, PPM) with strips of 16, 8 and 4: 45.7, 44.2 and 44.5
+    // us at 1024 x 4096 cells (2048 strips of 8), 20.5, 18.3 and 17.7 at 256 x
+    // 1024 (128), 19.7, 17.4 and 16.4 at 100 x 333 (26).
+    constexpr unsigned kRadFill = 1024;
     const unsigned gx = (unsigned)((a.n_cols + kRadBlock - 1) / kRadBlock);
+    const unsigned g8 = (unsigned)((a.n_rows + 7) / 8), g4 = (unsigned)((a.n_rows + 3) / 4);
     const dim3 b(kRadBlock);
-    if (f64) {
-        constexpr int S = 8;
-        const dim3 g(gx, (unsigned)((a.n_rows + S - 1) / S));
-        hipLaunchKernelGGL((k_radial<double, S>), g, b, 0, stream, a);
+    if (!f64 && g8 > 65535) {                        // (the grid's second dimension)
+        hipLaunchKernelGGL((k_radial<float, 16>), dim3(gx, (unsigned)((a.n_rows + 15) / 16)), b, 0,
+                           stream, a);
+    } else if ((int64_t)gx * g8 >= kRadFill) {
+        if (f64) hipLaunchKernelGGL((k_radial<double, 8>), dim3(gx, g8), b, 0, stream, a);
+        else hipLaunchKernelGGL((k_radial<float, 8>), dim3(gx, g8), b, 0, stream, a);
     } else {
-        constexpr int S = 16;
-        const dim3 g(gx, (unsigned)((a.n_rows + S - 1) / S));
-        hipLaunchKernelGGL((k_radial<float, S>), g, b, 0, stream, a);
+        if (f64) hipLaunchKernelGGL((k_radial<double, 4>), dim3(gx, g4), b, 0, stream, a);
+        else hipLaunchKernelGGL((k_radial<float, 4>), dim3(gx, g4), b, 0, stream, a);
     }
     return hipGetLastError();
 }
