@@ -790,7 +790,7 @@ constexpr size_t kLimStage = 4 * (kLimTab + 16);    // the window's averages
 template <int R, int NS>
 __device__ __forceinline__ void lim_tab_rows(const StepAdjArgs &a, const MeshTab &tb, int n,
                                              int base, int off, int W, int NE, int nd,
-                                             int64_t wl, int t, int (&kv)[NS],
+                                             int t, int (&kv)[NS],
                                              int (&kn)[NS], double (&thv)[NS],
                                              double (&hv)[NS], const float *sqw,
                                              const double *smb, double *tI, float4 *tD,
@@ -941,7 +941,7 @@ __device__ __forceinline__ void lim_tab_rows(const StepAdjArgs &a, const MeshTab
             // destination m's whole cells: window cells k .. kn - 1
             const double mb = smb[m + 1];
             for (int j = k; j < kne; ++j) {
-                const double dxj = j == k ? h : tb.dx[wrapi(wl + j, n)];
+                const double dxj = j == k ? h : tb.dx[cell(j)];
                 atomicAdd(&cacc[j], mb * dxj);
             }
         }
@@ -1077,12 +1077,15 @@ __device__ __forceinline__ void lim_tile(const StepAdjArgs &a, const FastTile &f
     double vp = 0.0;
     float *edge = (float *)a.edge + (int64_t)tile * (2 * P);
     if (windowed) {
-        lim_tab_rows<R>(a, tb, n, base, off, W, NE, nd, wl, t, kv, kn, thv, hv, sqw, smb,
+        lim_tab_rows<R>(a, tb, n, base, off, W, NE, nd, t, kv, kn, thv, hv, sqw, smb,
                         (double *)su, (float4 *)(su + kLimTabI),
                         (double *)(su + kLimTabI + kLimTabD), vp);
         const double *cacc = (const double *)(su + kLimTabI + kLimTabD);
-        for (int j = t; j < W; j += kLanes)
-            put_cell<P>(qbi, edge, wrapi(wl + j, n), j, W, (float)cacc[j]);
+        for (int j = t; j < W; j += kLanes) {
+            // (from base: a remainder of the extended index a cell took 3 us of 90)
+            const int c = base + j;
+            put_cell<P>(qbi, edge, c >= n ? c - n : c, j, W, (float)cacc[j]);
+        }
         if constexpr (V0) {
             vp = wave_sum(vp);
             if (t == 0) a.v0part[tile] = a.dt * vp;

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void k_adjf_edges(StepAdjArgs a, unsigned boun
     if (tile >= a.rows.n_tiles) return;
     const int n = (int)a.rows.n_cols;
     const int tpr = (n + kFastTile - 1) / kFastTile;
-    const int64_t row = tile / tpr;
+    const int64_t row = (int)tile / tpr;             // (fewer than 2^31 tiles)
     const int k0 = (int)(tile - row * tpr);
     // window start of the row's k-th tile, any k (k mod tpr, one period per wrap)
     auto start = [&](int k, int64_t &id) {
@@ -212,8 +212,10 @@ __global__ __launch_bounds__(256) void k_adjf_edges(StepAdjArgs a, unsigned boun
         TQ v[P];
 #pragma unroll
         for (int k = 0; k < P; ++k) v[k] = ((TQ)0 + e0[k]) + ep[P + k];
+        // (the record's start in the row: a0's remainder)
+        const int b0 = a.fast.rec[id0].base;
 #pragma unroll
-        for (int k = 0; k < P; ++k) qbi[wrapi(a0 + k, n)] = v[k];
+        for (int k = 0; k < P; ++k) qbi[b0 + k >= n ? b0 + k - n : b0 + k] = v[k];
         return;
     }
     const int64_t mend = min(a0 + P, a1);
