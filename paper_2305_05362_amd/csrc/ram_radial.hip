@@ -126,24 +126,27 @@ __global__ __launch_bounds__(kRadBlock) void k_radial(RadialArgs a)
 hipError_t launch_radial(const RadialArgs &a, bool f64, hipStream_t stream)
 {
     if (a.n_rows <= 0 || a.n_cols <= 0) return hipSuccess;
-    // strips of 8 rows; of 4 where those leave fewer than kRadFill workgroups (the
-    // chain of a strip's loads and arithmetic is then all there is to hide).  A
-    // 2D split step (FP32, PPM) with strips of 16, 8 and 4: 45.7, 44.2 and 44.5
-    // us at 1024 x 4096 cells (2048 strips of 8), 20.5, 18.3 and 17.7 at 256 x
-    // 1024 (128), 19.7, 17.4 and 16.4 at 100 x 333 (26).
-    constexpr unsigned kRadFill = 1024;
+    // strips of 8 rows: of 4 where those leave fewer than kRadFew workgroups (the
+    // chain of a strip's loads and arithmetic is then all there is to hide), in
+    // FP32 of 16 from kRadMany up (four halo rows in twenty instead of in twelve,
+    // and waves enough).  A 2D split step (FP32, PPM) with strips of 16, 8 and 4:
+    // 63.6, 64.0 and 64.5 us at 2048 x 4096 cells (4096 strips of 8), 45.7, 44.2
+    // and 44.5 at 1024 x 4096 (2048), 20.5, 18.3 and 17.7 at 256 x 1024 (128),
+    // 19.7, 17.4 and 16.4 at 100 x 333 (26); the radial kernel alone at 2048 x
+    // 16384 with strips of 16 and 8: 66.9 and 78.
+    constexpr unsigned kRadFew = 1024, kRadMany = 4096;
     const unsigned gx = (unsigned)((a.n_cols + kRadBlock - 1) / kRadBlock);
-    const unsigned g8 = (unsigned)((a.n_rows + 7) / 8), g4 = (unsigned)((a.n_rows + 3) / 4);
     const dim3 b(kRadBlock);
-    if (!f64 && g8 > 65535) {                        // (the grid's second dimension)
-        hipLaunchKernelGGL((k_radial<float, 16>), dim3(gx, (unsigned)((a.n_rows + 15) / 16)), b, 0,
-                           stream, a);
-    } else if ((int64_t)gx * g8 >= kRadFill) {
-        if (f64) hipLaunchKernelGGL((k_radial<double, 8>), dim3(gx, g8), b, 0, stream, a);
-        else hipLaunchKernelGGL((k_radial<float, 8>), dim3(gx, g8), b, 0, stream, a);
+    auto grid = [&](int rows) { return dim3(gx, (unsigned)((a.n_rows + rows - 1) / rows)); };
+    const int64_t strips = (int64_t)gx * grid(8).y;
+    if (!f64 && strips >= kRadMany) {
+        hipLaunchKernelGGL((k_radial<float, 16>), grid(16), b, 0, stream, a);
+    } else if (strips >= kRadFew) {
+        if (f64) hipLaunchKernelGGL((k_radial<double, 8>), grid(8), b, 0, stream, a);
+        else hipLaunchKernelGGL((k_radial<float, 8>), grid(8), b, 0, stream, a);
     } else {
-        if (f64) hipLaunchKernelGGL((k_radial<double, 4>), dim3(gx, g4), b, 0, stream, a);
-        else hipLaunchKernelGGL((k_radial<float, 4>), dim3(gx, g4), b, 0, stream, a);
+        if (f64) hipLaunchKernelGGL((k_radial<double, 4>), grid(4), b, 0, stream, a);
+        else hipLaunchKernelGGL((k_radial<float, 4>), grid(4), b, 0, stream, a);
     }
     return hipGetLastError();
 }

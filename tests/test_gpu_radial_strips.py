@@ -1,6 +1,7 @@
 """The radial step around its strips' lengths: rows that end a strip of four or
-eight rows, one less and one more, and on either side of the number of strips
-where they go from four rows to eight (1024 workgroups).  Against the oracle at
+eight rows, one less and one more, and on either side of the numbers of strips
+where they go from four rows to eight (1024 workgroups) and, in FP32, on to
+sixteen (4096).  Against the oracle at
 the radial tests' bars (FP64 1e-12 relative L1, FP32 1e-6 on FP32 inputs).
 """
 import numpy as np
@@ -17,7 +18,7 @@ DEV = torch.device("cuda:0")
 
 
 @pytest.mark.parametrize("dtype,bar", [(torch.float64, 1e-12), (torch.float32, 1e-6)])
-@pytest.mark.parametrize("n_r", [3, 4, 5, 8, 9, 8183, 8184, 8185, 8192, 8193])
+@pytest.mark.parametrize("n_r", [3, 4, 5, 8, 9, 8183, 8184, 8185, 8192, 8193, 32760, 32761])
 def test_strips(n_r, dtype, bar):
     wl = W.small_polar(n_r, 64, 2)
     u = W.radial_velocity(wl, 2, amp=0.05)
