@@ -344,7 +344,13 @@ bool use_fast_adjoint(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype,
 int step_tile_of(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype, ram_scan scan,
                  int items, bool fused)
 {
-    if (!L->edges_shared) return ram::rows_tile(fused);
+    // per-row meshes: batches of few waves, which latency bounds, take tiles of
+    // half the size, whose chain is shorter (FP32 two-sum with the residual: 8.2
+    // against 11.4 us a step at 16 rows of up to 200 cells, 8.8 and 12.7 at 300 of
+    // up to 600, 11.6 and 15.3 at 2000 of up to 300, 364,000 cells; FP64 sums 15.5
+    // and 17.0 there, 15.0 and 15.0 at 545,000 cells, 40.9 and 37.9 at 2.1 M)
+    constexpr int64_t kRowsFew = 384 * 1024;
+    if (!L->edges_shared) return ram::rows_tile(fused, layout_cells(L) <= kRowsFew ? 2 : 4);
     return use_fast(ctx, L, dtype, scan) ? ram::kFastTile : ram::step_tile_for(items, fused);
 }
 

@@ -242,9 +242,9 @@ static_assert(sizeof(RagTile) == 64, "one record a cache line half");
 // Cells of a per-row streaming tile: 255, so that its 256 shifted nodes fill
 // four slots of a wave (no residual halo on this path).
 constexpr int kRagTile = 255;
-// Cells per tile of the other per-row step kernel (k_rows): a wave's 256
-// shifted nodes, less the residual's two-cell halo a side.
-inline int rows_tile(bool fused) { return 255 - (fused ? 4 : 0); }
+// Cells per tile of the other per-row step kernel (k_rows): a wave's shifted
+// nodes, four slots of them (or two), less the residual's two-cell halo a side.
+inline int rows_tile(bool fused, int slots = 4) { return 64 * slots - 1 - (fused ? 4 : 0); }
 struct RagPlan {
     RagTile *rec = nullptr;
     float *wa = nullptr;       // order 5: four weights a slot, 3: two, 1: one

@@ -82,11 +82,14 @@ __device__ __forceinline__ void wrap_node(double xe, double s, double x0, double
 // wrapped coordinate.  The wave locates the two end nodes in the row, then
 // every node among the window's in LDS: the row is read once, in whole lines,
 // where a binary search a node reads thirteen lines a lane.
-template <int P, int NS>
+// `issue` is called once the window is known (its loads are on their way during
+// the search).
+template <int P, int NS, class Issue>
 __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, double x0, double xN,
                                             double len, double invlen, int NE, int t, int cap,
                                             const double (&xe)[NS], const int (&kx)[NS], double *xs,
-                                            RowsWindow &win, double (&xh)[NS], int (&j)[NS])
+                                            RowsWindow &win, double (&xh)[NS], int (&j)[NS],
+                                            Issue issue)
 {
     constexpr int LO = (P - 1) / 2;
     int64_t k[NS];
@@ -108,12 +111,14 @@ __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, do
     const double xa = __shfl(xh[0], 0), xb = __shfl(xl, last);
     int la, hb;
     find_two(x, n, xa, xb, t, la, hb);
-    const int64_t ga = (int64_t)la + __shfl(k[0], 0) * (int64_t)n;
+    const int64_t ka = __shfl(k[0], 0);
+    const int64_t ga = (int64_t)la + ka * (int64_t)n;
     const int64_t gb = (int64_t)(hb - 1) + __shfl(kl, last) * (int64_t)n;
     const int64_t wide = gb - ga + P;
     win.wlo = ga - LO;
-    win.k0 = win.wlo >= 0 ? win.wlo / n : -((-win.wlo + n - 1) / n);
-    win.base = (int)(win.wlo - win.k0 * n);
+    // (rows have more than LO cells)
+    win.k0 = ka - (la < LO ? 1 : 0);
+    win.base = la < LO ? la - LO + n : la - LO;
     win.seam = n - win.base;
     win.seam2 = win.seam + n;
     win.w = 0;
@@ -121,6 +126,7 @@ __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, do
     const int W = (int)wide;
     win.w = W;
     for (int i = t; i <= W; i += kLanes) xs[i] = x[win.at(i, n)];
+    issue();
     wave_sync();
     // the last window node at or below each shifted node, within its period
     int pos[NS], end[NS];

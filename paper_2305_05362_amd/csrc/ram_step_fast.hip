@@ -1490,7 +1490,7 @@ __global__ __launch_bounds__(kBlock) void k_plan_rag(StepArgs a, RagPlan pl)
     double xh[NS];
     int j[NS];
     const bool all = n >= P + 1 && rows_locate<P, NS>(x, n, s, x0, xN, len, invlen, NE, t, kFastWin, xe,
-                                                      kx, xs, win, xh, j);
+                                                      kx, xs, win, xh, j, [] {});
     const int64_t slot = tile * kFastNodes;
     if (all) {
 #pragma unroll

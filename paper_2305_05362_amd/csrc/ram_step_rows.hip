@@ -30,7 +30,8 @@
 // 300.  1024 rows of 64 .. 4096 cells, FP32, two-sum, with the residual: 44 us
 // (26 of them VALU issue); with 1019-cell tiles a workgroup (27 KB of LDS,
 // seven barriers, two lanes searching the row for the window while the others
-// wait) 74.  Five waves a SIMD spill (51 us).
+// wait) 74.  Five waves a SIMD spill (51 us).  Small batches take two node slots
+// a lane instead of four: the chain of one wave is what they cost.
 #include "ram_rows.h"
 
 #include <type_traits>
@@ -59,7 +60,8 @@ template <typename TQ, int S> struct RowsLds {
 };
 
 // sub: wave tiles a table tile holds (R.tile = sub times the wave's tile).
-template <typename TQ, int P, int S, int H>
+// NS: node slots a lane.
+template <typename TQ, int P, int S, int H, int NS>
 __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
 {
     using AC = Acc<S>;
@@ -70,7 +72,6 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
     using CT = TQ;
     constexpr int LO = (P - 1) / 2;
     constexpr bool kLocal = S == kScanF64;           // sums of the FP64 masses between
-    constexpr int NS = 4;                            // node slots a lane
     constexpr int NDT = kLanes * NS - 1 - 2 * H;     // destination cells
     constexpr int NQ = 5;                            // window slots loaded ahead
     __shared__ __attribute__((aligned(16))) unsigned char su_[kWaves][L::bytes];
@@ -79,11 +80,12 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
     const int t = (int)threadIdx.x % kLanes;
     const int64_t wave = (int64_t)blockIdx.x * kWaves + wid;
     const Rows &R = a.rows;
-    if (wave / sub >= R.n_tiles) return;
+    const int64_t tile = sub == 1 ? wave : wave / sub;
+    if (tile >= R.n_tiles) return;
     Tile ti;
-    if (!get_tile(R, wave / sub, ti)) return;
+    if (!get_tile(R, tile, ti)) return;
     const int n = ti.n;
-    const int i0 = ti.i0 + (int)(wave % sub) * NDT;
+    const int i0 = ti.i0 + (int)(wave - tile * sub) * NDT;
     if (n < P + 1 || i0 >= n) return;
     const int nd = min(NDT, n - i0);
     const int NC = nd + 2 * H;                       // shifted cells
@@ -115,21 +117,30 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
         xe[u] = x[e];
         xr[u] = x[e + 1];
     }
+    CT v[NS];                                        // face velocity of the cell's left face
+    if constexpr (H != 0) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) v[u] = (CT)((const TQ *)a.dv + ti.qoff)[cell[u]];
+    }
 
     // ---- (A) -------------------------------------------------------------------
     RowsWindow win;
     double xh[NS];
     int j[NS];
-    const bool windowed = rows_locate<P, NS>(x, n, s, x0, xN, len, invlen, NE, t, kRowsCap, xe, kx, xs,
-                                             win, xh, j);
+    TQ qv[NQ];
+    const bool windowed = rows_locate<P, NS>(
+        x, n, s, x0, xN, len, invlen, NE, t, kRowsCap, xe, kx, xs, win, xh, j, [&] {
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) qv[u] = q[win.at(min(t + u * kLanes, win.w - 1), n)];
+        });
     CT qs[NS];
+    double x2[NS];                                   // the residual's: the next cell's right node
+    if constexpr (H != 0) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) x2[u] = x[cell[u] + 2 <= n ? cell[u] + 2 : 1];
+    }
     if (windowed) {
         const int W = win.w;
-        TQ qv[NQ];
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-            qv[u] = q[win.at(min(t + u * kLanes, W - 1), n)];
-        }
         TQ w[NS][P + 1];
         if (win.seam > W) {
 #pragma unroll
@@ -232,13 +243,6 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
         constexpr int NL = kLanes * NS;
         CT *sq = (CT *)su, *sdx = sq + NL, *shv = sdx + NL, *sdi = shv + NL, *sf = sdi + NL;
         TQ *qmid = a.q_mid ? (TQ *)a.q_mid + ti.qoff : nullptr;
-        double x2[NS];
-        CT v[NS];                                    // face velocity of the cell's left face
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            x2[u] = x[cell[u] + 2 <= n ? cell[u] + 2 : 1];
-            v[u] = (CT)((const TQ *)a.dv + ti.qoff)[cell[u]];
-        }
         wave_sync();
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
@@ -282,16 +286,23 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
     }
 }
 
+template <typename TQ, int P, int S, int NS>
+hipError_t rows_ns(const StepArgs &a, int sub, hipStream_t st)
+{
+    const dim3 g((unsigned)((a.rows.n_tiles * sub + kWaves - 1) / kWaves)), b(kBlock);
+    if (a.dv) hipLaunchKernelGGL((k_rows<TQ, P, S, 2, NS>), g, b, 0, st, a, sub);
+    else hipLaunchKernelGGL((k_rows<TQ, P, S, 0, NS>), g, b, 0, st, a, sub);
+    return hipGetLastError();
+}
+
 template <typename TQ, int P, int S>
 hipError_t rows_h(const StepArgs &a, hipStream_t st)
 {
-    const int tile = rows_tile(a.dv != nullptr);
+    const bool fused = a.dv != nullptr;
+    if (a.rows.tile == rows_tile(fused, 2)) return rows_ns<TQ, P, S, 2>(a, 1, st);
+    const int tile = rows_tile(fused);
     if (a.rows.tile % tile != 0) return hipErrorInvalidValue;
-    const int sub = a.rows.tile / tile;
-    const dim3 g((unsigned)((a.rows.n_tiles * sub + kWaves - 1) / kWaves)), b(kBlock);
-    if (a.dv) hipLaunchKernelGGL((k_rows<TQ, P, S, 2>), g, b, 0, st, a, sub);
-    else hipLaunchKernelGGL((k_rows<TQ, P, S, 0>), g, b, 0, st, a, sub);
-    return hipGetLastError();
+    return rows_ns<TQ, P, S, 4>(a, a.rows.tile / tile, st);
 }
 
 template <int P>

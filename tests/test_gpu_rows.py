@@ -64,6 +64,21 @@ def test_row_lengths(order, with_dv, dtype, scan):
         assert_parity(got, ref, 1e-6, 2e-4)
 
 
+# the same in a batch of more than 393,216 cells (four node slots a lane, where a
+# small batch has two) and around the two slots' tiles (123 and 127 cells)
+@pytest.mark.parametrize("with_dv", [True, False])
+@pytest.mark.parametrize("dtype,scan", [(torch.float64, R.RAM_SCAN_F64), (torch.float32, R.RAM_SCAN_F64),
+                                        (torch.float32, R.RAM_SCAN_F32_TWOSUM)])
+@pytest.mark.parametrize("more", [0, 290])
+def test_both_tile_sizes(more, with_dv, dtype, scan):
+    lens = LENS + [122, 123, 124, 126, 127, 128, 246, 247, 381, 382] + [1400] * more
+    got, ref = run(batch(lens, 3, with_dv, 11), dtype, scan)
+    if dtype == torch.float64:
+        assert_parity(got, ref, 1e-12, CELL_F64)
+    else:
+        assert_parity(got, ref, 1e-6, 2e-4)
+
+
 @pytest.mark.parametrize("with_dv", [True, False])
 @pytest.mark.parametrize("steps", [1, 4])
 def test_windows_beyond_the_lds(with_dv, steps):
