@@ -100,7 +100,7 @@ TRAFFIC_FILE_LSADJ = os.path.join(ROOT, "profiles", "k_ladj_step_f32_ppm_polar20
 LSADJ_KERNEL = "k_ladj<2, true, true>"
 # the FP64 plain path's kernel (window prefix sums, fused residual)
 TRAFFIC_FILE_F64 = os.path.join(ROOT, "profiles", "k_step64_f64_prefix_polar2048x16384_traffic.md")
-F64_KERNEL = "k_step64<5, 2, 0, true>"
+F64_KERNEL = "k_step64<5, 2, 0, true, true>"
 
 
 def _finite(v):
@@ -543,7 +543,7 @@ def main():
                           "meshes, shift only, order 5", "steps": k3,
               "kernel": ("FP32: k_step_rag (255-cell wave tiles; each call plans every "
                          "node's weights and window cell once, k_plan_rag, inside the "
-                         "timed call); FP64: k_step"),
+                         "timed call); FP64: k_rows"),
               "f32_twosum": round(wl3.n_cells * k3 / t3 / 1e9, 3),
               "f32_plain_prefix": round(wl3.n_cells * k3 / t3p / 1e9, 3),
               "f32_direct": round(wl3.n_cells * k3 / t3s / 1e9, 3),

@@ -36,7 +36,7 @@ HIPCC_FLAGS = [
 # sources of the shared-mesh step kernel (the one the traffic counters cover)
 STEP_KERNEL_SOURCES = ["ram_step_shared.hip", "ram_device.h", "ram_internal.h"]
 # sources of each kernel family whose counters are committed
-FAST_SOURCES = ["ram_step_fast.hip", "ram_rows.h", "ram_wave.h", "ram_device.h", "ram_internal.h"]
+FAST_SOURCES = ["ram_step_fast.hip", "ram_rows.h", "ram_node64.h", "ram_wave.h", "ram_device.h", "ram_internal.h"]
 ADJ_FAST_SOURCES = ["ram_adjoint_fast.hip", "ram_adjoint_wave.h", "ram_adjoint_dev.h", "ram_wave.h", "ram_device.h",
                     "ram_internal.h"]
 KERNEL_SOURCES = {"k_step_sh": STEP_KERNEL_SOURCES,

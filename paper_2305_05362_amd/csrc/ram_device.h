@@ -406,7 +406,7 @@ __device__ inline double harmonic2(double a, double b)
     return 2.0 * a * b / (a + b);
 }
 
-// Direct path of k_step (tiles whose source window does not fit in LDS):
+// Direct path of the step kernels (tiles whose source window does not fit in LDS):
 // partial integrals from global memory, FP64.
 template <typename TQ, int P>
 __device__ __attribute__((noinline)) double direct_partial(

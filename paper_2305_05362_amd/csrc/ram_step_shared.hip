@@ -1,6 +1,6 @@
 // ram_step_shared.hip -- the RAM step on rows that share one mesh (gfx950).
 //
-// Same computation as k_step (bulk shift of Section 3, Steps 1-3, then the
+// Same computation as k_rows (bulk shift of Section 3, Steps 1-3, then the
 // residual upwind step), specialised for a mesh shared by every row, which is
 // the polar-disk layout: rows are radii, the shared mesh is the azimuthal one.
 // What the specialisation buys:
