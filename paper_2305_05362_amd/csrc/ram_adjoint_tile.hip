@@ -10,8 +10,8 @@
 //   * the residual's transpose runs in the state's type on four consecutive
 //     cells a lane, its six arrays passed through the wave's LDS in two turns
 //     of three;
-//   * no stencil shortcut on uniform runs (a run counts as uniform far above
-//     FP64 rounding): every node's weights are formed in the state's type from
+//   * no stencil shortcut on uniform runs in FP64 (a run counts as uniform far
+//     above FP64 rounding): every node's weights are formed in the state's type from
 //     its FP64 position and its source cell's stencil, and a uniform tile only
 //     saves the node plan;
 //   * the shift's transpose follows the forward sum term by term.  Cell i's
@@ -216,6 +216,68 @@ __device__ __forceinline__ void tile_stencil(const MeshTab &tb, int n, int c, bo
     node_stencil<P>(tb.stp, n, c, rth, rrd);
 }
 
+// (2), (3) of an FP32 tile in a uniform run, as the streaming adjoint takes it:
+// node e in window cell LO + e at one theta, so the shift's transpose is a fixed
+// stencil on Mbar' and v0bar one on Q^n (coefficients and sums in FP64).  1024 x
+// 4001 uniform cells: 37 us a step of eight; with every node's FP32 weights 55 (as
+// long as the general adjoint took), and their rounding in every gradient.
+template <int P, bool V0>
+__device__ __forceinline__ void tile_uniform(const StepAdjArgs &a, const FastTile &ft,
+                                             const TilePos &p, int n, double *sw, const double *smb,
+                                             int t)
+{
+    constexpr int NW = (kFT + P + kLanes - 1) / kLanes;       // window slots
+    const int nd = p.nd, W = ft.w, base = ft.base;
+    const int64_t qoff = (int64_t)p.row * n;
+    const double th = (double)__int_as_float(ft.pad[1]);
+    const double dx = TabT<double>::dx(a.rows.tab)[base];
+    float *qbi = (float *)a.qbar_in + qoff;
+    float *edge = (float *)a.edge + (int64_t)ft.pad[0] * (2 * P);
+    float wq[NW];
+    if constexpr (V0) {
+#pragma unroll
+        for (int u = 0; u < NW; ++u) {
+            const int c = base + min(t + u * kLanes, W - 1);
+            wq[u] = ((const float *)a.q_fwd + qoff)[c >= n ? c - n : c];
+        }
+    }
+    double cs[P + 1];
+    uniform_stencil<double, P>(th, cs);
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        const int j = t + u * kLanes;
+        if (j >= W) continue;
+        double acc = 0.0;
+#pragma unroll
+        for (int d = 0; d <= P; ++d) {
+            const int i = j - d;
+            if (i >= 0 && i < nd) acc += cs[d] * smb[1 + i];
+        }
+        const int c = base + j;
+        put_cell<P, float>(qbi, edge, c >= n ? c - n : c, j, W, (float)(acc * dx));
+    }
+    if constexpr (V0) {
+#pragma unroll
+        for (int u = 0; u < NW; ++u) sw[min(t + u * kLanes, W - 1)] = (double)wq[u];
+        double dw[P + 1], gd[P + 2];
+        uniform_dweights<double, P>(th, 1.0, dw);
+        outward_sums<double, P>(dw, gd);
+        wave_sync();
+        double vp = 0.0;
+#pragma unroll
+        for (int u = 0; u < kFT / kLanes; ++u) {
+            const int i = t + u * kLanes;
+            if (i >= nd) continue;
+            double dq = 0.0;
+#pragma unroll
+            for (int d = 0; d <= P; ++d) dq += (gd[d] - gd[d + 1]) * sw[i + d];
+            vp -= smb[1 + i] * dq;
+        }
+        vp = wave_sum(vp);
+        if (t == 0) a.v0part[ft.pad[0]] = a.dt * vp;
+    }
+}
+
 // (2), (3) of a tile whose window fits in LDS.
 template <typename TQ, int P, bool V0>
 __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile &ft, const TilePos &p,
@@ -381,7 +443,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_adj_tile(StepAdjArgs a)
     const FastTile ft = load_rec(a.fast.rec, i);
     const TilePos p = tile_pos(i, n, 0);
     tile_residual<TQ, RES>(a, p, n, su[wid], smb_[wid], t);
-    if (ft.kind != kFastDirect)
+    if (sizeof(TQ) == 4 && ft.kind == kFastUniform) {
+        if constexpr (sizeof(TQ) == 4) tile_uniform<P, V0>(a, ft, p, n, su[wid], smb_[wid], t);
+    } else if (ft.kind != kFastDirect)
         tile_shift<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], sjc_[wid], t);
     else
         direct_shift<TQ, P, V0>(a, ft, su[wid], smb_[wid], t);
