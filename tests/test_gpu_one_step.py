@@ -132,3 +132,25 @@ def test_odd_steps_elsewhere(k):
     R.ram_step_adjoint_steps(rows, traj, half, dv, bar, torch.empty_like(bar), v0, dt, 5, k)
     torch.cuda.synchronize()
     assert torch.equal(bar, g)
+
+
+# FP32 batches of 65,536 tiles have a plan, one tile fewer none
+@pytest.mark.parametrize("kind", ["runs", "stretched"])
+def test_both_sides_of_the_plan(kind):
+    n, few = 264, 32767                              # two tiles a row
+    rng = np.random.default_rng(8)
+    e = edges(kind, n)
+    out = []
+    q0 = torch.as_tensor(1.0 + 0.2 * rng.standard_normal((few + 1, n)), dtype=torch.float32, device=DEV)
+    dv0 = torch.as_tensor(rng.uniform(-1, 1, (few + 1, n)), dtype=torch.float32, device=DEV)
+    dt = 0.4 * float(np.diff(e).min())
+    v0 = dev(rng.uniform(-0.7, 0.7, few + 1) / dt)
+    for r in (few, few + 1):
+        wl = W.Workload("plan", r, n, np.arange(r + 1) * n, e, True, np.zeros((0,)), None,
+                        np.zeros(r), dt, 5, 1)
+        q = q0[:r].reshape(-1).clone()
+        R.ram_step(R.Rows.from_workload(wl, DEV), q, v0[:r].contiguous(),
+                   dv0[:r].reshape(-1).contiguous(), dt, 5, 1, R.RAM_SUM_DIRECT)
+        torch.cuda.synchronize()
+        out.append(q.view(r, n))
+    assert torch.equal(out[0], out[1][:few])
