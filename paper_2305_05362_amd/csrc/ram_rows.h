@@ -163,19 +163,14 @@ __device__ __forceinline__ float rows_recip(double h, float)
     const double r = __builtin_amdgcn_rcp(h);
     return (float)fma(fma(-h, r, 1.0), r, r);
 }
-__device__ __forceinline__ double rows_div(double a, double b) { return a / b; }
-__device__ __forceinline__ float rows_div(float a, float b)
-{
-    const float r = __builtin_amdgcn_rcpf(b);
-    const float q = a * r;
-    return fmaf(fmaf(-b, q, a), r, q);
-}
 
 // Lagrange weights of the node at xh in window cell j, in WT: of every stencil
 // node but the cell's own left one (w[LO] is not formed: no partial integral
 // uses it), from the nodes' positions in units of the cell's size, the cell's
 // own edges at 0 and 1.  The products of the node's distances from the front
-// and from the back, each weight's denominator from the pairwise distances.
+// and from the back, each weight's denominator from the pairwise distances; a
+// denominator past the type's largest number (in FP32 at order 5 from neighbours
+// 2e7 times the cell) leaves a weight of 0.
 // SEAM: the window crosses the row's end.
 template <typename WT, int P, bool SEAM>
 __device__ __forceinline__ void rows_weights(const double *xs, const RowsWindow &win, double len,
@@ -233,7 +228,7 @@ __device__ __forceinline__ void rows_weights(const double *xs, const RowsWindow 
     for (int b = 0; b <= P; ++b) {
         if (b == LO) continue;
         const WT num = (P - b) % 2 ? -(pre[b] * suf[b]) : pre[b] * suf[b];
-        w[b] = rows_div(num, den[b]);
+        w[b] = num / den[b];
     }
     w[LO] = (WT)0;
 }

@@ -1,0 +1,37 @@
+"""The per-row step's divisions, where an approximate quotient shows.
+
+* Cells of 1 beside cells of 2^20 and 2^40 of the unit: at order 5 denominators of
+  their stencils' outer weights pass FP32's largest number, and the weight is 0,
+  as the quotient by infinity is.  (Every node is an integer, and no two nodes of
+  a stencil round to one in FP32.)  With no shift every node lies on a mesh node,
+  every weight is a product with 0, and a step returns the state to the rounding
+  of (Q dx) / dx: two roundings, 2^-23 relative, doubled.  One step in each mode,
+  four in one call (planned) by direct sums: prefix sums of such masses cancel.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_05362_amd import _lib as R
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def dev(a, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a).reshape(-1), dtype=dtype, device=DEV)
+
+
+@pytest.mark.parametrize("scan,steps", [(R.RAM_SCAN_F64, 1), (R.RAM_SCAN_F32_TWOSUM, 1), (R.RAM_SCAN_F32, 1),
+                                        (R.RAM_SUM_DIRECT, 4)])
+def test_weights_past_the_largest_number(scan, steps):
+    w = np.exp2([0, 0, 0, 0, 20, 40, 40, 40, 40, 40, 40, 30, 20, 10])
+    n, nr = len(w), 3
+    e = np.concatenate([[0.0], np.cumsum(w)])
+    rows = R.Rows(dev(np.tile(e, nr)), nr, n, None, False)
+    q0 = np.random.default_rng(4).uniform(0.5, 2.0, n * nr).astype(np.float32)
+    q = dev(q0, torch.float32)
+    R.ram_step(rows, q, dev(np.zeros(nr)), None, 1.0, 5, steps, scan)
+    got = q.cpu().numpy()
+    assert np.isfinite(got).all(), np.argwhere(~np.isfinite(got)).ravel()
+    assert np.max(np.abs(got / q0 - 1.0)) <= steps * 2.0 ** -22
