@@ -155,15 +155,6 @@ __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, do
     return __all(ok ? 1 : 0) != 0;
 }
 
-// 1 / h in the type of the weights: FP64 by division; FP32 by the hardware's
-// FP64 reciprocal and one Newton step (its error far below FP32 rounding).
-__device__ __forceinline__ double rows_recip(double h, double) { return 1.0 / h; }
-__device__ __forceinline__ float rows_recip(double h, float)
-{
-    const double r = __builtin_amdgcn_rcp(h);
-    return (float)fma(fma(-h, r, 1.0), r, r);
-}
-
 // Lagrange weights of the node at xh in window cell j, in WT: of every stencil
 // node but the cell's own left one (w[LO] is not formed: no partial integral
 // uses it), from the nodes' positions in units of the cell's size, the cell's
@@ -185,21 +176,11 @@ __device__ __forceinline__ void rows_weights(const double *xs, const RowsWindow 
         return SEAM ? d + (double)(win.period(jb) - kc) * len : d;
     };
     WT th[P + 1], tt;
-    if constexpr (sizeof(WT) == 4) {
-        const double h = dist(LO + 1);
-        const double r = __builtin_amdgcn_rcp(h);
-        const double inv = fma(fma(-h, r, 1.0), r, r);
+    const double inv = 1.0 / dist(LO + 1);
 #pragma unroll
-        for (int b = 0; b <= P; ++b)
-            if (b != LO && b != LO + 1) th[b] = (WT)(dist(b) * inv);
-        tt = (WT)((xh - xc) * inv);
-    } else {
-        const double inv = 1.0 / dist(LO + 1);
-#pragma unroll
-        for (int b = 0; b <= P; ++b)
-            if (b != LO && b != LO + 1) th[b] = dist(b) * inv;
-        tt = (xh - xc) * inv;
-    }
+    for (int b = 0; b <= P; ++b)
+        if (b != LO && b != LO + 1) th[b] = (WT)(dist(b) * inv);
+    tt = (WT)((xh - xc) * inv);
     th[LO] = (WT)0;
     th[LO + 1] = (WT)1;
     WT d[P + 1], pre[P + 1], suf[P + 1];

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
             } else {
                 whole = jb - ja == 1 ? (D)sm[ja] : (D)AC::diff(sp[jb], sp[ja]);
             }
-            qs[u] = (CT)((whole + (sell[ci + 1] - sell[ci])) * rows_recip(xr[u] - xe[u], (D)0));
+            qs[u] = (CT)((whole + (sell[ci + 1] - sell[ci])) * (D)(1.0 / (xr[u] - xe[u])));
         }
     } else {
         // masses summed from global memory in FP64
@@ -253,8 +253,8 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
                 const double dx = xr[u] - xe[u];
                 sq[ci] = qs[u];
                 sdx[ci] = (CT)dx;
-                shv[ci] = rows_recip(c1 - 0.5 * (xe[u] + xr[u]), (CT)0);
-                sdi[ci] = rows_recip(dx, (CT)0);
+                shv[ci] = (CT)(1.0 / (c1 - 0.5 * (xe[u] + xr[u])));
+                sdi[ci] = (CT)(1.0 / dx);
                 if (qmid && ci >= H && ci < H + nd) qmid[cell[u]] = (TQ)qs[u];
             }
         }

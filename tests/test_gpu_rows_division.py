@@ -7,6 +7,9 @@
   every weight is a product with 0, and a step returns the state to the rounding
   of (Q dx) / dx: two roundings, 2^-23 relative, doubled.  One step in each mode,
   four in one call (planned) by direct sums: prefix sums of such masses cancel.
+* A reciprocal cell size that lies halfway between two FP32 numbers to FP64's last
+  place, for 4096 sizes: what flows into an empty cell comes out as a quarter of
+  the reciprocal rounded once, bit for bit.
 """
 import numpy as np
 import pytest
@@ -35,3 +38,20 @@ def test_weights_past_the_largest_number(scan, steps):
     got = q.cpu().numpy()
     assert np.isfinite(got).all(), np.argwhere(~np.isfinite(got)).ravel()
     assert np.max(np.abs(got / q0 - 1.0)) <= steps * 2.0 ** -22
+
+
+def test_reciprocal_sizes_rounded_once():
+    nr, n = 4096, 16
+    i = np.random.default_rng(6).integers(0, 1 << 23, nr)
+    dx = 1.0 / (1.0 + (2 * i + 1) * 2.0 ** -24)
+    e = np.tile(np.arange(n + 1.0), (nr, 1))
+    e[:, 1] = dx                                     # cell 0: from 0 to dx
+    rows = R.Rows(dev(e), nr, n, None, False)
+    q0, dv = np.zeros((nr, n)), np.zeros((nr, n))
+    q0[:, -1] = 1.0
+    dv[:, 0] = 1.0
+    q = dev(q0, torch.float32)
+    R.ram_step(rows, q, dev(np.zeros(nr)), dev(dv, torch.float32), 0.25, 5, 1, R.RAM_SCAN_F32_TWOSUM)
+    got = q.cpu().numpy().reshape(nr, n)[:, 0]
+    ref = np.float32(0.25) * (1.0 / dx).astype(np.float32)
+    assert np.array_equal(got, ref), int((got != ref).sum())
