@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
             } else {
                 whole = jb - ja == 1 ? (D)sm[ja] : (D)AC::diff(sp[jb], sp[ja]);
             }
-            qs[u] = (CT)((whole + (sell[ci + 1] - sell[ci])) * (D)(1.0 / (xr[u] - xe[u])));
+            qs[u] = (CT)((whole + (sell[ci + 1] - sell[ci])) / (D)(xr[u] - xe[u]));
         }
     } else {
         // masses summed from global memory in FP64

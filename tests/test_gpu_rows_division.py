@@ -10,6 +10,8 @@
 * A reciprocal cell size that lies halfway between two FP32 numbers to FP64's last
   place, for 4096 sizes: what flows into an empty cell comes out as a quarter of
   the reciprocal rounded once, bit for bit.
+* A shift of nothing: each cell is (Q dx) / dx in the type of the mode's sums,
+  product and quotient rounded once each, bit for bit.
 """
 import numpy as np
 import pytest
@@ -54,4 +56,24 @@ def test_reciprocal_sizes_rounded_once():
     R.ram_step(rows, q, dev(np.zeros(nr)), dev(dv, torch.float32), 0.25, 5, 1, R.RAM_SCAN_F32_TWOSUM)
     got = q.cpu().numpy().reshape(nr, n)[:, 0]
     ref = np.float32(0.25) * (1.0 / dx).astype(np.float32)
+    assert np.array_equal(got, ref), int((got != ref).sum())
+
+
+@pytest.mark.parametrize("dtype,scan", [(torch.float64, R.RAM_SCAN_F64), (torch.float32, R.RAM_SCAN_F64),
+                                        (torch.float32, R.RAM_SCAN_F32_TWOSUM), (torch.float32, R.RAM_SCAN_F32)])
+@pytest.mark.parametrize("nr", [40, 600])
+def test_mass_over_size(nr, dtype, scan):
+    # (both tile sizes: batches of up to 393,216 cells and of more)
+    n = 700
+    rng = np.random.default_rng(8)
+    e = np.concatenate([np.zeros((nr, 1)), np.cumsum(20.0 ** rng.random((nr, n)), axis=1)], axis=1)
+    dx = np.diff(e, axis=1)
+    q0 = rng.uniform(0.5, 2.0, (nr, n)).astype(np.float32)
+    t = np.float64 if scan == R.RAM_SCAN_F64 else np.float32
+    ref = (q0.astype(t) * dx.astype(t)) / dx.astype(t)
+    rows = R.Rows(dev(e), nr, n, None, False)
+    out = torch.empty(nr * n, dtype=dtype, device=DEV)
+    R.ram_shift(rows, dev(q0, dtype), out, dev(np.zeros(nr)), 1.0, 5, scan)
+    got = out.cpu().numpy().reshape(nr, n)
+    ref = ref.astype(got.dtype)
     assert np.array_equal(got, ref), int((got != ref).sum())
