@@ -9,11 +9,11 @@ namespace ram {
 namespace dev {
 
 // A tile's source window: extended index of its first cell, the period it lies
-// in, length, first cell within the row, window index of the first node of the
-// next period and of the one after (a window as long as its row crosses the
-// row's end twice).
+// in, the length its end nodes give it, its length here, first cell within the
+// row, window index of the first node of the next period and of the one after (a
+// window as long as its row crosses the row's end twice).
 struct RowsWindow {
-    int64_t wlo, k0;
+    int64_t wlo, k0, wide;
     int w, base, seam, seam2;
     __device__ __forceinline__ int period(int j) const { return (j >= seam ? 1 : 0) + (j >= seam2 ? 1 : 0); }
     // row index of window cell or node j (a node past the last period's end: n)
@@ -70,6 +70,29 @@ __device__ __forceinline__ void wrap_node(double xe, double s, double x0, double
     else if (xh < x0) { xh += len; k -= 1; }
 }
 
+// The last node at or below each xh among window nodes xs[0 .. W], within period
+// dk of the window (0, 1 or 2).
+template <int NS>
+__device__ __forceinline__ void rows_search(const double *xs, const RowsWindow &win, int W,
+                                            const double (&xh)[NS], const int (&dk)[NS], int (&j)[NS])
+{
+    int end[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        j[u] = dk[u] == 0 ? 0 : min(dk[u] == 1 ? win.seam : win.seam2, W);
+        end[u] = min(dk[u] == 0 ? win.seam : (dk[u] == 1 ? win.seam2 : W + 1), W + 1);
+    }
+    int top = 1;
+    while (2 * top <= W) top *= 2;
+    for (int step = top; step > 0; step >>= 1) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int at = j[u] + step;
+            if (at < end[u] && xs[min(at, W)] <= xh[u]) j[u] = at;
+        }
+    }
+}
+
 // The tile's window and its nodes' cells.  Nodes e0 .. e0 + NE - 1 of the row
 // (e0 may be a few below 0, the last a few past n), node m = t + 64 u in slot u
 // of lane t (slots past the last repeat it), given as their unshifted
@@ -115,6 +138,7 @@ __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, do
     const int64_t ga = (int64_t)la + ka * (int64_t)n;
     const int64_t gb = (int64_t)(hb - 1) + __shfl(kl, last) * (int64_t)n;
     const int64_t wide = gb - ga + P;
+    win.wide = wide;
     win.wlo = ga - LO;
     // (rows have more than LO cells)
     win.k0 = ka - (la < LO ? 1 : 0);
@@ -125,31 +149,27 @@ __device__ __forceinline__ bool rows_locate(const double *x, int n, double s, do
     if (wide < P || wide > cap || win.base + wide > 3 * (int64_t)n) return false;
     const int W = (int)wide;
     win.w = W;
-    for (int i = t; i <= W; i += kLanes) xs[i] = x[win.at(i, n)];
+    constexpr int NX = 4;                            // nodes a lane has in flight
+    for (int i0 = t; i0 - t <= W; i0 += NX * kLanes) {
+        double v[NX];
+#pragma unroll
+        for (int u = 0; u < NX; ++u) v[u] = x[win.at(min(i0 + u * kLanes, W), n)];
+#pragma unroll
+        for (int u = 0; u < NX; ++u) xs[min(i0 + u * kLanes, W)] = v[u];
+    }
     issue();
     wave_sync();
-    // the last window node at or below each shifted node, within its period
-    int pos[NS], end[NS];
     bool ok = true;
+    int dk[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        const int64_t dk = k[u] - win.k0;
-        ok = ok && dk >= 0 && dk <= 2;
-        pos[u] = dk == 0 ? 0 : min(dk == 1 ? win.seam : win.seam2, W);
-        end[u] = min(dk == 0 ? win.seam : (dk == 1 ? win.seam2 : W + 1), W + 1);
+        const int64_t d = k[u] - win.k0;
+        ok = ok && d >= 0 && d <= 2;
+        dk[u] = (int)d;
     }
-    int top = 1;
-    while (2 * top <= W) top *= 2;
-    for (int step = top; step > 0; step >>= 1) {
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            const int at = pos[u] + step;
-            if (at < end[u] && xs[min(at, W)] <= xh[u]) pos[u] = at;
-        }
-    }
+    rows_search<NS>(xs, win, W, xh, dk, j);
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        j[u] = pos[u];
         ok = ok && j[u] >= LO && j[u] + P - LO <= W && xs[j[u]] <= xh[u];
     }
     return __all(ok ? 1 : 0) != 0;

@@ -20,8 +20,8 @@
 //       two partial integrals, over its size;
 //   (E) the residual from the shifted state in LDS, one face, then one cell a
 //       lane.
-// A window beyond kRowsCap cells, or of a row so short that it crosses its end
-// more than twice, is summed from global memory.
+// A window beyond the LDS, or of a row so short that it crosses its end
+// more than twice, passes through LDS in pieces (rows_wide).
 //
 // VALU issue bounds it, with the chain of dependent loads that starts a wave
 // (the table, the row, its ends and nodes, two rounds of the window search, the
@@ -41,31 +41,193 @@ namespace {
 
 using namespace dev;
 
-constexpr int kRowsCap = 448;        // LDS window, cells
+// Waves a SIMD that the registers allow: only rows_wide spills.
+template <typename TQ, int S, int NS> constexpr int rows_waves()
+{
+    return sizeof(TQ) == 8 ? 3 : (S == kScanF64 || NS == 4 ? 4 : 5);
+}
 
 // LDS of one wave: window nodes, later the cumulative; masses; partial
 // integrals; window cells of the nodes.  The residual's five arrays reuse it.
-template <typename TQ, int S> struct RowsLds {
+// The window takes what that many waves leave of the CU's 160 KB (in allocations of
+// 1280 bytes): 704 cells for FP32 prefix sums with four slots, 668 for FP64, 464 for
+// FP32 states summed in FP64.
+template <typename TQ, int S, int NS> struct RowsLds {
     using M = typename Acc<S>::M;
     using A = typename Acc<S>::A;
     using D = typename std::conditional<std::is_same<TQ, double>::value, double,
                                         typename Acc<S>::D>::type;
-    static constexpr size_t xs = 8 * (kRowsCap + 8);
-    static constexpr size_t sm = sizeof(M) * (kRowsCap + 8);
-    static constexpr size_t sell = sizeof(D) * (kLanes * 4);
-    static constexpr size_t res = 5 * sizeof(TQ) * (kLanes * 4);
-    static constexpr size_t sum = xs + sm + sell;
-    static constexpr size_t bytes = sum > res ? sum : res;
-    static_assert(sizeof(A) <= 8 && 8 * kLanes * 4 <= xs, "the nodes' bytes hold the cumulative");
+    static constexpr size_t wave = 163840 / rows_waves<TQ, S, NS>() / 1280 * 1280 / kWaves;
+    static constexpr size_t sell = sizeof(D) * (kLanes * NS);
+    static constexpr size_t sjc = sizeof(short) * (kLanes * NS);
+    static constexpr int cap = (int)((wave - sell - sjc) / (8 + sizeof(M))) / 4 * 4 - 8;  // cells
+    static constexpr size_t xs = 8 * (cap + 8);
+    static constexpr size_t sm = sizeof(M) * (cap + 8);
+    static constexpr size_t res = 5 * sizeof(TQ) * (kLanes * NS);
+    static constexpr size_t bytes = xs + sm + sell;
+    static_assert(sizeof(A) <= 8 && 8 * kLanes * NS <= xs && res <= bytes, "the nodes' bytes are used again");
 };
+
+// A tile whose window does not fit in LDS: the window in pieces of up to SPAN
+// cells, each staged whole (nodes and masses) and starting p - 1 cells before
+// the last one's end.  The nodes whose stencil a piece holds get their partial
+// integral from it, and every cell adds the piece's share of its whole source
+// cells, so that a cell of the row is read once, in whole lines, and nothing but
+// those sums outlives a piece.  FP64 throughout; cell ci's mass goes to sell[ci].
+// Nodes e0 .. e0 + NE - 1 of the row; the window's start from rows_locate.
+//
+// Latency bounds it: two or three pieces for a tile of 251 cells on a mesh refined
+// tenfold.  A shift of 2.1 M cells in such rows by anything in their period, rows of
+// 700, 1000 and 2000 cells, FP32 two-sum: 43, 45 and 59 us, FP64 48, 50 and 65; with
+// 448 cells of LDS window and every wider one summed from global memory, a search a
+// node and a remainder a cell, 68, 61 and 64, FP64 85, 80 and 82.
+template <typename TQ, int P, int NS, int SPAN, typename D>
+__device__ __forceinline__ void rows_wide(const double *x, const TQ *q, int n, double s, double x0,
+                                          double xN, double len, double invlen, int e0, int NE, int t,
+                                          RowsWindow win, double *xs, D *sell, short *sjc)
+{
+    constexpr int LO = (P - 1) / 2;
+    constexpr int NQ = 5;                            // staged cells a lane has in flight
+    constexpr int kAhead = 0x7fff;                   // a node of a later piece
+    double *sm = xs + SPAN + 1;
+    double xh[NS], whole[NS];
+    int per[NS], in[NS];                             // period; 0: ahead, 1: in this piece, 2: done
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int m = min(t + u * kLanes, NE - 1);
+        int e = e0 + m, kx = 0;
+        if (e < 0) { e += n; kx = -1; }
+        while (e >= n) { e -= n; kx += 1; }
+        int64_t k;
+        wrap_node(x[e], s, x0, xN, len, invlen, xh[u], k);
+        per[u] = (int)min(max(k + kx - win.k0, (int64_t)-1), (int64_t)1 << 30);
+        in[u] = 0;
+        whole[u] = 0.0;
+        sell[m] = (D)__builtin_nan("");
+    }
+    // (a tile's nodes span less than two periods, so its window less than 3 n cells)
+    int64_t left = min(win.wide, 3 * (int64_t)n);
+    int p0 = 0;                                      // the piece's first cell: its period
+    bool all = false;
+    while (!all && left > 0) {
+        const int span = (int)min((int64_t)SPAN, 3 * (int64_t)n - win.base);
+        const int step = span - P + 1;
+        win.seam = n - win.base;
+        win.seam2 = win.seam + n;
+        // ---- nodes and masses (lanes past the last cell repeat it) -----------------
+#pragma unroll 1
+        for (int i0 = t; i0 - t < span; i0 += NQ * kLanes) {
+            double xv[NQ], xw[NQ];
+            TQ qv[NQ];
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) {
+                const int c = win.at(min(i0 + u * kLanes, span - 1), n);
+                xv[u] = x[c];
+                xw[u] = x[c + 1];
+                qv[u] = q[c];
+            }
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) {
+                const int i = min(i0 + u * kLanes, span - 1);
+                xs[i] = xv[u];
+                sm[i] = (double)qv[u] * (xw[u] - xv[u]);
+                // (the node after the last cell: the row's first again past its end)
+                if (i == span - 1) xs[span] = win.at(span, n) == 0 ? x0 : xw[u];
+            }
+        }
+        wave_sync();
+        // ---- which nodes, and where ------------------------------------------------
+        int dk[NS], j[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) dk[u] = min(max(per[u] - p0, 0), 2);
+        rows_search<NS>(xs, win, span, xh, dk, j);
+        bool done = true;
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const bool here = in[u] == 0 && dk[u] == per[u] - p0 && j[u] >= LO && j[u] < LO + step &&
+                              xs[j[u]] <= xh[u];
+            in[u] = here ? 1 : (in[u] != 0 ? 2 : 0);
+            j[u] = min(max(j[u], LO), LO + step - 1);
+            sjc[min(t + u * kLanes, NE - 1)] = (short)(in[u] == 1 ? j[u] : (in[u] == 2 ? 0 : kAhead));
+            done = done && in[u] != 0;
+        }
+        // ---- their partial integrals (one copy of the code: the slots move past it) --
+#pragma unroll 1
+        for (int u = 0; u < NS; ++u) {
+            if (__any(in[0] == 1 ? 1 : 0)) {
+                double w[P + 1];
+                rows_weights<double, P, true>(xs, win, len, xh[0], j[0], w);
+                double ell = 0.0, up = 0.0, dn = 0.0;
+#pragma unroll
+                for (int b = LO + 1; b <= P; ++b) {
+                    up += sm[j[0] + b - LO - 1];
+                    ell += w[b] * up;
+                }
+#pragma unroll
+                for (int b = LO - 1; b >= 0; --b) {
+                    dn += sm[j[0] - LO + b];
+                    ell -= w[b] * dn;
+                }
+                if (in[0] == 1) sell[min(t + u * kLanes, NE - 1)] = (D)ell;
+            }
+            slot_turn(xh);
+            slot_turn(in);
+            slot_turn(j);
+        }
+        wave_sync();
+        // ---- the piece's share of the whole source cells -----------------------------
+        all = __all(done ? 1 : 0) != 0;
+        left -= step;
+        win.base += step;
+        const int over = win.base / n;
+        win.base -= over * n;
+        p0 += over;
+        int ja[NS], jb[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int ci = min(t + u * kLanes, NE - 2);
+            ja[u] = max((int)sjc[ci], LO);
+            jb[u] = min((int)sjc[ci + 1], LO + step);
+        }
+        // (every slot's next two cells at once)
+        for (;;) {
+            bool more = false;
+            double m0[NS], m1[NS];
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                const int i = min(ja[u], LO + step - 1);
+                m0[u] = sm[i];
+                m1[u] = sm[i + 1];
+            }
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                if (ja[u] < jb[u]) whole[u] += m0[u];
+                if (ja[u] + 1 < jb[u]) whole[u] += m1[u];
+                ja[u] += 2;
+                more = more || ja[u] < jb[u];
+            }
+            if (!__any(more ? 1 : 0)) break;
+        }
+        wave_sync();
+    }
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int ci = min(t + u * kLanes, NE - 2);
+        whole[u] += (double)sell[ci + 1] - (double)sell[ci];
+    }
+    wave_sync();
+#pragma unroll
+    for (int u = 0; u < NS; ++u) sell[min(t + u * kLanes, NE - 2)] = (D)whole[u];
+    wave_sync();
+}
 
 // sub: wave tiles a table tile holds (R.tile = sub times the wave's tile).
 // NS: node slots a lane.
 template <typename TQ, int P, int S, int H, int NS>
-__global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
+__global__ __launch_bounds__(kBlock, (rows_waves<TQ, S, NS>())) void k_rows(StepArgs a, int sub)
 {
     using AC = Acc<S>;
-    using L = RowsLds<TQ, S>;
+    using L = RowsLds<TQ, S, NS>;
     using M = typename L::M;
     using A = typename L::A;
     using D = typename L::D;
@@ -74,6 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
     constexpr bool kLocal = S == kScanF64;           // sums of the FP64 masses between
     constexpr int NDT = kLanes * NS - 1 - 2 * H;     // destination cells
     constexpr int NQ = 5;                            // window slots loaded ahead
+    constexpr int NR = 4;                            // and of a longer one a round
     __shared__ __attribute__((aligned(16))) unsigned char su_[kWaves][L::bytes];
     __shared__ short sjc_[kWaves][kLanes * NS];
     const int wid = wave_id();
@@ -129,7 +292,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
     int j[NS];
     TQ qv[NQ];
     const bool windowed = rows_locate<P, NS>(
-        x, n, s, x0, xN, len, invlen, NE, t, kRowsCap, xe, kx, xs, win, xh, j, [&] {
+        x, n, s, x0, xN, len, invlen, NE, t, L::cap, xe, kx, xs, win, xh, j, [&] {
 #pragma unroll
             for (int u = 0; u < NQ; ++u) qv[u] = q[win.at(min(t + u * kLanes, win.w - 1), n)];
         });
@@ -139,7 +302,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
 #pragma unroll
         for (int u = 0; u < NS; ++u) x2[u] = x[cell[u] + 2 <= n ? cell[u] + 2 : 1];
     }
-    if (windowed) {
+    if (__builtin_expect(windowed, 1)) {
         const int W = win.w;
         TQ w[NS][P + 1];
         if (win.seam > W) {
@@ -161,8 +324,16 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
             const int i = t + u * kLanes;
             if (i < W) sm[i] = AC::template mass<TQ>(qv[u], rows_size(xs, win, xN, i));
         }
-        for (int i = t + NQ * kLanes; i < W; i += kLanes)
-            sm[i] = AC::template mass<TQ>(q[win.at(i, n)], rows_size(xs, win, xN, i));
+        for (int i0 = t + NQ * kLanes; i0 - t < W; i0 += NR * kLanes) {
+            TQ v[NR];
+#pragma unroll
+            for (int u = 0; u < NR; ++u) v[u] = q[win.at(min(i0 + u * kLanes, W - 1), n)];
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const int i = i0 + u * kLanes;
+                if (i < W) sm[i] = AC::template mass<TQ>(v[u], rows_size(xs, win, xN, i));
+            }
+        }
         wave_sync();                                 // the nodes are dead
         if constexpr (!kLocal) {
             rows_prefix<S>(sp, sm, W, t);
@@ -210,28 +381,27 @@ __global__ __launch_bounds__(kBlock) void k_rows(StepArgs a, int sub)
             qs[u] = (CT)((whole + (sell[ci + 1] - sell[ci])) / (D)(xr[u] - xe[u]));
         }
     } else {
-        // masses summed from global memory in FP64
+        constexpr int kSpan = (int)((L::xs + L::sm) / 16) - 1;
         wave_sync();
-        int64_t *sg = (int64_t *)su;
-#pragma unroll 1
-        for (int m = t; m < NE; m += kLanes) {
-            int e = i0 - H + m, k1 = 0;
-            if (e < 0) { e += n; k1 = -1; }
-            while (e >= n) { e -= n; k1 += 1; }
-            double xn;
-            int64_t k;
-            shifted_node_inv(x, n, s, e, invlen, len, xn, k);
-            const int64_t g = (int64_t)find_cell(x, n, xn) + (k + k1) * (int64_t)n;
-            sg[m] = g;
-            sell[m] = (D)direct_partial<TQ, P>(x, q, n, len, s, invlen, i0 - H + m, g);
-        }
-        wave_sync();
+        // (the nodes, their cells' geometry and velocities are read again, at an offset
+        // of 0 that the compiler does not see: held in registers all along, they would
+        // be spilled, by the other tiles too)
+        int zero = 0;
+        asm volatile("" : "+s"(zero));
+        const double *xz = x + zero;
+        rows_wide<TQ, P, NS, kSpan, D>(xz, q, n, s, x0, xN, len, invlen, i0 - H, NE, t, win, xs, sell, sjc);
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
-            const int ci = min(t + u * kLanes, NC - 1);
-            const double wh = direct_whole<TQ>(x, q, n, sg[ci], sg[ci + 1]);
-            qs[u] = (CT)((D)(wh + ((double)sell[ci + 1] - (double)sell[ci])) / (D)(xr[u] - xe[u]));
+            const int c = cell[u];
+            xe[u] = xz[c];
+            xr[u] = xz[c + 1];
+            if constexpr (H != 0) {
+                x2[u] = xz[c + 2 <= n ? c + 2 : 1];
+                v[u] = (CT)((const TQ *)a.dv + ti.qoff + zero)[c];
+            }
         }
+#pragma unroll
+        for (int u = 0; u < NS; ++u) qs[u] = (CT)(sell[min(t + u * kLanes, NC - 1)] / (D)(xr[u] - xe[u]));
     }
     if constexpr (H == 0) {
 #pragma unroll
