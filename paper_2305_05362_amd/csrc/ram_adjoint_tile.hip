@@ -42,8 +42,6 @@ constexpr int kSt = kFT + 8;             // staged cells of one array (cell i0 -
 constexpr int kWin = kFastWin + 8;
 constexpr int kU = 3 * kSt > kWin ? 3 * kSt : kWin;   // doubles: staging, window or node data
 
-static_assert(2 * kFastNodes <= kU, "direct tiles' node data");
-
 // The residual step's transpose on four consecutive cells of a lane, from
 // cells a-2 .. a+5 (index w): the state the residual read q, the gradient of
 // its result qb, 1/dx di, dx, the inverse centre gaps hv (cell w to w+1), and
@@ -429,6 +427,199 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
     }
 }
 
+// (2), (3) of a tile whose window does not fit in LDS: the sums of tile_shift, in its
+// order, on pieces of the window.  A piece holds C + P cells; the nodes whose terms
+// end in it are added, its first C cells are then whole and go out, and its last P
+// begin the next piece.  Every node's weights are formed in FP64, whatever the state.
+//
+// Latency bounds it, as the tiles that fit.  512 rows refined tenfold, shifted by
+// anything in their period, with every gradient: FP64 rows of 1600 and 4096 cells 48
+// and 96 us, FP32 rows of 1301 and 2047 38 and 44; with every window cell's nodes
+// searched and weighed from global memory 115 and 178, 68 and 82.
+template <typename TQ, int P, bool V0>
+__device__ __forceinline__ void tile_wide(const StepAdjArgs &a, const FastTile &ft, const TilePos &p,
+                                          int n, double *su, const double *smb, int t)
+{
+    constexpr int LO = (P - 1) / 2;
+    constexpr int NS = (kFT + 1 + kLanes - 1) / kLanes;       // node slots
+    constexpr int NC = kFT / kLanes;
+    constexpr int NB = 5;                            // window cells a lane has in flight
+    constexpr int kNode = kFastNodes / 2;            // doubles the nodes' cells take
+    constexpr int CP = kU - kNode, C = CP - P;
+    const MeshTab &tb = a.rows.tab;
+    const int i0 = p.i0, nd = p.nd, NE = nd + 1, base = ft.base;
+    const int64_t qoff = (int64_t)p.row * n;
+    const double *x = a.rows.edges;
+    const double x0 = x[0], xN = x[n];
+    const RowShift rs = row_shift(a.v0[p.row] * a.dt, xN - x0, tb.scal[1]);
+    int *sj = (int *)su;                             // each node's window cell
+    double *sw = su + kNode;                         // the piece
+    // (a window is shorter than two periods and the stencil)
+    auto wcell = [&](int j) { return wrap_small(base + j, n); };
+    // the window: this tile's first node's stencil up to the next tile's (the row's
+    // first tile one period on, for the last tile of a row)
+    const int tpr = (n + kFT - 1) / kFT;
+    auto wlo_of = [&](int k) {
+        const FastTile &r = a.fast.rec[k];
+        return (int64_t)(((uint64_t)(uint32_t)r.wlo_hi << 32) | (uint32_t)r.wlo_lo);
+    };
+    const int64_t wlo = wlo_of(ft.pad[0]);
+    const int64_t wend = i0 + nd >= n ? wlo_of(ft.pad[0] - (tpr - 1)) + n : wlo_of(ft.pad[0] + 1);
+    const int W = (int)(wend - wlo) + P;
+
+    // ---- each node's window cell and position in it ----------------------------
+    int jv[NS];
+    double thv[NS];
+    {
+        int ce[NS], kx[NS];
+        double xt[NS];
+        locate_nodes<NS>(x, n, tb, rs, x0, xN, i0, NE, t, ce, kx, xt);
+        const int jbase = (int)(rs.kf0 * (int64_t)n - wlo);
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            jv[u] = min(max(ce[u] + kx[u] + jbase, LO), W - (P - LO));
+            thv[u] = cell_theta(tb.stpd, ce[u], xt[u], xN - x0, false);
+            sj[min(t + u * kLanes, NE - 1)] = jv[u];
+        }
+    }
+    wave_sync();                                     // node cells visible
+    TQ *qbi = (TQ *)a.qbar_in + qoff;
+    TQ *edge = (TQ *)a.edge + (int64_t)ft.pad[0] * (2 * P);
+    for (int b = 0; b < W; b += C) {
+        const bool last = b + CP >= W;
+        const int end = min(b + CP, W);
+        // ---- whole cells: the piece's own ones, after the P carried on ------------
+        const int from = b == 0 ? 0 : b + P;
+        for (int j = from + t; j < end; j += kLanes) sw[j - b] = 0.0;
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int i = t + u * kLanes;
+            if (i < nd) {
+                const int ja = max(sj[i], from), jb = min(sj[i + 1], end);
+                const double mb = smb[1 + i];
+                for (int j = ja; j < jb; ++j) sw[j - b] = mb;
+            }
+        }
+        wave_sync();
+        // ---- the terms of the nodes whose cells the piece holds ---------------------
+#pragma unroll 1
+        for (int u = 0; u < NS; ++u) {
+            const int m = t + u * kLanes, mc = min(m, NE - 1);
+            const int j = jv[0];
+            const bool here = m < NE && j - LO >= b && (last || j - LO < b + C);
+            uint64_t todo = __ballot(here);
+            if (todo) {
+                double rth[P + 1], rrd[P + 1], wk[P + 1], tm[P];
+                node_stencil<P>(tb.stpd, n, wcell(j), rth, rrd);
+                // the slot's nodes before this one in its source cell
+                const bool first = t == 0 || sj[max(mc - 1, 0)] != j;
+                const uint64_t starts = __ballot(first) & (~0ull >> (kLanes - 1 - t));
+                const int rank = t - (63 - __clzll((long long)starts));
+                node_weights<P>(rth, rrd, thv[0], wk);
+                const double vb = smb[mc] - smb[mc + 1];
+                double s = 0.0;
+#pragma unroll
+                for (int k = P; k > LO; --k) {
+                    s += wk[k];
+                    tm[k - 1] = s * vb;
+                }
+                s = 0.0;
+#pragma unroll
+                for (int k = 0; k < LO; ++k) {
+                    s += wk[k];
+                    tm[k] = -s * vb;
+                }
+                double *at = sw + (here ? j - LO - b : 0);
+                for (int turn = 0; todo; ++turn) {
+                    const bool now = here && rank == turn;
+                    if (now) {
+#pragma unroll
+                        for (int k = 0; k < P; ++k) atomicAdd(at + k, tm[k]);
+                    }
+                    todo &= ~__ballot(now);
+                }
+            }
+            slot_turn(jv);
+            slot_turn(thv);
+        }
+        wave_sync();
+        // ---- Qbar^n = Mbar dx, one window cell a lane -------------------------------
+        const int out = last ? W : b + C;
+        for (int j0 = b + t; j0 - t < out; j0 += NB * kLanes) {
+            double wd[NB];
+            int cw[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                cw[u] = wcell(min(j0 + u * kLanes, out - 1));
+                wd[u] = TabT<double>::dx(tb)[cw[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int j = j0 + u * kLanes;
+                if (j < out) put_cell<P, TQ>(qbi, edge, cw[u], j, W, (TQ)(sw[j - b] * wd[u]));
+            }
+        }
+        if (last) break;
+        const double carry = sw[C + min(t, P - 1)];
+        wave_sync();
+        if (t < P) sw[t] = carry;
+    }
+    // ---- v0bar: q~ at the nodes from the window's masses, a piece after the other ----
+    if constexpr (V0) {
+        const TQ *qf = (const TQ *)a.q_fwd + qoff;
+        double qt[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) qt[u] = 0.0;
+        for (int b = 0; b < W; b += C) {
+            const bool last = b + CP >= W;
+            const int len = min(CP, W - b);
+            wave_sync();                             // the gradients, or the last piece, are dead
+            for (int k0 = t; k0 - t < len; k0 += NB * kLanes) {
+                double wq[NB], wd[NB];
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int c = wcell(b + min(k0 + u * kLanes, len - 1));
+                    wq[u] = (double)qf[c];
+                    wd[u] = TabT<double>::dx(tb)[c];
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u)
+                    if (k0 + u * kLanes < len) sw[k0 + u * kLanes] = wq[u] * wd[u];
+            }
+            wave_sync();
+#pragma unroll 1
+            for (int u = 0; u < NS; ++u) {
+                const int j = jv[0];
+                const bool here = j - LO >= b && (last || j - LO < b + C);
+                if (__any(here ? 1 : 0)) {
+                    const int c = wcell(j), k = here ? j - LO - b : 0;
+                    TQ rth[P + 1], rrd[P + 1], dw[P + 1];
+                    tile_stencil<P>(tb, n, c, false, rth, rrd);
+                    node_dweights<P>(rth, rrd, (TQ)thv[0], dw);
+                    double dq = 0.0, up = 0.0, dn = 0.0;
+#pragma unroll
+                    for (int d = LO + 1; d <= P; ++d) {
+                        up += sw[k + d - 1];
+                        dq += (double)dw[d] * up;
+                    }
+#pragma unroll
+                    for (int d = LO - 1; d >= 0; --d) {
+                        dn += sw[k + d];
+                        dq -= (double)dw[d] * dn;
+                    }
+                    if (here) qt[0] = dq * tb.stpd[c].y;
+                }
+                slot_turn(qt);
+                slot_turn(jv);
+                slot_turn(thv);
+            }
+            if (last) break;
+        }
+        v0_term<NS>(a, ft.pad[0], qt, smb, nd, t);
+    }
+}
+
 template <typename TQ, int P, bool RES, bool V0>
 __global__ __launch_bounds__(kBlock, 4) void k_adj_tile(StepAdjArgs a)
 {
@@ -448,7 +639,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_adj_tile(StepAdjArgs a)
     } else if (ft.kind != kFastDirect)
         tile_shift<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], sjc_[wid], t);
     else
-        direct_shift<TQ, P, V0>(a, ft, su[wid], smb_[wid], t);
+        tile_wide<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], t);
 }
 
 template <typename TQ, int P, bool RES, bool V0>

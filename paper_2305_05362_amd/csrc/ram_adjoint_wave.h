@@ -78,7 +78,7 @@ __device__ __forceinline__ double qtilde_global(const double *x, const TQ *q, in
     return dq;
 }
 
-// The shift's transpose of a tile whose window does not fit, from Mbar' of its
+// The streaming adjoint's shift of a tile whose window does not fit, from Mbar' of its
 // cells in smb[1 ..] (zeros at both ends); su holds 16 kFastNodes bytes.
 template <typename TQ, int P, bool V0, typename MT>
 __device__ __forceinline__ void direct_shift(const StepAdjArgs &a, const FastTile &ft, void *su,
