@@ -198,18 +198,16 @@ __device__ __forceinline__ void tile_residual(const StepAdjArgs &a, const TilePo
     wave_sync();
 }
 
-// Source cell c's stencil in the state's type (FP64: a uniform run's from its
-// FP32 deviations).
+// Source cell c's stencil in the state's type.
 template <int P>
-__device__ __forceinline__ void tile_stencil(const MeshTab &tb, int n, int c, bool uniform,
-                                             double (&rth)[P + 1], double (&rrd)[P + 1])
+__device__ __forceinline__ void tile_stencil(const MeshTab &tb, int n, int c, double (&rth)[P + 1],
+                                             double (&rrd)[P + 1])
 {
-    if (uniform) node_stencil_uni<P>(tb.stdv, n, c, rth, rrd);
-    else node_stencil<P>(tb.stpd, n, c, rth, rrd);
+    node_stencil<P>(tb.stpd, n, c, rth, rrd);
 }
 template <int P>
-__device__ __forceinline__ void tile_stencil(const MeshTab &tb, int n, int c, bool,
-                                             float (&rth)[P + 1], float (&rrd)[P + 1])
+__device__ __forceinline__ void tile_stencil(const MeshTab &tb, int n, int c, float (&rth)[P + 1],
+                                             float (&rrd)[P + 1])
 {
     node_stencil<P>(tb.stp, n, c, rth, rrd);
 }
@@ -289,7 +287,6 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
     const int i0 = p.i0, nd = p.nd, NE = nd + 1;
     const int64_t qoff = (int64_t)p.row * n;
     const int W = ft.w, base = ft.base;
-    const bool uniform = ft.kind == kFastUniform;
     const double *x = a.rows.edges;
     const double x0 = x[0], xN = x[n];
     const RowShift rs = row_shift(a.v0[p.row] * a.dt, xN - x0, tb.scal[1]);
@@ -333,7 +330,7 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
         const int j = jv[0], c = wcell(j);
         TQ rth[P + 1], rrd[P + 1], wk[P + 1];
         double tm[P];
-        tile_stencil<P>(tb, n, c, uniform, rth, rrd);
+        tile_stencil<P>(tb, n, c, rth, rrd);
         // the slot's nodes before this one in its source cell
         const bool first = t == 0 || (int)sjc[max(mc - 1, 0)] != j;
         const uint64_t starts = __ballot(first) & (~0ull >> (kLanes - 1 - t));
@@ -405,7 +402,7 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
         for (int u = 0; u < NS; ++u) {
             const int j = jv[0], c = wcell(j);
             TQ rth[P + 1], rrd[P + 1], dw[P + 1];
-            tile_stencil<P>(tb, n, c, uniform, rth, rrd);
+            tile_stencil<P>(tb, n, c, rth, rrd);
             node_dweights<P>(rth, rrd, (TQ)thv[0], dw);
             double dq = 0.0, up = 0.0, dn = 0.0;
 #pragma unroll
@@ -595,7 +592,7 @@ __device__ __forceinline__ void tile_wide(const StepAdjArgs &a, const FastTile &
                 if (__any(here ? 1 : 0)) {
                     const int c = wcell(j), k = here ? j - LO - b : 0;
                     TQ rth[P + 1], rrd[P + 1], dw[P + 1];
-                    tile_stencil<P>(tb, n, c, false, rth, rrd);
+                    tile_stencil<P>(tb, n, c, rth, rrd);
                     node_dweights<P>(rth, rrd, (TQ)thv[0], dw);
                     double dq = 0.0, up = 0.0, dn = 0.0;
 #pragma unroll
