@@ -223,10 +223,19 @@ __device__ __forceinline__ void tile_uniform(const StepAdjArgs &a, const FastTil
                                              int t)
 {
     constexpr int NW = (kFT + P + kLanes - 1) / kLanes;       // window slots
+    constexpr int LO = (P - 1) / 2;
+    const MeshTab &tb = a.rows.tab;
     const int nd = p.nd, W = ft.w, base = ft.base;
     const int64_t qoff = (int64_t)p.row * n;
-    const double th = (double)__int_as_float(ft.pad[1]);
-    const double dx = TabT<double>::dx(a.rows.tab)[base];
+    const double dx = TabT<double>::dx(tb)[base];
+    // the theta of the first node, in window cell LO, as the plan forms it: the
+    // record's is rounded to FP32, one error for the whole tile
+    const double *x = a.rows.edges;
+    const double x0 = x[0], xN = x[n];
+    const RowShift rs = row_shift(a.v0[p.row] * a.dt, xN - x0, tb.scal[1]);
+    int dk;
+    const double xt = node_wrap(x[p.i0], rs, x0, xN, dk);
+    const double th = cell_theta(tb.stpd, base + LO >= n ? base + LO - n : base + LO, xt, xN - x0, false);
     float *qbi = (float *)a.qbar_in + qoff;
     float *edge = (float *)a.edge + (int64_t)ft.pad[0] * (2 * P);
     float wq[NW];

@@ -4,12 +4,18 @@ granted changes nothing in the gradient.
 * FP64: rows whose nodes are the same in a stretch of equal cells, once a uniform run
   (its cells are the mesh's smallest), once not (two other cells beyond it, one
   smaller and one larger): the gradients there are equal bit for bit.
+* FP32 rows not a multiple of four cells: on cells of a power of two the products
+  with sizes and their reciprocals are exact and the stencil's sums are FP64, so a
+  gradient is the exact one rounded once, but for the p window cells that a tile
+  shares with the next, which are sums of rounded terms.
 """
 import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2305_05362_amd import _lib as R
+from paper_2305_05362_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -43,3 +49,22 @@ def test_fp64_gradient_in_a_run(h, order):
         R.ram_step_adjoint(rows, None, None, None, bar, out, v0, 1.0, order)
         got.append(out.cpu().numpy().reshape(nr, n)[:, 320:1400])
     assert np.array_equal(got[0], got[1]), int((got[0] != got[1]).sum())
+
+
+@pytest.mark.parametrize("order", [1, 3, 5])
+@pytest.mark.parametrize("n", [1025, 2047])
+def test_fp32_gradient_rounded_once(n, order):
+    nr = 8
+    e = np.arange(n + 1.0) / 1024
+    rng = np.random.default_rng(3)
+    bar = rng.standard_normal((nr, n)).astype(np.float32)
+    wl = W.Workload("run", nr, n, np.arange(nr + 1) * n, e, True, np.ones((nr, n)), None,
+                    rng.uniform(-0.7, 0.7, nr), 1.0, order, 1)
+    out = torch.empty(nr * n, dtype=torch.float32, device=DEV)
+    R.ram_step_adjoint(R.Rows.from_workload(wl, DEV), None, None, None, dev(bar, torch.float32), out,
+                       dev(wl.v0), 1.0, order)
+    ref = oracle.shift_adjoint(oracle.Rows.from_workload(wl), wl.q0.reshape(-1),
+                               bar.astype(np.float64).reshape(-1), wl.v0, 1.0, order)[0]
+    got = out.cpu().numpy()
+    wrong = int((got != ref.astype(np.float32)).sum())
+    assert wrong <= nr * -(-n // 256) * order, wrong
