@@ -238,7 +238,7 @@ RowsPlan plan_rows(Carve &cv, const ram_layout *L, int tile, int tab_order)
     if (L->n_cols == 0) p.rag_off = cv.take(ragged_bytes(L, tile));
     if (L->edges_shared && tab_order > 0) {
         p.order = tab_order;
-        p.tab_off = cv.take(ram::mesh_tab_bytes(L->n_cols, tab_order));
+        p.tab_off = cv.take(ram::mesh_layout(L->n_cols).bytes);
     }
     return p;
 }

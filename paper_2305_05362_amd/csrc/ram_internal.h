@@ -6,6 +6,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "ram_mesh_layout.h"
+
 namespace ram {
 
 // Destination cells per workgroup tile, threads per workgroup, and the
@@ -35,8 +37,6 @@ enum ScanMode { kScanF64 = 0, kScanTwoSum = 1, kScanF32 = 2, kSumDirect = 3 };
 // Limited reconstructions of the bulk shift (Section 3.1): PLM with the van
 // Leer slope, PPM with the interface values and constraints of App. A.
 enum Recon { kReconPLM = 1, kReconPPM = 2 };
-
-constexpr int kMeshPad = 16;
 
 // Mesh-only tables for a mesh shared by every row (built once per call by
 // launch_mesh_prep): cell sizes and their reciprocals, reciprocal centre gaps
@@ -97,8 +97,8 @@ template <typename T> struct CellRec {
     T th[6];
     T rd[6];
 };
-static_assert(sizeof(CellRec<float>) == 64, "one cache line");
-static_assert(sizeof(CellRec<double>) == 112, "FP64 record");
+static_assert(sizeof(CellRec<float>) == kCellRecF32, "one cache line");
+static_assert(sizeof(CellRec<double>) == kCellRecF64, "FP64 record");
 // Stencil data of source cell c (order p, lo = (p-1)/2), in units of dx_c:
 //   th[a] = (x_{c-lo+a} - x_c) / dx_c                   a = 0..p
 //   rd[a] = 1 / prod_{b != a} (th[a] - th[b])
@@ -405,9 +405,7 @@ struct CopyJob {
 hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
                              int64_t *tile_ptr, int32_t *tile_row,
                              hipStream_t stream, const CopyJob &copy = CopyJob());
-// Bytes of scratch the shared-mesh tables of an n-cell mesh need.
-size_t mesh_tab_bytes(int64_t n, int order);
-// Build the tables in `mem` (mesh_tab_bytes) and point `tab` at them, with the
+// Build the tables in `mem` (mesh_layout(n).bytes) and point `tab` at them, with the
 // uniform-run counts if `uniform`: one launch.
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
                             MeshTab &tab, hipStream_t stream, bool uniform = false,

@@ -572,47 +572,35 @@ hipError_t mesh_prep_launch(const double *x, int64_t n, int order, const MeshTab
     return hipGetLastError();
 }
 
-size_t al256(size_t v) { return (v + 255) & ~size_t(255); }
-
 } // namespace
-
-size_t mesh_tab_bytes(int64_t n, int order)
-{
-    const int64_t nb = 4 * n;
-    return 3 * al256(8 * n) + 3 * al256(4 * n) + al256(8 * n * 2 * (order + 1)) +
-           al256(4 * n * 2 * (order + 1)) + al256(4 * nb) + al256(16 * nb) + al256(16) +
-           al256(sizeof(CellRec<float>) * n) + al256(sizeof(CellRec<double>) * n) +
-           al256(8 * n) + al256(36 * n) + al256(16 * n) + al256(96 * n) + al256(36 * n) + al256(40 * n) +
-           al256(20 * n) +
-           2 * al256(4 * (n + 1));
-}
 
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
                             MeshTab &tab, hipStream_t stream, bool uniform, const CopyJob &copy)
 {
+    const MeshLayout m = mesh_layout(n);
     char *p = (char *)mem;
     MeshTabW w;
-    w.dx = (double *)p; p += al256(8 * n);
-    w.dxinv = (double *)p; p += al256(8 * n);
-    w.hinv = (double *)p; p += al256(8 * n);
-    w.dxf = (float *)p; p += al256(4 * (n + kMeshPad));
-    w.dxinvf = (float *)p; p += al256(4 * (n + kMeshPad));
-    w.hinvf = (float *)p; p += al256(4 * n);
-    w.bucket = (int32_t *)p; p += al256(4 * 4 * n);
+    w.dx = (double *)(p + m.dx);
+    w.dxinv = (double *)(p + m.dxinv);
+    w.hinv = (double *)(p + m.hinv);
+    w.dxf = (float *)(p + m.dxf);
+    w.dxinvf = (float *)(p + m.dxinvf);
+    w.hinvf = (float *)(p + m.hinvf);
+    w.bucket = (int32_t *)(p + m.bucket);
     w.nb = (int32_t)(4 * n);
-    w.bnext = (double2 *)p; p += al256(16 * 4 * n);
-    w.scal = (double *)p; p += al256(24);
-    w.crf = (CellRec<float> *)p; p += al256(sizeof(CellRec<float>) * n);
-    w.crd = (CellRec<double> *)p; p += al256(sizeof(CellRec<double>) * n);
-    w.rrf = (float2 *)p; p += al256(8 * (n + kMeshPad));
-    w.stp = (float *)p; p += al256(36 * n);
-    w.rrd = (double2 *)p; p += al256(16 * n);
-    w.stpd = (double2 *)p; p += al256(96 * n);
-    w.stdv = (float *)p; p += al256(36 * n);
-    w.ppmd = (double *)p; p += al256(40 * n);
-    w.ppmf = (float *)p; p += al256(20 * n);
-    w.nonu = (int32_t *)p; p += al256(4 * (n + 1));
-    w.nonu_min = (int32_t *)p;
+    w.bnext = (double2 *)(p + m.bnext);
+    w.scal = (double *)(p + m.scal);
+    w.crf = (CellRec<float> *)(p + m.crf);
+    w.crd = (CellRec<double> *)(p + m.crd);
+    w.rrf = (float2 *)(p + m.rrf);
+    w.stp = (float *)(p + m.stp);
+    w.rrd = (double2 *)(p + m.rrd);
+    w.stpd = (double2 *)(p + m.stpd);
+    w.stdv = (float *)(p + m.stdv);
+    w.ppmd = (double *)(p + m.ppmd);
+    w.ppmf = (float *)(p + m.ppmf);
+    w.nonu = (int32_t *)(p + m.nonu);
+    w.nonu_min = (int32_t *)(p + m.nonu_min);
     tab.dx = w.dx; tab.dxinv = w.dxinv; tab.hinv = w.hinv;
     tab.dxf = w.dxf; tab.dxinvf = w.dxinvf; tab.hinvf = w.hinvf;
     tab.bucket = w.bucket;
