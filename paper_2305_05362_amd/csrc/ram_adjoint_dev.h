@@ -9,13 +9,15 @@ namespace ram {
 namespace dev {
 
 // Shifted node -> extended source index g, its cell c, the wrapped position
-// xh and the Lagrange weights of its stencil (the search of the step kernel).
-template <typename WT, int P>
+// xh and the Lagrange weights of its stencil (the search of the step kernel).  SAME:
+// by the streaming plan's arithmetic (node_pos_same), for a window that it placed.
+template <typename WT, int P, bool SAME = false>
 __device__ inline int64_t node_eval_adj(const double *x, int n, const MeshTab &tb,
                                         const RowShift &rs, double len, double xe,
                                         int kx, WT *w, int &cc, double &xh_out)
 {
-    const NodePos np = node_pos(xe, rs, x[0], x[n], tb.scal[0], tb.scal[2], tb.nb);
+    const NodePos np = SAME ? node_pos_same(xe, rs, x[0], x[n], tb.scal[0], tb.scal[2], tb.nb)
+                            : node_pos(xe, rs, x[0], x[n], tb.scal[0], tb.scal[2], tb.nb);
     const double2 nx = tb.bnext[np.b];
     int c = cell_from_bucket(tb.bucket[np.b], nx, np.xt);
     if (np.xt >= nx.y) c = cell_walk(x, n, c, np.xt);

@@ -1042,7 +1042,8 @@ __device__ __forceinline__ void lim_tile(const StepAdjArgs &a, const FastTile &f
         const int m = min(t + u * kLanes, NE - 1);
         const int e = i0 + m;
         const int kx = e >= n ? 1 : 0;
-        const NodePos np = node_pos(x[e - kx * n], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
+        // (the plan's arithmetic: the window starts where it put the first node)
+        const NodePos np = node_pos_same(x[e - kx * n], rs, x0, xN, tb.scal[0], tb.scal[2], tb.nb);
         int c, k;
         if (planned) {
             k = uniform ? LO + m : (int)jcp[m];

@@ -111,7 +111,7 @@ __device__ __forceinline__ void direct_shift(const StepAdjArgs &a, const FastTil
             TQ w[P + 1];
             double xh;
             int c;
-            sgd[m] = node_eval_adj<TQ, P>(x, n, tb, rs, len, x[en - kx * n], kx, w, c, xh);
+            sgd[m] = node_eval_adj<TQ, P, true>(x, n, tb, rs, len, x[en - kx * n], kx, w, c, xh);
             svb[m] = (double)smb[m] - (double)smb[m + 1];
             if constexpr (V0) {
                 double dwd[P + 1];
@@ -148,7 +148,7 @@ __device__ __forceinline__ void direct_shift(const StepAdjArgs &a, const FastTil
             const int kx = en >= n ? 1 : 0;
             double ww[P + 1], xh2;
             int c2;
-            node_eval_adj<double, P>(x, n, tb, rs, len, x[en - kx * n], kx, ww, c2, xh2);
+            node_eval_adj<double, P, true>(x, n, tb, rs, len, x[en - kx * n], kx, ww, c2, xh2);
             // the share of the node's weights on cumulative nodes above the
             // cell, the own weight taken as one minus the others
             const int bmin = (int)min((int64_t)P, max((int64_t)1, target - sgd[e] + 1));
