@@ -283,9 +283,10 @@ __device__ __forceinline__ void tile_uniform(const StepAdjArgs &a, const FastTil
     }
 }
 
-// (2), (3) of a tile whose window fits in LDS.
+// (2), (3) of a tile whose window fits in LDS.  False, and nothing done: a node is not
+// in the window.
 template <typename TQ, int P, bool V0>
-__device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile &ft, const TilePos &p,
+__device__ __forceinline__ bool tile_shift(const StepAdjArgs &a, const FastTile &ft, const TilePos &p,
                                            int n, double *sw, const double *smb, short *sjc, int t)
 {
     constexpr int LO = (P - 1) / 2;
@@ -311,8 +312,8 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
     double thv[NS];
     if (a.fast.jc)
         tile_nodes<P, NS, true>(a.fast, ft, x, n, tb, rs, x0, xN, i0, NE, wcell, t, jv, thv);
-    else
-        tile_nodes<P, NS, false>(a.fast, ft, x, n, tb, rs, x0, xN, i0, NE, wcell, t, jv, thv);
+    else if (!tile_nodes<P, NS, false>(a.fast, ft, x, n, tb, rs, x0, xN, i0, NE, wcell, t, jv, thv))
+        return false;
 #pragma unroll
     for (int u = 0; u < NS; ++u) sjc[min(t + u * kLanes, NE - 1)] = (short)jv[u];
     wave_sync();                                     // node cells visible
@@ -431,6 +432,7 @@ __device__ __forceinline__ void tile_shift(const StepAdjArgs &a, const FastTile 
         }
         v0_term<NS>(a, ft.pad[0], qt, smb, nd, t);
     }
+    return true;
 }
 
 // (2), (3) of a tile whose window does not fit in LDS: the sums of tile_shift, in its
@@ -640,11 +642,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_adj_tile(StepAdjArgs a)
     const FastTile ft = load_rec(a.fast.rec, i);
     const TilePos p = tile_pos(i, n, 0);
     tile_residual<TQ, RES>(a, p, n, su[wid], smb_[wid], t);
-    if (sizeof(TQ) == 4 && ft.kind == kFastUniform) {
-        if constexpr (sizeof(TQ) == 4) tile_uniform<P, V0>(a, ft, p, n, su[wid], smb_[wid], t);
-    } else if (ft.kind != kFastDirect)
-        tile_shift<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], sjc_[wid], t);
-    else
+    if constexpr (sizeof(TQ) == 4) {
+        if (ft.kind == kFastUniform) return tile_uniform<P, V0>(a, ft, p, n, su[wid], smb_[wid], t);
+    }
+    if (ft.kind == kFastDirect || !tile_shift<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], sjc_[wid], t))
         tile_wide<TQ, P, V0>(a, ft, p, n, su[wid], smb_[wid], t);
 }
 

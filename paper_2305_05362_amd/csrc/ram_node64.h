@@ -172,15 +172,25 @@ __device__ __forceinline__ void locate_nodes(const double *x, int n, const MeshT
     }
 }
 
-// The window index of extended cell ce + kx of a window of W cells that starts
-// at wlo (a planned tile's nodes lie in it; the clamp keeps a read in bounds).
-template <int P>
-__device__ __forceinline__ int window_index(int ce, int kx, const RowShift &rs, int n,
-                                            const FastTile &ft)
+// The window indices of a tile's nodes (extended cells ce + kx) in its window, and
+// whether they hold every node's stencil (not expected otherwise: the record sized
+// the window from the end nodes, and on increasing nodes the ones between lie
+// between; a tile whose nodes do not goes the way of a window beyond the LDS, as
+// the plan sends it).
+template <int P, int NS>
+__device__ __forceinline__ bool window_indices(const int (&ce)[NS], const int (&kx)[NS], const RowShift &rs,
+                                               int n, const FastTile &ft, int (&j)[NS])
 {
     constexpr int LO = (P - 1) / 2;
     const int64_t wlo = (int64_t)(((uint64_t)(uint32_t)ft.wlo_hi << 32) | (uint32_t)ft.wlo_lo);
-    return min(max(ce + kx + (int)(rs.kf0 * (int64_t)n - wlo), LO), ft.w - (P - LO));
+    const int jbase = (int)(rs.kf0 * (int64_t)n - wlo);
+    bool ok = true;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        j[u] = ce[u] + kx[u] + jbase;
+        ok = ok && j[u] >= LO && j[u] + P - LO <= ft.w;
+    }
+    return __all(ok ? 1 : 0) != 0;
 }
 
 // Position in cell c (pair 0 of stpd: its left edge and 1/dx) of a node at
@@ -289,9 +299,9 @@ __device__ __forceinline__ FastTile plan_wave(const StepArgs &a, int tile, int H
 // plan, or located here where the call has none (one step: the plan's launch
 // costs more than the search: one FP64 step of a row of 256 cells 17 us
 // against 20, an FP32 step back over 24,000 searching tiles 131 against 157).  wcell: window
-// index -> cell of the row.
+// index -> cell of the row.  False: a node located here is not in the window.
 template <int P, int NS, bool PLAN, class Cell>
-__device__ __forceinline__ void tile_nodes(const FastPlan &pl, const FastTile &ft, const double *x,
+__device__ __forceinline__ bool tile_nodes(const FastPlan &pl, const FastTile &ft, const double *x,
                                            int n, const MeshTab &tb, const RowShift &rs, double x0,
                                            double xN, int e0, int NE, Cell wcell, int t,
                                            int (&jv)[NS], double (&thv)[NS])
@@ -304,11 +314,8 @@ __device__ __forceinline__ void tile_nodes(const FastPlan &pl, const FastTile &f
         double xt[NS];
         locate_nodes<NS>(x, n, tb, rs, x0, xN, e0, NE, t, ce, kx, xt);
 #pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            jv[u] = window_index<P>(ce[u], kx[u], rs, n, ft);
-            thv[u] = cell_theta(tb.stpd, ce[u], xt[u], len, false);
-        }
-        return;
+        for (int u = 0; u < NS; ++u) thv[u] = cell_theta(tb.stpd, ce[u], xt[u], len, false);
+        return window_indices<P, NS>(ce, kx, rs, n, ft, jv);
     }
     const int16_t *jcp = uniform ? nullptr : pl.jc + (int64_t)ft.pad[1] * kFastNodes;
 #pragma unroll
@@ -331,6 +338,7 @@ __device__ __forceinline__ void tile_nodes(const FastPlan &pl, const FastTile &f
         jv[u] = j;
         thv[u] = th;
     }
+    return true;
 }
 
 } // namespace dev

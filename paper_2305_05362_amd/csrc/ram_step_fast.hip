@@ -417,36 +417,57 @@ __global__ __launch_bounds__(kBlock) void k_plan_nodes(StepArgs a, int lists)
     }
 }
 
-// The window index and FP32 theta of a searching tile's nodes: the call's node
-// plan, or (PLAN false: one step) located here by the same arithmetic.
-template <int P, int NS, bool PLAN>
-__device__ __forceinline__ void node_data(const StepArgs &a, const FastTile &ft, int n, int row, int e0,
-                                          int NE, int t, float (&thv)[NS], int (&jv)[NS])
-{
-    if constexpr (PLAN) {
-        const float *thp = a.fast.theta + (int64_t)ft.pad[1] * kFastNodes;
-        const int16_t *jcp = a.fast.jc + (int64_t)ft.pad[1] * kFastNodes;
+// The window index and FP32 theta of a searching tile's nodes, as the tile's code
+// takes them when it needs them: from the call's node plan, or (one step) located
+// before by the same arithmetic.
+template <int H> constexpr int kNodeSlots = (kFT + 2 * H + 1 + kLanes - 1) / kLanes;
+template <int H> struct PlannedNodes {
+    const float *theta;
+    const int16_t *jc;
+    __device__ __forceinline__ PlannedNodes(const StepArgs &a, const FastTile &ft)
+        : theta(a.fast.theta + (int64_t)ft.pad[1] * kFastNodes),
+          jc(a.fast.jc + (int64_t)ft.pad[1] * kFastNodes)
+    {
+    }
+    __device__ __forceinline__ void get(int t, float (&thv)[kNodeSlots<H>], int (&jv)[kNodeSlots<H>]) const
+    {
 #pragma unroll
-        for (int u = 0; u < NS; ++u) {
+        for (int u = 0; u < kNodeSlots<H>; ++u) {
             const int m = min(t + u * kLanes, kFastNodes - 1);
-            thv[u] = thp[m];
-            jv[u] = jcp[m];
-        }
-    } else {
-        const MeshTab &tb = a.rows.tab;
-        const double *x = a.rows.edges;
-        const double x0 = x[0], xN = x[n];
-        const RowShift rs = row_shift(a.v0[row] * a.dt, xN - x0, tb.scal[1]);
-        int ce[NS], kx[NS];
-        double xt[NS];
-        locate_nodes<NS>(x, n, tb, rs, x0, xN, e0, NE, t, ce, kx, xt);
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            thv[u] = (float)((xt[u] - x[ce[u]]) * tb.dxinv[ce[u]]);
-            jv[u] = window_index<P>(ce[u], kx[u], rs, n, ft);
+            thv[u] = theta[m];
+            jv[u] = jc[m];
         }
     }
-}
+};
+template <int H> struct LocatedNodes {
+    float th[kNodeSlots<H>];
+    int j[kNodeSlots<H>];
+    // false: a node is not in the window
+    template <int P> __device__ __forceinline__ bool locate(const StepArgs &a, const FastTile &ft, int t)
+    {
+        constexpr int NS = kNodeSlots<H>;
+        const MeshTab &tb = a.rows.tab;
+        const int n = (int)a.rows.n_cols;
+        const TilePos tp = tile_pos(ft.pad[0], n, H);
+        const double *x = a.rows.edges;
+        const double x0 = x[0], xN = x[n];
+        const RowShift rs = row_shift(a.v0[tp.row] * a.dt, xN - x0, tb.scal[1]);
+        int ce[NS], kx[NS];
+        double xt[NS];
+        locate_nodes<NS>(x, n, tb, rs, x0, xN, tp.i0 - H, tp.nd + 2 * H + 1, t, ce, kx, xt);
+#pragma unroll
+        for (int u = 0; u < NS; ++u) th[u] = (float)((xt[u] - x[ce[u]]) * tb.dxinv[ce[u]]);
+        return window_indices<P, NS>(ce, kx, rs, n, ft, j);
+    }
+    __device__ __forceinline__ void get(int, float (&thv)[kNodeSlots<H>], int (&jv)[kNodeSlots<H>]) const
+    {
+#pragma unroll
+        for (int u = 0; u < kNodeSlots<H>; ++u) {
+            thv[u] = th[u];
+            jv[u] = j[u];
+        }
+    }
+};
 
 // LDS window of the limited step's searching tiles, in cells: four arrays of
 // it (masses; averages, later the cubics' C; slopes or PLM kappa, later A;
@@ -540,9 +561,10 @@ __device__ __forceinline__ void lim_window_partials(const StepArgs &a, const Mes
 // window of at most kGenLimWin cells is tabulated in LDS (lim_window_partials,
 // su then holds kGenLimLds bytes); wider ones take the global-memory path,
 // each node's partial integral the limited profile of its cell (Section 3.1).
-template <int P, int H, bool VEC, int LR = 0, bool PLAN = true>
-__device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &ft,
-                                             unsigned char *su, float *sell, short *sjc, int t)
+template <int P, int H, bool VEC, int LR, class Nodes>
+__device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &ft, bool located,
+                                             const Nodes &nodes, unsigned char *su, float *sell,
+                                             short *sjc, int t)
 {
     constexpr int LO = (P - 1) / 2;
     constexpr int NV = 4 + 2 * H;                    // shifted cells a lane reads
@@ -566,14 +588,14 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
     float *qo = (float *)a.q_out + qoff;
     float *qmid = a.q_mid ? (float *)a.q_mid + qoff : nullptr;
     const int W = ft.w, base = ft.base;
-    const bool windowed = ft.kind == kFastWindow &&
-                          (LR == 0 || (ft.w <= kGenLimWin && ft.w + ft.base <= 2 * n));
+    const bool windowed =
+        located && (LR == 0 || (ft.w <= kGenLimWin && ft.w + ft.base <= 2 * n));
 
     if (windowed) {
         // ---- round trip 1: window masses, the nodes' window index and theta
         float thv[NS];
         int jv[NS];
-        node_data<P, NS, PLAN>(a, ft, n, row, i0 - H, NE, t, thv, jv);
+        nodes.get(t, thv, jv);
         if constexpr (LR != 0) {
             lim_window_partials<LR, NS>(a, tb, n, base, W, NE, qoff, t, thv, jv, (float *)su,
                                         sell, sjc);
@@ -772,8 +794,8 @@ __device__ __forceinline__ void general_tile(const StepArgs &a, const FastTile &
 // six the rows not a multiple of four spill (70 against 58).
 // ---------------------------------------------------------------------------
 
-template <int P, int H, int S, bool VEC, bool PLAN>
-__device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &ft,
+template <int P, int H, int S, bool VEC, class Nodes>
+__device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &ft, const Nodes &nodes,
                                             unsigned char *su, float *sell, short *sjc, int t)
 {
     using AC = Acc<S == kSumDirect ? kScanF32 : S>;
@@ -807,7 +829,7 @@ __device__ __forceinline__ void window_tile(const StepArgs &a, const FastTile &f
     // ---- 1. node plan, window, faces ------------------------------------------
     float thv[NS];
     int jv[NS];
-    node_data<P, NS, PLAN>(a, ft, n, tp.row, i0 - H, NC + 1, t, thv, jv);
+    nodes.get(t, thv, jv);
     // window values and cell sizes (FP64 sizes for the FP64 prefix)
     constexpr bool kDx64 = S == kScanF64;
     float4 wq[NG], wd[NG];
@@ -1204,10 +1226,19 @@ __device__ __forceinline__ void other_tile(const StepArgs &a, const FastTile &r,
 {
     const int wid = wave_id();
     const int n = (int)a.rows.n_cols;
-    if (r.kind == kFastWindow && r.base + r.w + 3 < 2 * n && (VEC || n >= 8))
-        window_tile<P, H, S, VEC, PLAN>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
-    else
-        general_tile<P, H, VEC, 0, PLAN>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+    auto run = [&](const auto &nodes, bool located) {
+        if (located && r.base + r.w + 3 < 2 * n && (VEC || n >= 8))
+            window_tile<P, H, S, VEC>(a, r, nodes, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+        else
+            general_tile<P, H, VEC, 0>(a, r, located, nodes, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+    };
+    if constexpr (PLAN) {
+        run(PlannedNodes<H>(a, r), r.kind == kFastWindow);
+    } else {
+        LocatedNodes<H> nodes;
+        const bool located = r.kind == kFastWindow && nodes.template locate<P>(a, r, t);
+        run(nodes, located);
+    }
 }
 // Wave `wave` of `waves`.
 template <int P, int H, bool VEC, int S>
@@ -1342,7 +1373,8 @@ __device__ __forceinline__ void other_tiles_lim(const StepArgs &a, GenLimLds &ld
     const int total = a.fast.totals[1];
     for (int i = wave; i < total; i += waves) {
         const FastTile r = load_rec(a.fast.rec, load_index(a.fast.oid, i));
-        general_tile<P, H, VEC, R>(a, r, lds.su[wid], lds.sell[wid], lds.sjc[wid], t);
+        general_tile<P, H, VEC, R>(a, r, r.kind == kFastWindow, PlannedNodes<H>(a, r), lds.su[wid],
+                                   lds.sell[wid], lds.sjc[wid], t);
         wave_sync();                                 // the next tile reuses the LDS
     }
 }

@@ -97,7 +97,7 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
     const double *q = (const double *)a.q_in + qoff;
     double *qo = (double *)a.q_out + qoff;
     const int W = ft.w, base = ft.base;
-    const bool direct = ft.kind == kFastDirect || ft.w > win64_cells<S>();
+    bool direct = ft.kind == kFastDirect || ft.w > win64_cells<S>();
     const bool uniform = ft.kind == kFastUniform;
     const double *x = R.edges;
     const double x0 = x[0], xN = x[n];
@@ -138,6 +138,8 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
 
     // window cell j at sw[j + off]
     int off = 0;
+    int jv[NS], cv[NS];
+    double thv[NS];
     if (!direct) {
         // ---- window masses M = Q dx, every load issued ---------------------------
         if (VEC && base + W + 1 < 2 * n) {
@@ -186,12 +188,12 @@ __device__ __forceinline__ void tile64(const StepArgs &a, const FastTile &ft, do
             const int c = base + j;
             return wrapw ? wrap_small(c, n) : (c >= n ? c - n : c);
         };
-        int jv[NS], cv[NS];
-        double thv[NS];
-        tile_nodes<P, NS, PLAN>(a.fast, ft, x, n, tb, rs, x0, xN, i0 - H, NE, wcell, t, jv, thv);
+        direct = !tile_nodes<P, NS, PLAN>(a.fast, ft, x, n, tb, rs, x0, xN, i0 - H, NE, wcell, t, jv, thv);
 #pragma unroll
         for (int u = 0; u < NS; ++u) cv[u] = wcell(jv[u]);
         wave_sync();                                 // the window masses
+    }
+    if (!direct) {
         if constexpr (kPre) {
             // exclusive FP64 cumulative of the masses into sp: LDS cells 4g ..
             // 4g+3 a lane (group g = lane + 64 s), cells past the window as zero
