@@ -1264,17 +1264,6 @@ hipError_t adjf_kernels(const StepAdjArgs &a, hipStream_t st)
     if (nt < kTogether) {
         const unsigned others = gu.x;                // a wave a tile: it may be any of them
         hipLaunchKernelGGL((k_adjf_both<P, RES, V0>), dim3(2 * others), b, 0, st, a, (int)others);
-    } else if (const ForkJoin *fj = capture_fork) {
-        // inside a captured loop: the two kinds of tile (disjoint outputs and
-        // partials) as parallel graph branches, joined before the edges pass
-        hipError_t e = hipEventRecord(fj->fork, st);
-        if (e == hipSuccess) e = hipStreamWaitEvent(fj->side, fj->fork, 0);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_adjf_gen<P, RES, V0>), gg, b, 0, fj->side, a);
-        e = hipEventRecord(fj->join, fj->side);
-        hipLaunchKernelGGL((k_adjf_uni<P, RES, V0>), gu, b, 0, st, a);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, fj->join, 0);
-        if (e != hipSuccess) return e;
     } else {
         hipLaunchKernelGGL((k_adjf_uni<P, RES, V0>), gu, b, 0, st, a);
         hipLaunchKernelGGL((k_adjf_gen<P, RES, V0>), gg, b, 0, st, a);

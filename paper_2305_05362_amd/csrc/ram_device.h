@@ -154,35 +154,6 @@ __device__ inline void lagrange_weights(double xh, const double *X, double *w)
     }
 }
 
-// Lagrange weights at t of the nodes X[0..P] given relative to the stencil's
-// cell (X[lo] = 0, X[lo+1] = dx_c): normalised by dx_c, products of all
-// differences but one, one division per weight, in WT.
-template <typename WT, int P>
-__device__ inline void lagrange_rel(double t, const double *X, WT *w)
-{
-    constexpr int LO = (P - 1) / 2;
-    const double inv = 1.0 / X[LO + 1];
-    WT th[P + 1];
-#pragma unroll
-    for (int a = 0; a <= P; ++a) th[a] = (WT)(X[a] * inv);
-    const WT tt = (WT)(t * inv);
-    WT pre[P + 1], suf[P + 1];
-    pre[0] = (WT)1;
-#pragma unroll
-    for (int a = 1; a <= P; ++a) pre[a] = pre[a - 1] * (tt - th[a - 1]);
-    suf[P] = (WT)1;
-#pragma unroll
-    for (int a = P - 1; a >= 0; --a) suf[a] = suf[a + 1] * (tt - th[a + 1]);
-#pragma unroll
-    for (int a = 0; a <= P; ++a) {
-        WT den = (WT)1;
-#pragma unroll
-        for (int b = 0; b <= P; ++b)
-            if (b != a) den *= th[a] - th[b];
-        w[a] = pre[a] * suf[a] / den;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // prefix-sum precisions
 // ---------------------------------------------------------------------------
@@ -206,7 +177,6 @@ template <> struct Acc<kScanF64> {
     __device__ static A add(A a, M m) { return a + m; }
     __device__ static A comb(A a, A b) { return a + b; }
     __device__ static D diff(A b, A a) { return b - a; }
-    __device__ static A shfl_up(A v, int d) { return __shfl_up(v, d); }
     template <int C, int RM, int BM> __device__ static A dpp(A v) { return dpp_d<C, RM, BM>(v); }
 };
 
@@ -237,10 +207,6 @@ template <> struct Acc<kScanTwoSum> {
     {
         return (b.x - a.x) + (b.y - a.y);
     }
-    __device__ static A shfl_up(A v, int d)
-    {
-        return make_float2(__shfl_up(v.x, d), __shfl_up(v.y, d));
-    }
     template <int C, int RM, int BM> __device__ static A dpp(A v)
     {
         return make_float2(dpp_f<C, RM, BM>(v.x), dpp_f<C, RM, BM>(v.y));
@@ -257,40 +223,8 @@ template <> struct Acc<kScanF32> {
     __device__ static A add(A a, M m) { return a + m; }
     __device__ static A comb(A a, A b) { return a + b; }
     __device__ static D diff(A b, A a) { return b - a; }
-    __device__ static A shfl_up(A v, int d) { return __shfl_up(v, d); }
     template <int C, int RM, int BM> __device__ static A dpp(A v) { return dpp_f<C, RM, BM>(v); }
 };
-
-// Exclusive scan over the workgroup of one value per thread; also returns
-// the total.  wave_tot: LDS scratch of kBlock/64 entries.
-template <class AC>
-__device__ typename AC::A block_exscan(typename AC::A v, typename AC::A *wave_tot,
-                                       typename AC::A &total)
-{
-    using A = typename AC::A;
-    const int lane = threadIdx.x & 63;
-    const int wid = threadIdx.x >> 6;
-    A inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const A o = AC::shfl_up(inc, d);
-        if (lane >= d) inc = AC::comb(o, inc);
-    }
-    A exc = AC::shfl_up(inc, 1);
-    if (lane == 0) exc = AC::zero();
-    if (lane == 63) wave_tot[wid] = inc;
-    __syncthreads();
-    A off = AC::zero();
-    A tot = AC::zero();
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-        if (w < wid) off = AC::comb(off, wave_tot[w]);
-        tot = AC::comb(tot, wave_tot[w]);
-    }
-    total = tot;
-    __syncthreads();
-    return AC::comb(off, exc);
-}
 
 // Exclusive scan over the workgroup of one value per thread, with DPP lane
 // movements inside each wave and the wave totals combined through LDS; also

@@ -10,11 +10,9 @@
 
 namespace ram {
 
-// Destination cells per workgroup tile, threads per workgroup, and the
-// capacity (in source cells) of the LDS window that holds a tile's sources.
+// Destination cells per workgroup tile, and threads per workgroup.
 constexpr int kTile = 256;
 constexpr int kBlock = 256;
-constexpr int kWindowCap = 2048;
 // Cells per tile of the residual step alone: four per thread, with the
 // two-cell halo a side staged in one item per thread.
 constexpr int kResTile = 1020;
