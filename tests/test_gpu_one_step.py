@@ -154,3 +154,18 @@ def test_both_sides_of_the_plan(kind):
         torch.cuda.synchronize()
         out.append(q.view(r, n))
     assert torch.equal(out[0], out[1][:few])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_odd_steps_with_a_schedule(k, dtype):
+    rows, q, v0, dv, dt = inputs(1023, "runs", 3, True, dtype, 0)
+    ctx = R.context(0)
+    ctx.set_schedule(4)
+    try:
+        traj, _ = record(rows, q, v0, dv, dt, 5, k, R.RAM_SUM_DIRECT)
+        R.ram_step(rows, q, v0, dv, dt, 5, k, R.RAM_SUM_DIRECT)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_schedule(0)
+    assert torch.equal(q, traj[k])
