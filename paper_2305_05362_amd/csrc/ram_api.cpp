@@ -884,10 +884,12 @@ ram_status ram_shift_noalloc(ram_ctx *ctx, const ram_layout *layout, ram_dtype d
                     "its static buffer holds %zu",
                     cv.off, ram::kNoAllocBytes);
     if (!layout->edges_shared) {
-        // per-row meshes run k_rows, four wave tiles a table tile: its table
-        // is smaller than what was reserved above, which stays the limit
+        // per-row meshes run k_rows on the tiles that ram_shift takes for them
+        // (the prefix modes' roundings go by the tile).  Their table, 4 bytes a
+        // tile, is smaller than the table and plan of the 1019-cell tiles counted
+        // above, 24 bytes each, which stay the limit.
         Carve own;
-        rp = plan_rows(own, layout, 4 * ram::rows_tile(false), order);
+        rp = plan_rows(own, layout, step_tile_of(ctx, layout, dtype, scan, items, false), order);
     }
     ram::StepArgs a;
     if ((st = make_rows(ctx, layout, edges, rp, a.rows, mem)) != RAM_OK) return st;

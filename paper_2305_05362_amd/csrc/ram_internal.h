@@ -408,8 +408,7 @@ hipError_t launch_tiles_prep(const int64_t *row_ptr, int64_t n_rows, int tile,
 hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
                             MeshTab &tab, hipStream_t stream, bool uniform = false,
                             const CopyJob &copy = CopyJob());
-// The step on per-row meshes (ram_step_rows.hip): tiles of rows_tile cells, or
-// of a multiple of it.
+// The step on per-row meshes (ram_step_rows.hip): tiles of rows_tile cells.
 hipError_t launch_step(const StepArgs &a, bool f64, int scan, int order,
                        hipStream_t stream);
 // Shared-mesh specialisation: plan the tiles' source windows once per call

@@ -221,10 +221,9 @@ __device__ __forceinline__ void rows_wide(const double *x, const TQ *q, int n, d
     wave_sync();
 }
 
-// sub: wave tiles a table tile holds (R.tile = sub times the wave's tile).
 // NS: node slots a lane.
 template <typename TQ, int P, int S, int H, int NS>
-__global__ __launch_bounds__(kBlock, (rows_waves<TQ, S, NS>())) void k_rows(StepArgs a, int sub)
+__global__ __launch_bounds__(kBlock, (rows_waves<TQ, S, NS>())) void k_rows(StepArgs a)
 {
     using AC = Acc<S>;
     using L = RowsLds<TQ, S, NS>;
@@ -241,15 +240,14 @@ __global__ __launch_bounds__(kBlock, (rows_waves<TQ, S, NS>())) void k_rows(Step
     __shared__ short sjc_[kWaves][kLanes * NS];
     const int wid = wave_id();
     const int t = (int)threadIdx.x % kLanes;
-    const int64_t wave = (int64_t)blockIdx.x * kWaves + wid;
+    const int64_t tile = (int64_t)blockIdx.x * kWaves + wid;
     const Rows &R = a.rows;
-    const int64_t tile = sub == 1 ? wave : wave / sub;
     if (tile >= R.n_tiles) return;
     Tile ti;
     if (!get_tile(R, tile, ti)) return;
     const int n = ti.n;
-    const int i0 = ti.i0 + (int)(wave - tile * sub) * NDT;
-    if (n < P + 1 || i0 >= n) return;
+    const int i0 = ti.i0;
+    if (n < P + 1) return;
     const int nd = min(NDT, n - i0);
     const int NC = nd + 2 * H;                       // shifted cells
     const int NE = NC + 1;                           // shifted nodes
@@ -457,11 +455,11 @@ __global__ __launch_bounds__(kBlock, (rows_waves<TQ, S, NS>())) void k_rows(Step
 }
 
 template <typename TQ, int P, int S, int NS>
-hipError_t rows_ns(const StepArgs &a, int sub, hipStream_t st)
+hipError_t rows_ns(const StepArgs &a, hipStream_t st)
 {
-    const dim3 g((unsigned)((a.rows.n_tiles * sub + kWaves - 1) / kWaves)), b(kBlock);
-    if (a.dv) hipLaunchKernelGGL((k_rows<TQ, P, S, 2, NS>), g, b, 0, st, a, sub);
-    else hipLaunchKernelGGL((k_rows<TQ, P, S, 0, NS>), g, b, 0, st, a, sub);
+    const dim3 g((unsigned)((a.rows.n_tiles + kWaves - 1) / kWaves)), b(kBlock);
+    if (a.dv) hipLaunchKernelGGL((k_rows<TQ, P, S, 2, NS>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_rows<TQ, P, S, 0, NS>), g, b, 0, st, a);
     return hipGetLastError();
 }
 
@@ -469,10 +467,9 @@ template <typename TQ, int P, int S>
 hipError_t rows_h(const StepArgs &a, hipStream_t st)
 {
     const bool fused = a.dv != nullptr;
-    if (a.rows.tile == rows_tile(fused, 2)) return rows_ns<TQ, P, S, 2>(a, 1, st);
-    const int tile = rows_tile(fused);
-    if (a.rows.tile % tile != 0) return hipErrorInvalidValue;
-    return rows_ns<TQ, P, S, 4>(a, a.rows.tile / tile, st);
+    if (a.rows.tile == rows_tile(fused, 2)) return rows_ns<TQ, P, S, 2>(a, st);
+    if (a.rows.tile == rows_tile(fused, 4)) return rows_ns<TQ, P, S, 4>(a, st);
+    return hipErrorInvalidValue;
 }
 
 template <int P>
