@@ -135,6 +135,8 @@ struct MeshTabW {
     float *ppmf;
     int32_t *nonu;
     int32_t *nonu_min;
+    double2 *runs_size;
+    int2 *runs_cnt;
 };
 
 // Every table of the mesh in one launch of B-thread workgroups, each with one
@@ -144,7 +146,7 @@ struct MeshTabW {
 // node loads of about a microsecond when first touched), not bytes, so the
 // parts run side by side instead of one after the other in one thread, and
 // the run counts do not wait for a launch of their own.  B: the run counts'
-// one workgroup sets the time of long rows (it keeps its cells in registers,
+// one workgroup sets the time of rows up to kRunsAlone (it keeps its cells in registers,
 // 32 a lane at 16384 cells), four waves a workgroup are quicker to start on
 // short ones: 256 threads against 512 4.6 and 6.2 us at 2048 cells, 5.9 and
 // 6.3 at 4096, 15.5 and 7.5 at 6001, 20.5 and 12.2 at 16384.  One thread a
@@ -348,11 +350,11 @@ __device__ __forceinline__ void prep_buckets(const double *x, int n, int j, cons
 
 // Uniform runs of a shared mesh: prefix counts of the cells whose size
 // differs from the largest (nonu) and from the smallest (nonu_min) by more
-// than kUniformTol of it.  One workgroup: each of its waves takes one
-// contiguous segment of the row, whose first 64 KEEP cells it keeps in
-// registers (one load of the nodes on rows of up to B KEEP cells); both sizes by a block reduction, then each wave counts its flagged
-// cells, and after one scan of the waves' counts writes its segment's prefix
-// 64 cells at a time from one ballot per flag.
+// than kUniformTol of it.  One workgroup (rows of up to B KEEP cells): each of its
+// waves takes one contiguous segment of the row, whose cells it keeps in registers
+// (one load of the nodes); both sizes by a block reduction, then each wave counts
+// its flagged cells, and after one scan of the waves' counts writes its segment's
+// prefix 64 cells at a time from one ballot per flag.
 template <int B, int KEEP>
 __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *nonu,
                                              int32_t *nonu_min, double *sx)
@@ -374,12 +376,6 @@ __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *no
     for (int k = 0; k < KEEP; ++k) {
         mx = fmax(mx, keep[k]);                      // (clamped lanes: cells of the row as well)
         mn = fmin(mn, keep[k]);
-    }
-#pragma unroll 8
-    for (int j = a0 + 64 * KEEP + lane; j < a1; j += 64) {
-        const double d = x[j + 1] - x[j];
-        mx = fmax(mx, d);
-        mn = fmin(mn, d);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -405,12 +401,6 @@ __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *no
         const bool in = a0 + 64 * k + lane < a1;
         cx += __popcll(__ballot(in && off_max(keep[k])));
         cn += __popcll(__ballot(in && off_min(keep[k])));
-    }
-    for (int j0 = a0 + 64 * KEEP; j0 < a1; j0 += 64) {
-        const int j = min(j0 + lane, n - 1);
-        const double d = x[j + 1] - x[j];
-        cx += __popcll(__ballot(j0 + lane < a1 && off_max(d)));
-        cn += __popcll(__ballot(j0 + lane < a1 && off_min(d)));
     }
     if (lane == 0) {
         soff[wv] = cx;
@@ -441,19 +431,153 @@ __device__ __forceinline__ void prep_uniform(const double *x, int n, int32_t *no
 #pragma unroll
     for (int k = 0; k < KEEP; ++k)
         if (a0 + 64 * k < a1) put(a0 + 64 * k, keep[k]);
-    for (int j0 = a0 + 64 * KEEP; j0 < a1; j0 += 64) {
-        const int j = min(j0 + lane, n - 1);
-        put(j0, x[j + 1] - x[j]);
-    }
     if (t == 0) {
         nonu[n] = tx;
         nonu_min[n] = tn;
     }
 }
 
+// The same of a row beyond kRunsAlone cells, shared out: every workgroup takes one
+// contiguous segment.  Here its largest and smallest size; in k_runs_count the
+// row's, and its waves' flagged cells; in k_runs_write the prefix.  One shift of a
+// row of 2^20 cells: FP32 189 us, 2160 with the counts as one workgroup; three rows
+// of 100,001 cells 64 and 157.
+constexpr int kRunsB = 64 * kRunsWaves;
+__device__ __forceinline__ int runs_segment(int n, int groups)
+{
+    return ((n + groups - 1) / groups + kRunsB - 1) / kRunsB * kRunsB;
+}
+
+__device__ __forceinline__ double2 runs_reduce(double mx, double mn, double *sx)
+{
+    const int t = (int)threadIdx.x;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mx = fmax(mx, __shfl_xor(mx, o, 64));
+        mn = fmin(mn, __shfl_xor(mn, o, 64));
+    }
+    if ((t & 63) == 0) {
+        sx[t >> 6] = mx;
+        sx[kRunsWaves + (t >> 6)] = mn;
+    }
+    __syncthreads();
+    mx = sx[0];
+    mn = sx[kRunsWaves];
+#pragma unroll
+    for (int w = 1; w < kRunsWaves; ++w) {
+        mx = fmax(mx, sx[w]);
+        mn = fmin(mn, sx[kRunsWaves + w]);
+    }
+    return make_double2(mx, mn);
+}
+
+__device__ __forceinline__ void prep_runs_size(const double *x, int n, int b, int groups,
+                                               double2 *size, double *sx)
+{
+    const int seg = runs_segment(n, groups);
+    const int64_t a0 = (int64_t)b * seg;
+    const int a1 = (int)min((int64_t)n, a0 + seg);
+    double mx = 0.0, mn = __builtin_huge_val();
+#pragma unroll 4
+    for (int64_t j = a0 + threadIdx.x; j < a1; j += kRunsB) {
+        const double d = x[j + 1] - x[j];
+        mx = fmax(mx, d);
+        mn = fmin(mn, d);
+    }
+    const double2 m = runs_reduce(mx, mn, sx);
+    if (threadIdx.x == 0) size[b] = m;
+}
+
+// Cell j's flags: its size is not the largest, not the smallest (to kUniformTol of it).
+__device__ __forceinline__ void run_flags(const double *x, int64_t j, int a1, double2 h, uint64_t &fx,
+                                          uint64_t &fn)
+{
+    const bool in = j < a1;
+    const int64_t c = min(j, (int64_t)a1 - 1);
+    const double d = x[c + 1] - x[c];
+    fx = __ballot(in && fabs(d - h.x) > kUniformTol * h.x);
+    fn = __ballot(in && fabs(d - h.y) > kUniformTol * h.y);
+}
+
+__global__ __launch_bounds__(kRunsB) void k_runs_count(const double *x, int n, int groups,
+                                                       double2 *size, int2 *cnt)
+{
+    __shared__ double sx[2 * kRunsWaves];
+    const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6, b = (int)blockIdx.x;
+    static_assert(kRunsGroups <= kRunsB, "a group's sizes a thread");
+    double2 m = make_double2(0.0, __builtin_huge_val());
+    if (t < groups) m = size[t];
+    m = runs_reduce(m.x, m.y, sx);
+    if (b == 0 && t == 0) size[kRunsGroups] = m;
+    const int seg = runs_segment(n, groups), part = seg / kRunsWaves;
+    const int64_t a0 = min((int64_t)n, (int64_t)b * seg + wv * part);
+    const int a1 = (int)min((int64_t)n, a0 + part);
+    int2 c = make_int2(0, 0);
+#pragma unroll 4
+    for (int64_t j0 = a0; j0 < a1; j0 += 64) {
+        uint64_t fx, fn;
+        run_flags(x, j0 + lane, a1, m, fx, fn);
+        c.x += __popcll(fx);
+        c.y += __popcll(fn);
+    }
+    if (lane == 0) cnt[b * kRunsWaves + wv] = c;
+}
+
+__global__ __launch_bounds__(kRunsB) void k_runs_write(const double *x, int n, int groups,
+                                                       const double2 *size, const int2 *cnt,
+                                                       int32_t *nonu, int32_t *nonu_min)
+{
+    __shared__ int2 sc[kRunsWaves];
+    const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6, b = (int)blockIdx.x;
+    const double2 m = size[kRunsGroups];
+    // the flagged cells before this wave's
+    int2 c = make_int2(0, 0);
+    for (int i = t; i < b * kRunsWaves; i += kRunsB) {
+        c.x += cnt[i].x;
+        c.y += cnt[i].y;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        c.x += __shfl_xor(c.x, o, 64);
+        c.y += __shfl_xor(c.y, o, 64);
+    }
+    if (lane == 0) sc[wv] = c;
+    __syncthreads();
+    int32_t bx = 0, bn = 0;
+#pragma unroll
+    for (int w = 0; w < kRunsWaves; ++w) {
+        bx += sc[w].x;
+        bn += sc[w].y;
+        if (w < wv) {
+            bx += cnt[b * kRunsWaves + w].x;
+            bn += cnt[b * kRunsWaves + w].y;
+        }
+    }
+    const int seg = runs_segment(n, groups), part = seg / kRunsWaves;
+    const int64_t a0 = min((int64_t)n, (int64_t)b * seg + wv * part);
+    const int a1 = (int)min((int64_t)n, a0 + part);
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll 2
+    for (int64_t j0 = a0; j0 < a1; j0 += 64) {
+        uint64_t fx, fn;
+        run_flags(x, j0 + lane, a1, m, fx, fn);
+        if (j0 + lane < a1) {
+            nonu[j0 + lane] = bx + __popcll(fx & below);
+            nonu_min[j0 + lane] = bn + __popcll(fn & below);
+        }
+        bx += __popcll(fx);
+        bn += __popcll(fn);
+    }
+    if (b == groups - 1 && wv == kRunsWaves - 1 && lane == 0) {
+        nonu[n] = bx;
+        nonu_min[n] = bn;
+    }
+}
+
+// runs: workgroups that take the uniform-run counts (0: not asked for).
 template <int P, int B>
 __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTabW T,
-                                                 int uniform, unsigned groups, CopyJob copy)
+                                                 int runs, unsigned groups, CopyJob copy)
 {
     if (blockIdx.x >= groups) return copy_part(copy, blockIdx.x - groups, gridDim.x - groups);
     __shared__ double sx[B];
@@ -461,15 +585,14 @@ __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTab
     const int t = (int)threadIdx.x;
     const int nc = (n + B - 1) / B;
     int b = (int)blockIdx.x;
-    if (uniform) {
-        if (b == 0) {
-            constexpr int K1 = B == 256 ? 4 : 12, K2 = B == 256 ? 16 : 32;
-            if (n <= B * K1) prep_uniform<B, K1>(x, n, T.nonu, T.nonu_min, sx);
-            else prep_uniform<B, K2>(x, n, T.nonu, T.nonu_min, sx);
-            return;
-        }
-        --b;
+    if (b < runs) {
+        constexpr int K1 = B == 256 ? 4 : 12, K2 = B == 256 ? 16 : 32;
+        if (B == kRunsB && runs > 1) prep_runs_size(x, n, b, runs, T.runs_size, sx);
+        else if (n <= B * K1) prep_uniform<B, K1>(x, n, T.nonu, T.nonu_min, sx);
+        else prep_uniform<B, K2>(x, n, T.nonu, T.nonu_min, sx);
+        return;
     }
+    b -= runs;
     if (b < nc) {
         const int j = b * B + t;
         if (j < n) prep_sizes(x, n, j, T);
@@ -561,13 +684,19 @@ hipError_t mesh_prep_launch(const double *x, int64_t n, int order, const MeshTab
                             const CopyJob &c, hipStream_t st)
 {
     const int64_t nc = (n + B - 1) / B;
-    const unsigned gp = (unsigned)(2 * nc + ((int64_t)w.nb + B - 1) / B + (uniform ? 1 : 0));
+    const int u = uniform ? (n > kRunsAlone ? runs_groups(n) : 1) : 0;
+    const unsigned gp = (unsigned)(2 * nc + ((int64_t)w.nb + B - 1) / B + u);
     const dim3 g(gp + c.blocks(B)), b(B);
-    const int u = uniform ? 1 : 0;
     switch (order) {
     case 1: hipLaunchKernelGGL((k_mesh_prep<1, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
     case 3: hipLaunchKernelGGL((k_mesh_prep<3, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
     default: hipLaunchKernelGGL((k_mesh_prep<5, B>), g, b, 0, st, x, (int)n, w, u, gp, c); break;
+    }
+    if (u > 1) {
+        hipLaunchKernelGGL(k_runs_count, dim3(u), dim3(kRunsB), 0, st, x, (int)n, u, w.runs_size,
+                           w.runs_cnt);
+        hipLaunchKernelGGL(k_runs_write, dim3(u), dim3(kRunsB), 0, st, x, (int)n, u, w.runs_size,
+                           w.runs_cnt, w.nonu, w.nonu_min);
     }
     return hipGetLastError();
 }
@@ -601,6 +730,8 @@ hipError_t launch_mesh_prep(const double *x, int64_t n, int order, void *mem,
     w.ppmf = (float *)(p + m.ppmf);
     w.nonu = (int32_t *)(p + m.nonu);
     w.nonu_min = (int32_t *)(p + m.nonu_min);
+    w.runs_size = (double2 *)(p + m.runs_size);
+    w.runs_cnt = (int2 *)(p + m.runs_cnt);
     tab.dx = w.dx; tab.dxinv = w.dxinv; tab.hinv = w.hinv;
     tab.dxf = w.dxf; tab.dxinvf = w.dxinvf; tab.hinvf = w.hinvf;
     tab.bucket = w.bucket;

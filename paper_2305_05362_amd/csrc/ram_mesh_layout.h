@@ -14,6 +14,17 @@ constexpr int kMeshPad = 16;
 // Bytes of one record of a cell's stencil (CellRec).
 constexpr size_t kCellRecF32 = 64, kCellRecF64 = 112;
 
+// Uniform-run counts: one workgroup up to kRunsAlone cells, else runs_groups of them,
+// each with its largest and smallest size and its waves' counts kept (then the two
+// sizes of the row).
+constexpr int64_t kRunsAlone = 16384;
+constexpr int kRunsGroups = 512, kRunsWaves = 8;
+inline int runs_groups(int64_t n)
+{
+    const int64_t g = (n + 4095) / 4096;
+    return (int)(g < kRunsGroups ? g : kRunsGroups);
+}
+
 // Byte offsets, 256-byte aligned each, and the bytes of all.
 struct MeshLayout {
     size_t dx, dxinv, hinv;          // FP64 a cell
@@ -25,6 +36,7 @@ struct MeshLayout {
     size_t stp, stpd, stdv;          // stencil planes: FP32, FP64, FP32 deviations
     size_t ppmd, ppmf;               // PPM interface weights, five planes
     size_t nonu, nonu_min;           // uniform-run counts, one more than cells
+    size_t runs_size, runs_cnt;      // their groups' sizes and counts (long rows)
     size_t bytes;
 };
 
@@ -58,6 +70,9 @@ inline MeshLayout mesh_layout(int64_t n_cells)
     m.ppmf = take(20 * n);
     m.nonu = take(4 * (n + 1));
     m.nonu_min = take(4 * (n + 1));
+    const size_t groups = n_cells > kRunsAlone ? (size_t)kRunsGroups : 0;
+    m.runs_size = take(groups ? 16 * (groups + 1) : 0);
+    m.runs_cnt = take(8 * groups * kRunsWaves);
     m.bytes = off;
     return m;
 }

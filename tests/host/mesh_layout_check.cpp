@@ -8,7 +8,7 @@
 
 int main()
 {
-    for (int64_t n = 2; n < 5000; n += n < 600 ? 1 : 37) {
+    for (int64_t n = 2; n < 40000; n += n < 600 ? 1 : 37) {
         const ram::MeshLayout m = ram::mesh_layout(n);
         const size_t c = (size_t)n, pad = c + 16;
         const struct { const char *name; size_t at, need; } t[] = {
@@ -22,6 +22,8 @@ int main()
             {"stpd", m.stpd, 96 * c},      {"stdv", m.stdv, 36 * c},
             {"ppmd", m.ppmd, 40 * c},      {"ppmf", m.ppmf, 20 * c},
             {"nonu", m.nonu, 4 * (c + 1)}, {"nonu_min", m.nonu_min, 4 * (c + 1)},
+            {"runs_size", m.runs_size, n > 16384 ? 16 * 513u : 0u},
+            {"runs_cnt", m.runs_cnt, n > 16384 ? 8 * 512 * 8u : 0u},
         };
         const int k = (int)(sizeof(t) / sizeof(t[0]));
         size_t sum = 0;

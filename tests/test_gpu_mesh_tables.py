@@ -75,3 +75,32 @@ def test_tile_paths_around_one_cell(n):
                                                          (i0 - lo, i0 - lo + nd + order)))
             want.append(R.RAM_TILE_WINDOW if hit else R.RAM_TILE_UNIFORM)
         assert got.cpu().tolist() == want, (n, odd)
+
+
+# rows whose run counts are shared out over workgroups (beyond 16384 cells; from two
+# million on as many as there are), odd cells around the edges of their segments and waves
+@pytest.mark.parametrize("n", [16385, 20480, 33000, 100001, (1 << 20) + 3, (1 << 21) + 4097])
+def test_tile_paths_on_long_rows(n):
+    order, lo = 5, 2
+    rng = np.random.default_rng(n)
+    odd = np.unique(np.concatenate([[0, n - 1, 511, 512, 4095, 4096, 4097, n // 2],
+                                    rng.integers(0, n, 40)]))
+    for size in (1.01, 0.99):                        # beside the smallest, beside the largest
+        w = np.ones(n)
+        w[odd] = size
+        e = np.concatenate([[0.0], np.cumsum(w)])
+        rows = R.Rows(dev(e), 1, n, None, True)
+        got = R.context(0).ram_step_tile_paths(rows, dev(np.zeros(1)), 1.0, order, False).cpu().numpy()
+        i0 = np.arange(0, n, 256)
+        nd = np.minimum(256, n - i0)
+        # (from the sizes as the nodes have them: past a million cells the nodes' own
+        # rounding passes the tolerance of 1e-10 here and there)
+        d = np.diff(e)
+        uniform = np.zeros(len(i0), dtype=bool)
+        for h in (d.max(), d.min()):
+            flag = (np.abs(d - h) > 1e-10 * h).astype(np.int64)
+            count = np.concatenate([[0], np.cumsum(np.tile(flag, 3))])
+            uniform |= ((count[n + i0 + nd + 1] - count[n + i0 - 1]) +
+                        (count[n + i0 - lo + nd + order] - count[n + i0 - lo])) == 0
+        want = np.where(uniform, R.RAM_TILE_UNIFORM, R.RAM_TILE_WINDOW)
+        assert np.array_equal(got, want), (n, size, np.argwhere(got != want).ravel()[:10])
