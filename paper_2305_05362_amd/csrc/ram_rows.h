@@ -27,7 +27,8 @@ struct RowsWindow {
 // Brackets of the cells that hold two coordinates at once (lanes 0 to 31 search
 // for xa, the others for xb): x[lo] <= xh, or lo 0, and x[hi] > xh, or hi n, at
 // most kBracket apart.  32 nodes a side a load, so two loads deep on rows of
-// 8192 cells where a binary search is thirteen.
+// 8192 cells where a binary search is thirteen.  (At least one load: on a row of a
+// few cells the brackets would be all of it, and the window too long for it.)
 constexpr int kBracket = 8;
 __device__ __forceinline__ void find_two(const double *x, int n, double xa, double xb, int t, int &la,
                                          int &hb)
@@ -36,14 +37,14 @@ __device__ __forceinline__ void find_two(const double *x, int n, double xa, doub
     const double target = hi_half ? xb : xa;
     const double inf = __builtin_huge_val();
     int lo = 0, hi = n;
-    while (__any(hi - lo > kBracket ? 1 : 0)) {
+    do {
         const int step = max((hi - lo + 31) / 32, 1);
         const int at = lo + (t & 31) * step;
         const uint64_t m = __ballot((at < hi ? x[at] : inf) <= target);
         const int k = __popc((uint32_t)(hi_half ? m >> 32 : m));
         lo = min(lo + max(k - 1, 0) * step, n - 1);
         hi = min(hi, lo + step);
-    }
+    } while (__any(hi - lo > kBracket ? 1 : 0));
     la = __shfl(lo, 0);
     hb = __shfl(max(hi, lo + 1), 32);
 }
