@@ -620,8 +620,10 @@ __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTab
 // tiles' rows, kFillRows rows a wave, a row at a time with consecutive tiles on
 // the lanes: the fill is instruction issue, too much for one CU.  4096 rows of
 // 17 tiles on average: 10 us; 48 as one workgroup, each thread writing its own
-// rows' tiles one after the other.
+// rows' tiles one after the other.  A batch of few rows of few tiles keeps to that
+// form: 3000 rows of 6 .. 200 cells 1.2 us less of a call.
 constexpr int kFillRows = 8;
+constexpr int64_t kFillFew = 8192, kFillTiles = 8;
 __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
                                                      int64_t n_rows, int tile,
                                                      int64_t *tile_ptr,
@@ -635,9 +637,12 @@ __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
     const int64_t r0 = min(n_rows, (int64_t)t * per);
     const int64_t r1 = min(n_rows, r0 + per);
     int64_t run = 0, p0 = r0 < r1 ? row_ptr[r0] : 0;
+    bool many = n_rows > kFillFew;
     for (int64_t r = r0; r < r1; ++r) {
         const int64_t p1 = row_ptr[r + 1];
-        run += (p1 - p0 + tile - 1) / tile;
+        const int64_t k = (p1 - p0 + tile - 1) / tile;
+        run += k;
+        many = many || k > kFillTiles;
         p0 = p1;
     }
     int64_t inc = run;
@@ -647,7 +652,8 @@ __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
         if (lane >= d) inc += o;
     }
     if (lane == 63) swt[wv] = inc;
-    __syncthreads();
+    const bool own = __syncthreads_or(many ? 1 : 0) == 0;
+    if (own && blockIdx.x > 0) return;
     int64_t acc = inc - run, total = 0;
     for (int w = 0; w < 16; ++w) {
         acc += w < wv ? swt[w] : 0;
@@ -656,11 +662,15 @@ __global__ __launch_bounds__(1024) void k_tiles_prep(const int64_t *row_ptr,
     p0 = r0 < r1 ? row_ptr[r0] : 0;
     for (int64_t r = r0; r < r1; ++r) {
         const int64_t p1 = row_ptr[r + 1];
+        const int64_t to = acc + (p1 - p0 + tile - 1) / tile;
         tile_ptr[r] = acc;
-        acc += (p1 - p0 + tile - 1) / tile;
+        if (own)
+            for (int64_t i = acc; i < to; ++i) tile_row[i] = (int32_t)r;
+        acc = to;
         p0 = p1;
     }
     if (t == 1023) tile_ptr[n_rows] = total;
+    if (own) return;
     __threadfence_block();
     __syncthreads();
     const int64_t wave = (int64_t)blockIdx.x * 16 + wv;

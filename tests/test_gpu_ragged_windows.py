@@ -57,3 +57,22 @@ def test_rows_of_a_few_cells(n, order, scan, steps):
         ref = (ref * dx) / dx
     got = q.cpu().numpy().reshape(nr, n)
     assert np.array_equal(got, ref), int((got != ref).sum())
+
+
+# the tile table: one workgroup up to 8192 rows of eight tiles each, else all share the fill
+@pytest.mark.parametrize("nr,tall", [(1, 6), (3000, 20), (3000, 1016), (3000, 1017), (8192, 30), (8193, 30),
+                                     (2000, 9000)])
+def test_tile_table(nr, tall):
+    rng = np.random.default_rng(nr + tall)
+    lens = rng.integers(6, 20, nr)
+    lens[nr // 2] = tall
+    ptr = np.concatenate([[0], np.cumsum(lens)])
+    es = [W.stretched_edges(int(n), 2.0, rng) for n in lens]
+    q = rng.uniform(0.5, 2.0, int(ptr[-1]))
+    v0 = rng.uniform(-0.9, 0.9, nr)
+    wl = W.Workload("table", nr, 0, ptr, np.concatenate(es), False, q, None, v0, 1.0, 1, 1)
+    out = torch.empty(len(q), dtype=torch.float64, device=DEV)
+    R.ram_shift(R.Rows.from_workload(wl, DEV), torch.as_tensor(q, device=DEV), out,
+                torch.as_tensor(v0, device=DEV), 1.0, 1)
+    ref = oracle.shift(oracle.Rows.from_workload(wl), q, v0, 1.0, 1)
+    assert_parity(out.cpu().numpy(), ref, 1e-12, 1e-11)
