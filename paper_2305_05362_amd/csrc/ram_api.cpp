@@ -345,10 +345,10 @@ int step_tile_of(const ram_ctx *ctx, const ram_layout *L, ram_dtype dtype, ram_s
                  int items, bool fused)
 {
     // per-row meshes: batches of few waves, which latency bounds, take tiles of
-    // half the size, whose chain is shorter (FP32 two-sum with the residual: 8.2
-    // against 11.4 us a step at 16 rows of up to 200 cells, 8.8 and 12.7 at 300 of
-    // up to 600, 11.6 and 15.3 at 2000 of up to 300, 364,000 cells; FP64 sums 15.5
-    // and 17.0 there, 15.0 and 15.0 at 545,000 cells, 40.9 and 37.9 at 2.1 M)
+    // half the size, whose chain is shorter (FP32 two-sum with the residual: 8.4
+    // against 12.3 us a step at 16 rows of up to 200 cells, 9.0 and 13.7 at 300 of
+    // up to 600, 12.7 and 17.3 at 2000 of up to 300, 364,000 cells; FP64 sums 16.0
+    // and 19.0 there, 20.5 and 25.6 at 545,000 cells, 56.8 and 51.6 at 2.1 M)
     constexpr int64_t kRowsFew = 384 * 1024;
     if (!L->edges_shared) return ram::rows_tile(fused, layout_cells(L) <= kRowsFew ? 2 : 4);
     return use_fast(ctx, L, dtype, scan) ? ram::kFastTile : ram::step_tile_for(items, fused);
@@ -365,9 +365,13 @@ size_t plan_w_bytes(int64_t nt)
 // records, tile lists and node data, or the general kernel's window plan.
 // A single unlimited step has no plan: its waves make their tiles' records and
 // locate their nodes, which costs what the plan's kernels do without their
-// launches and their passes over memory.  Only FP32 batches from kAloneTiles
-// tiles up have one: their uniform tiles run faster in a kernel of their own,
-// which needs the lists.  With and without a plan, us a call, FP32 | FP64:
+// launches and their passes over memory.  FP32 batches from kAloneTiles tiles up
+// have one: what decides is the mesh, which the host does not see.  Uniform tiles
+// run faster in a kernel of their own, which needs the lists, by 7 and 19 % (70 and
+// 75, 147 and 182 us below, at 65,536 and 131,072 tiles; the bump mesh by 0 and
+// 10 %); tiles in no run lose 17 and 10 % by the plan (209 and 173, 418 and 376).
+// The line is where a batch of uniform runs starts to gain; a large stretched one
+// pays for it.  With and without a plan, us a call, FP32 | FP64:
 //                      stretched mesh         uniform mesh           bump
 //   1024 x 4096        67 50 | 100 77         32 27 | 75 71          41 35 | 81 73
 //   2048 x 8192        209 173 | 356 304      70 75 | 268 270        97 97 | 303 300

@@ -612,7 +612,7 @@ __global__ __launch_bounds__(B) void k_mesh_prep(const double *x, int n, MeshTab
 
 // ---------------------------------------------------------------------------
 // ragged-row tile table: tile_ptr[r] = sum_{r'<r} ceil(N_r'/tile) and
-// tile_row[t] = row of tile t.  One workgroup of 1024 threads.
+// tile_row[t] = row of tile t.
 // ---------------------------------------------------------------------------
 
 // Every workgroup scans all the rows' tile counts (consecutive rows a thread;

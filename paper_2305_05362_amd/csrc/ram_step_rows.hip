@@ -25,13 +25,13 @@
 //
 // VALU issue bounds it, with the chain of dependent loads that starts a wave
 // (the table, the row, its ends and nodes, two rounds of the window search, the
-// window): 1,726 VALU instructions a tile at order 5 with the residual, of
-// which the weights of its 256 nodes take about 500 and their search in LDS
-// 300.  1024 rows of 64 .. 4096 cells, FP32, two-sum, with the residual: 44 us
-// (26 of them VALU issue); with 1019-cell tiles a workgroup (27 KB of LDS,
-// seven barriers, two lanes searching the row for the window while the others
-// wait) 74.  Five waves a SIMD spill (51 us).  Small batches take two node slots
-// a lane instead of four: the chain of one wave is what they cost.
+// window): 2,034 VALU instructions a tile at order 5 with the residual, more than
+// half of them the weights of its 256 nodes (an FP64 and five FP32 divisions each)
+// and their search in LDS.  1024 rows of 64 .. 4096 cells, FP32, two-sum, with the
+// residual: 46 us (31 of them VALU issue); with 1019-cell tiles a workgroup (27 KB
+// of LDS, seven barriers, two lanes searching the row for the window while the
+// others wait) 74.  Five waves a SIMD spill (51 us; 44 at four then).  Small batches take two node
+// slots a lane instead of four: the chain of one wave is what they cost.
 #include "ram_rows.h"
 
 #include <type_traits>
