@@ -104,3 +104,9 @@ def test_tile_paths_on_long_rows(n):
                         (count[n + i0 - lo + nd + order] - count[n + i0 - lo])) == 0
         want = np.where(uniform, R.RAM_TILE_UNIFORM, R.RAM_TILE_WINDOW)
         assert np.array_equal(got, want), (n, size, np.argwhere(got != want).ravel()[:10])
+
+
+# the same where one workgroup counts, its lanes' cells flagged as bits (12 and 32 a lane)
+@pytest.mark.parametrize("n", [4100, 6144, 6145, 12001, 16384])
+def test_tile_paths_of_one_workgroups_counts(n):
+    test_tile_paths_on_long_rows(n)
